@@ -23,21 +23,42 @@ static_assert(kParams == 66435, "parameter count");
 __host__ __device__ constexpr int64_t param_offset_W(int l) { return l * kLayerParams; }
 __host__ __device__ constexpr int64_t param_offset_b(int l) { return l * kLayerParams + (int64_t)kWidth * kWidth; }
 
-hipError_t launch_rff(const float *q, int64_t n, const float *B, __bf16 *X, hipStream_t s);
-hipError_t launch_layer_fwd(const __bf16 *X, int64_t n, const __bf16 *W, const float *b, float *Z,
-                            __bf16 *H, hipStream_t s);
-hipError_t launch_layer_bwd_data(const __bf16 *dZ, int64_t n, const __bf16 *WT, const float *Zprev,
-                                 __bf16 *dZprev, hipStream_t s);
-hipError_t launch_grad_w(const __bf16 *dZ, const __bf16 *H, int64_t n, float *part, hipStream_t s);
-hipError_t launch_reduce(const float *part, int64_t slices, int64_t stride, int64_t count, float *out,
-                         hipStream_t s);
-hipError_t launch_out_fwd(const __bf16 *H, int64_t n, const float *W5, const float *b5, float *pred,
-                          hipStream_t s);
-hipError_t launch_out_bwd(const float *pred, const float *target, int64_t n, const __bf16 *H,
-                          const float *Z, const float *W5, __bf16 *dZ, float *part, hipStream_t s);
-int64_t out_blocks(int64_t n);
-hipError_t launch_adam(float *w, float *m, float *v, const float *g, int64_t count, double lr, double b1,
-                       double b2, double eps, int t, hipStream_t s);
+// Where minibatches come from: the coarse lattice's tracers (dims d, box
+// lengths L), drawn by a hash of (seed, step, sample).
+struct BatchSource {
+    const float *x, *y, *z;
+    int32_t d[3];
+    double L[3];
+    uint64_t seed;
+};
+hipError_t launch_gather_batch(const BatchSource &S, uint64_t step, int64_t nb, float *q, float *target,
+                               hipStream_t s);
+
+// Device arrays of a training step of n samples.  Feature-major arrays hold
+// ld = train_rows(n) samples per feature, zeros from n on.
+__host__ __device__ constexpr int64_t train_rows(int64_t n) { return (n + kSlice - 1) / kSlice * kSlice; }
+struct TrainNet {
+    float *master, *m, *v;   // parameters and moments
+    const float *B;          // Fourier frequencies
+    float *q, *target, *pred;  // [n][3]
+    __bf16 *Wb, *WTb;        // hidden weights in bf16, row-major and transposed
+    __bf16 *act;             // [kDepth + 1][kWidth][ld]: features, H1 .. H4
+    __bf16 *err;             // [kDepth][kWidth][ld]: dZ1 .. dZ4
+    float *dout;             // [4][ld]: the output's gradient, then the squared error
+};
+struct AdamStep {
+    float lr, b1, a1, b2, a2, eps, c1, c2;
+};
+AdamStep adam_step(double lr, double b1, double b2, double eps, int t);
+// Forward and backward of T.q against T.target: pred, act, err, dout.
+hipError_t launch_train_pass(const TrainNet &T, int64_t n, hipStream_t s);
+// After it: the gradients into grad[kParams] and the summed squared error
+// into *loss (null: not wanted); or the Adam update of T's parameters, and
+// the minibatch of step `next` (0: none) into T.q and T.target.
+hipError_t launch_train_grads(const TrainNet &T, int64_t n, float *grad, float *loss, hipStream_t s);
+hipError_t launch_train_update(const TrainNet &T, int64_t n, const AdamStep &A, float *loss, const BatchSource &S,
+                               uint64_t next, hipStream_t s);
+hipError_t launch_adam(float *w, float *m, float *v, const float *g, int64_t count, const AdamStep &A, hipStream_t s);
 hipError_t launch_cast_weights(const float *master, __bf16 *Wb, __bf16 *WTb, hipStream_t s);
 // Inference: pred[n][3] from q[n][3] in one pass (features, hidden layers
 // and output layer per 16-sample tile in registers; bf16 operands rounded
@@ -50,9 +71,6 @@ hipError_t launch_mlp_infer(const float *q, int64_t n, const float *B, const flo
 
 namespace tess {
 namespace mlp {
-hipError_t launch_gather_batch(const float *x, const float *y, const float *z, const int dims[3],
-                               const double box[3], uint64_t seed, uint64_t step, int64_t nb, float *q,
-                               float *target, hipStream_t s);
 hipError_t launch_fine_q(int64_t first, int64_t n, const int fdims[3], float *q, hipStream_t s);
 hipError_t launch_place_mlp(const float *cx, const float *cy, const float *cz, const int cdims[3], int r,
                             int64_t first, int64_t n, const float *q, const float *pred,

@@ -1,7 +1,7 @@
-// Refinement network kernels (gfx950): random Fourier features, a bf16 MFMA
-// GEMM for the four 128-wide layers (forward and backward-data), a split-K
-// MFMA GEMM for the weight gradients, the 128 -> 3 output layer, the mean
-// squared error and Adam on FP32 master weights.
+// Refinement network kernels (gfx950): the training step (forward, loss,
+// backward to the first layer in one kernel; the weight gradients with Adam
+// on FP32 master weights in another), the fused inference, and the placement
+// of the refined lattice.
 //
 // Network: g = [sin 2 pi B q, cos 2 pi B q] (B integer, 64 x 3), then four
 // times h = GELU(W h + b) (128 -> 128), then s = W5 h + b5 (128 -> 3).  The
@@ -20,6 +20,7 @@ namespace mlp {
 
 typedef __bf16 bf16;
 typedef bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 // D(16x16) += A(16x32) * B(32x16) on one wavefront.  Lane l supplies
@@ -30,311 +31,459 @@ __device__ inline floatx4 mma16(bf16x8 a, bf16x8 b, floatx4 c) {
 }
 
 __device__ inline float gelu(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
-__device__ inline float gelu_grad(float x) {
-    const float cdf = 0.5f * (1.0f + erff(x * 0.70710678118654752f));
+
+// GELU(x) and its derivative (one erf for both).
+__device__ inline void gelu_both(float x, float &h, float &g) {
+    const float p = 1.0f + erff(x * 0.70710678118654752f);
+    h = 0.5f * x * p;
     const float pdf = 0.39894228040143268f * __expf(-0.5f * x * x);
-    return cdf + x * pdf;
+    g = 0.5f * p + x * pdf;
 }
 
-// ------------------------------------------------------------------ RFF
-// X[n][f] = sin(2 pi B_f . q_n), X[n][64 + f] = cos(...), bf16.  B is integer,
-// so sinpi/cospi of 2 B.q reduce exactly for dyadic q.
-__global__ void k_rff(const float *__restrict__ q, int64_t n, const float *__restrict__ B,
-                      bf16 *__restrict__ X) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n * kFreq) return;
-    const int64_t p = idx / kFreq;
-    const int f = (int)(idx % kFreq);
-    const float t = 2.0f * (B[3 * f] * q[3 * p] + B[3 * f + 1] * q[3 * p + 1] + B[3 * f + 2] * q[3 * p + 2]);
-    X[p * kWidth + f] = (bf16)sinpif(t);
-    X[p * kWidth + kFreq + f] = (bf16)cospif(t);
+// SplitMix64 (Steele, Lea & Flood 2014): counter-based 64-bit mixer.
+__host__ __device__ inline uint64_t splitmix64(uint64_t x) {
+    uint64_t z = x + 0x9E3779B97F4A7C15ull;
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    return z ^ (z >> 31);
 }
 
-hipError_t launch_rff(const float *q, int64_t n, const float *B, bf16 *X, hipStream_t s) {
-    const int64_t total = n * kFreq;
-    hipLaunchKernelGGL(k_rff, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, q, n, B, X);
+__device__ inline double min_image(double d, double L) { return d - L * ceil(d / L - 0.5); }
+
+// Sample j of minibatch `step`: a coarse vertex drawn with replacement by a
+// counter hash, its q (unit torus) and target displacement s = (x - q L) / L,
+// minimal image.
+__device__ inline void gather_sample(const BatchSource &S, uint64_t step, int64_t j, float *__restrict__ q,
+                                     float *__restrict__ target) {
+    const int64_t n = (int64_t)S.d[0] * S.d[1] * S.d[2];
+    const int64_t id = (int64_t)(splitmix64(S.seed ^ (step * 0x100000001B3ull + (uint64_t)j)) % (uint64_t)n);
+    const int i = (int)(id % S.d[0]), jj = (int)((id / S.d[0]) % S.d[1]), k = (int)(id / ((int64_t)S.d[0] * S.d[1]));
+    const double qu[3] = {(double)i / S.d[0], (double)jj / S.d[1], (double)k / S.d[2]};
+    q[3 * j] = (float)qu[0];
+    q[3 * j + 1] = (float)qu[1];
+    q[3 * j + 2] = (float)qu[2];
+    target[3 * j] = (float)(min_image((double)S.x[id] - qu[0] * S.L[0], S.L[0]) / S.L[0]);
+    target[3 * j + 1] = (float)(min_image((double)S.y[id] - qu[1] * S.L[1], S.L[1]) / S.L[1]);
+    target[3 * j + 2] = (float)(min_image((double)S.z[id] - qu[2] * S.L[2], S.L[2]) / S.L[2]);
+}
+
+__global__ void k_gather_batch(BatchSource S, uint64_t step, int64_t nb, float *__restrict__ q,
+                               float *__restrict__ target) {
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j < nb) gather_sample(S, step, j, q, target);
+}
+
+hipError_t launch_gather_batch(const BatchSource &S, uint64_t step, int64_t nb, float *q, float *target,
+                               hipStream_t s) {
+    hipLaunchKernelGGL(k_gather_batch, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, S, step, nb, q, target);
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------ NT GEMM
-// Y[n][o] = sum_i A[n][i] * M[o][i] for a 128 x 128 bf16 matrix M (row o
-// contiguous), followed by an epilogue:
-//   EPI_FWD : Z = Y + b (FP32, optional), H = GELU(Z) (bf16)
-//   EPI_BWD : dZ = Y * GELU'(Zprev) (bf16)
-// Each wavefront owns 16-row blocks (grid-stride); M sits in LDS.
-enum { EPI_FWD = 0, EPI_BWD = 1 };
+// ------------------------------------------------------- training step
+// A training step is two launches: k_train_pass takes 32 samples per block
+// through the features, the four layers forward, the output layer, the loss
+// and back to the first layer, with every activation in LDS and registers;
+// k_train_grads sums the weight gradients and updates the parameters.  In
+// between only the activations H and the errors dZ cross memory, transposed
+// (feature-major, `ld` samples per feature), which is the layout in which
+// the gradient's contraction over the samples reads both operands in 16-byte
+// pieces.  (A launch per layer and operation, 25 a step, took 430 us a step
+// at 8192 samples: each kernel was shorter than its launch and start-up,
+// the gradients went through 34 MB of partial sums written and read back,
+// and the output layer's backward read its FP32 pre-activations row by row.)
+//
+// k_train_pass: wavefront w owns output columns 16 w .. 16 w + 15 of every
+// layer for both 16-row tiles, so that its weights are 4 KB per layer, read
+// once, a layer ahead, straight into the MFMA's B operand; GELU' of its
+// pre-activations stays in its registers for the way back.
+constexpr int kTrainRows = 32, kTrainThreads = 512;
 
-template <int EPI>
-__global__ void __launch_bounds__(256) k_gemm_nt(const bf16 *__restrict__ A, int64_t n,
-                                                 const bf16 *__restrict__ M,
-                                                 const float *__restrict__ bias,
-                                                 const float *__restrict__ Zin,
-                                                 float *__restrict__ Zout, bf16 *__restrict__ Out) {
-    constexpr int LDM = kWidth + 8;  // padded row (bf16 elements)
-    __shared__ bf16 sM[kWidth * LDM];
-    for (int e = threadIdx.x; e < kWidth * kWidth / 8; e += blockDim.x) {
-        const int r = e / (kWidth / 8), c8 = e % (kWidth / 8);
-        *(bf16x8 *)&sM[r * LDM + c8 * 8] = *(const bf16x8 *)&M[r * kWidth + c8 * 8];
+__global__ void __launch_bounds__(kTrainThreads) k_train_pass(TrainNet T, int64_t n, int64_t ld) {
+    constexpr int LDA = kWidth + 8;  // padded row (bf16 elements)
+    __shared__ bf16 sA[2][kTrainRows * LDA];
+    __shared__ float sW5[3 * kWidth + 3];
+    __shared__ float sB[3 * kFreq];
+    __shared__ float sQ[3 * kTrainRows], sE[3 * kTrainRows];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lq = lane >> 4, lk = 8 * lq;
+    const int64_t row0 = (int64_t)blockIdx.x * kTrainRows;
+    const int col = 16 * wave + lr;
+    bf16x8 w[4];  // this wavefront's columns of the next product's matrix
+    auto load_w = [&](const bf16 *M) {
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) w[ks] = *(const bf16x8 *)&M[col * kWidth + ks * 32 + lk];
+    };
+    load_w(T.Wb);
+    for (int e = threadIdx.x; e < 3 * kWidth; e += kTrainThreads) sW5[e] = (float)(bf16)T.master[kOffW5 + e];
+    if (threadIdx.x < 3) sW5[3 * kWidth + threadIdx.x] = T.master[kOffB5 + threadIdx.x];
+    if (threadIdx.x < 3 * kFreq) sB[threadIdx.x] = T.B[threadIdx.x];
+    if (threadIdx.x < 3 * kTrainRows) {
+        const int64_t e = 3 * row0 + threadIdx.x;
+        sQ[threadIdx.x] = e < 3 * n ? T.q[e] : 0.f;
     }
     __syncthreads();
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int lr = lane & 15, lk = (lane >> 4) * 8;  // operand row/col and k offset
-    const int64_t nblk = (n + 15) / 16;
-    for (int64_t blk = (int64_t)blockIdx.x * 4 + wave; blk < nblk; blk += (int64_t)gridDim.x * 4) {
-        const int64_t row0 = blk * 16;
-        // A fragments for the four 32-wide k steps
-        bf16x8 a[4];
-        const int64_t ar = row0 + lr;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            if (ar < n)
-                a[ks] = *(const bf16x8 *)&A[ar * kWidth + ks * 32 + lk];
-            else
-                a[ks] = bf16x8{};
+    // features: sin(2 pi B_f . q) and cos(...) (B is integer, so sinpi and
+    // cospi of 2 B.q reduce exactly for dyadic q)
+    {
+        const int f = threadIdx.x & (kFreq - 1);
+        for (int r = threadIdx.x >> 6; r < kTrainRows; r += kTrainThreads / 64) {
+            const float t = 2.0f * (sB[3 * f] * sQ[3 * r] + sB[3 * f + 1] * sQ[3 * r + 1] + sB[3 * f + 2] * sQ[3 * r + 2]);
+            sA[0][r * LDA + f] = (bf16)sinpif(t);
+            sA[0][r * LDA + kFreq + f] = (bf16)cospif(t);
         }
+    }
+    __syncthreads();
+    {  // transposed copy: 8 samples of one feature per thread
+        const int c = threadIdx.x >> 2, r8 = 8 * (threadIdx.x & 3);
+        bf16x8 v;
 #pragma unroll
-        for (int ot = 0; ot < kWidth / 16; ++ot) {
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < 8; ++j) v[j] = row0 + r8 + j < n ? sA[0][(r8 + j) * LDA + c] : (bf16)0.0f;
+        *(bf16x8 *)&T.act[(int64_t)c * ld + row0 + r8] = v;
+    }
+    // one product of the 32 rows in sA[cur] with this wavefront's columns
+    auto product = [&](int cur, floatx4 acc[2]) {
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) {
+            acc[rt] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
-                const bf16x8 b = *(const bf16x8 *)&sM[(ot * 16 + lr) * LDM + ks * 32 + lk];
-                acc = mma16(a[ks], b, acc);
+                const bf16x8 a = *(const bf16x8 *)&sA[cur][(rt * 16 + lr) * LDA + ks * 32 + lk];
+                acc[rt] = mma16(a, w[ks], acc[rt]);
             }
-            const int col = ot * 16 + lr;
+        }
+    };
+    // the values v of this lane's rows 16 rt + 4 lq + i: to LDS for the next
+    // product and, transposed, to memory (zeros past the last sample)
+    auto put = [&](int nxt, const float v[2][4], bf16 *__restrict__ out) {
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) {
+            bf16x4 p;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int64_t row = row0 + (lane >> 4) * 4 + i;
-                if (row >= n) continue;
-                const int64_t o = row * kWidth + col;
-                if (EPI == EPI_FWD) {
-                    const float z = acc[i] + bias[col];
-                    if (Zout) Zout[o] = z;
-                    Out[o] = (bf16)gelu(z);
-                } else {
-                    Out[o] = (bf16)(acc[i] * gelu_grad(Zin[o]));
+                const int r = 16 * rt + 4 * lq + i;
+                p[i] = (bf16)v[rt][i];
+                sA[nxt][r * LDA + col] = p[i];
+                if (row0 + r >= n) p[i] = (bf16)0.0f;
+            }
+            *(bf16x4 *)&out[(int64_t)col * ld + row0 + 16 * rt + 4 * lq] = p;
+        }
+    };
+    const int64_t plane = (int64_t)kWidth * ld;
+    float G[kDepth][2][4];
+#pragma unroll
+    for (int l = 0; l < kDepth; ++l) {
+        floatx4 acc[2];
+        product(l & 1, acc);
+        load_w(l + 1 < kDepth ? T.Wb + (size_t)(l + 1) * kWidth * kWidth : T.WTb + (size_t)l * kWidth * kWidth);
+        const float bias = T.master[param_offset_b(l) + col];
+        float v[2][4];
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) gelu_both(acc[rt][i] + bias, v[rt][i], G[l][rt][i]);
+        put(1 - (l & 1), v, T.act + (l + 1) * plane);
+        __syncthreads();
+    }
+    static_assert(kDepth % 2 == 0, "the last activations are in buffer 0");
+    // output layer, a thread per (sample, component), and the error
+    if (threadIdx.x < 3 * kTrainRows) {
+        const int r = threadIdx.x / 3, c = threadIdx.x % 3;
+        float a = 0.f;
+        for (int i = 0; i < kWidth; i += 8) {
+            const bf16x8 h = *(const bf16x8 *)&sA[0][r * LDA + i];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) a += (float)h[j] * sW5[c * kWidth + i + j];
+        }
+        const float p = a + sW5[3 * kWidth + c];
+        const int64_t e = 3 * row0 + threadIdx.x;
+        float err = 0.f;
+        if (e < 3 * n) {
+            T.pred[e] = p;
+            err = p - T.target[e];
+        }
+        sE[threadIdx.x] = err;
+    }
+    __syncthreads();
+    const float sc = 2.0f / (float)n;
+    if (threadIdx.x < kTrainRows) {
+        const float e0 = sE[3 * threadIdx.x], e1 = sE[3 * threadIdx.x + 1], e2 = sE[3 * threadIdx.x + 2];
+        T.dout[3 * ld + row0 + threadIdx.x] = e0 * e0 + e1 * e1 + e2 * e2;
+    }
+    if (threadIdx.x < 3 * kTrainRows) {
+        const int c = threadIdx.x / kTrainRows, r = threadIdx.x % kTrainRows;
+        T.dout[c * ld + row0 + r] = sc * sE[3 * r + c];
+    }
+    {
+        float v[2][4];
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int r = 16 * rt + 4 * lq + i;
+                const float d0 = sc * sE[3 * r], d1 = sc * sE[3 * r + 1], d2 = sc * sE[3 * r + 2];
+                const float g = d0 * sW5[col] + d1 * sW5[kWidth + col] + d2 * sW5[2 * kWidth + col];
+                v[rt][i] = g * G[kDepth - 1][rt][i];
+            }
+        put(1, v, T.err + (kDepth - 1) * plane);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int l = kDepth - 1; l > 0; --l) {
+        floatx4 acc[2];
+        product(l & 1, acc);
+        if (l > 1) load_w(T.WTb + (size_t)(l - 1) * kWidth * kWidth);
+        float v[2][4];
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[rt][i] = acc[rt][i] * G[l - 1][rt][i];
+        put(1 - (l & 1), v, T.err + (l - 1) * plane);
+        __syncthreads();
+    }
+}
+
+hipError_t launch_train_pass(const TrainNet &T, int64_t n, hipStream_t s) {
+    hipLaunchKernelGGL(k_train_pass, dim3((unsigned)(train_rows(n) / kTrainRows)), dim3(kTrainThreads), 0, s, T, n,
+                       train_rows(n));
+    return hipGetLastError();
+}
+
+// Weight gradients and (ADAM) the parameter update, the transposed bf16
+// copies and the next minibatch.  Sums keep one fixed order: within a slice
+// of kSlice samples by the MFMA (hidden weights) or one sample after
+// another (biases; the output layer takes slices of kOutSlice), then slice
+// after slice, in FP32.  Blocks:
+//   0 .. 255   one 16 x 16 tile of a hidden layer's weights each: the
+//              wavefronts take slices in turn, the slices' sums meet in LDS
+//              and are added there in slice order (through memory they would
+//              be 34 MB a step at 8192 samples).  A layer's tiles sit on two
+//              of the eight XCDs (blocks go round the XCDs), whose L2 then
+//              holds that layer's 4 MB of operands at 8192 samples;
+//   256 .. 287 16 biases of a hidden layer each (in the tiles' blocks their
+//              serial sums held up a row of tiles: 25 us against 19);
+//   288 .. 319 4 columns of the output layer's weights each;
+//   320        the output biases and (on request) the loss;
+//   321 ..     the next minibatch, 512 samples each.
+// The blocks read the activations and errors and write their own
+// parameters; none reads what another writes.
+constexpr int kGradThreads = 512, kGradChunk = 64, kOutSlice = 256;
+constexpr int kGradTiles = kDepth * 64, kGradBias = kGradTiles + kDepth * 8;
+constexpr int kGradOutCols = 4;  // columns of the output layer per block
+constexpr int kGradOut = kGradBias + kWidth / kGradOutCols, kGradRest = kGradOut + 1;
+
+template <bool ADAM>
+__global__ void __launch_bounds__(kGradThreads) k_train_grads(TrainNet T, int64_t n, int64_t ld, AdamStep A,
+                                                              float *__restrict__ grad, float *__restrict__ loss,
+                                                              BatchSource S, uint64_t next) {
+    constexpr int kWaves = kGradThreads / 64;
+    constexpr int LP = 256;  // sums of one slice
+    __shared__ float part[kGradChunk * LP];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lq = lane >> 4, lk = 8 * lq;
+    const int64_t plane = (int64_t)kWidth * ld;
+    // a parameter's gradient g is complete: the update, or the gradient itself
+    auto finish = [&](int64_t e, float g) -> float {
+        if constexpr (ADAM) {
+            const float mi = A.b1 * T.m[e] + A.a1 * g;
+            const float vi = A.b2 * T.v[e] + A.a2 * g * g;
+            T.m[e] = mi;
+            T.v[e] = vi;
+            float w = T.master[e];
+            w -= A.lr * (mi / A.c1) / (sqrtf(vi / A.c2) + A.eps);
+            T.master[e] = w;
+            return w;
+        } else {
+            grad[e] = g;
+            return 0.f;
+        }
+    };
+    if (blockIdx.x < kGradTiles) {
+        const int l = (int)(blockIdx.x & 7u) >> 1, tile = (int)(blockIdx.x >> 3) * 2 + (int)(blockIdx.x & 1u);
+        const int to = tile >> 3, ti = tile & 7;
+        const bf16 *dz = T.err + l * plane + (int64_t)(16 * to) * ld;
+        const bf16 *hh = T.act + l * plane + (int64_t)(16 * ti) * ld;
+        const int64_t slices = (n + kSlice - 1) / kSlice;
+        float sum = 0.f;  // thread t < 256: element t
+        for (int64_t k0 = 0; k0 < slices; k0 += kGradChunk) {
+            const int nk = (int)(slices - k0 < kGradChunk ? slices - k0 : kGradChunk);
+            // four slices' operands in flight per wavefront (one at a time
+            // waits for memory 16 times)
+            for (int kb = wave; kb < nk; kb += 4 * kWaves) {
+                bf16x8 a[4][kSlice / 32], b[4][kSlice / 32];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int k = kb + u * kWaves < nk ? kb + u * kWaves : kb;
+                    const int64_t at = (int64_t)lr * ld + (k0 + k) * kSlice + lk;
+#pragma unroll
+                    for (int ks = 0; ks < kSlice / 32; ++ks) {
+                        a[u][ks] = *(const bf16x8 *)&dz[at + 32 * ks];
+                        b[u][ks] = *(const bf16x8 *)&hh[at + 32 * ks];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int k = kb + u * kWaves;
+                    if (k >= nk) break;
+                    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ks = 0; ks < kSlice / 32; ++ks) acc = mma16(a[u][ks], b[u][ks], acc);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) part[k * LP + (4 * lq + i) * 16 + lr] = acc[i];
                 }
             }
+            __syncthreads();
+            if (threadIdx.x < 256)
+#pragma unroll 8
+                for (int k = 0; k < nk; ++k) sum += part[k * LP + threadIdx.x];
+            __syncthreads();
         }
+        if (threadIdx.x < 256) {
+            const int r = 16 * to + (threadIdx.x >> 4), c = 16 * ti + (threadIdx.x & 15);
+            const float w = finish(param_offset_W(l) + r * kWidth + c, sum);
+            if constexpr (ADAM) {
+                T.Wb[(size_t)l * kWidth * kWidth + r * kWidth + c] = (bf16)w;
+                T.WTb[(size_t)l * kWidth * kWidth + c * kWidth + r] = (bf16)w;
+            }
+        }
+        return;
     }
-}
-
-static int gemm_blocks(int64_t n) {
-    const int64_t nblk = (n + 15) / 16;
-    const int64_t want = (nblk + 3) / 4;
-    return (int)(want < 4096 ? (want > 0 ? want : 1) : 4096);
-}
-
-hipError_t launch_layer_fwd(const bf16 *X, int64_t n, const bf16 *W, const float *b, float *Z,
-                            bf16 *H, hipStream_t s) {
-    hipLaunchKernelGGL(k_gemm_nt<EPI_FWD>, dim3(gemm_blocks(n)), dim3(256), 0, s, X, n, W, b,
-                       (const float *)nullptr, Z, H);
-    return hipGetLastError();
-}
-
-hipError_t launch_layer_bwd_data(const bf16 *dZ, int64_t n, const bf16 *WT, const float *Zprev,
-                                 bf16 *dZprev, hipStream_t s) {
-    hipLaunchKernelGGL(k_gemm_nt<EPI_BWD>, dim3(gemm_blocks(n)), dim3(256), 0, s, dZ, n, WT,
-                       (const float *)nullptr, Zprev, (float *)nullptr, dZprev);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------ weight gradient
-// Partial dW[o][i] = sum over the slice's rows n of dZ[n][o] * H[n][i], and
-// partial db[o] = sum dZ[n][o].  Slice rows are transposed into LDS so both
-// MFMA operands are contiguous: A = dZ^T (o x n), B[n][i] = H[n][i] read as
-// H^T rows.  Output: part[slice][128 * 128 + 128].
-__global__ void __launch_bounds__(256) k_grad_w(const bf16 *__restrict__ dZ,
-                                                const bf16 *__restrict__ H, int64_t n,
-                                                float *__restrict__ part) {
-    constexpr int LD = kSlice + 8;
-    __shared__ bf16 sZT[kWidth * LD];
-    __shared__ bf16 sHT[kWidth * LD];
-    const int64_t r0 = (int64_t)blockIdx.x * kSlice;
-    for (int e = threadIdx.x; e < kSlice * kWidth; e += blockDim.x) {
-        const int r = e / kWidth, c = e % kWidth;
-        const int64_t g = r0 + r;
-        const bf16 z = g < n ? dZ[g * kWidth + c] : (bf16)0.0f;
-        const bf16 h = g < n ? H[g * kWidth + c] : (bf16)0.0f;
-        sZT[c * LD + r] = z;
-        sHT[c * LD + r] = h;
-    }
-    __syncthreads();
-    float *out = part + (size_t)blockIdx.x * (kWidth * kWidth + kWidth);
-    if (threadIdx.x < kWidth) {
-        float s = 0.f;
-        for (int r = 0; r < kSlice; ++r) s += (float)sZT[threadIdx.x * LD + r];
-        out[kWidth * kWidth + threadIdx.x] = s;
-    }
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int lr = lane & 15, lk = (lane >> 4) * 8;
-    // 64 output tiles (8 x 8 of 16 x 16); wave w takes tile rows 2w, 2w+1
-#pragma unroll 1
-    for (int tt = 0; tt < 16; ++tt) {
-        const int to = wave * 2 + tt / 8, ti = tt % 8;
-        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    if (blockIdx.x < kGradBias) {
+        // 16 biases of a hidden layer
+        const int l = (int)(blockIdx.x - kGradTiles) >> 3, o0 = 16 * ((int)(blockIdx.x - kGradTiles) & 7);
+        const bf16 *dz = T.err + l * plane + (int64_t)o0 * ld;
+        const int64_t slices = (n + kSlice - 1) / kSlice;
+        float sum = 0.f;
+        for (int64_t k0 = 0; k0 < slices; k0 += kGradChunk) {
+            const int nk = (int)(slices - k0 < kGradChunk ? slices - k0 : kGradChunk);
+            for (int c = threadIdx.x; c < 16 * nk; c += kGradThreads) {
+                const int o = c / nk, k = c - o * nk;
+                bf16x8 v[kSlice / 8];
 #pragma unroll
-        for (int ks = 0; ks < kSlice / 32; ++ks) {
-            const bf16x8 a = *(const bf16x8 *)&sZT[(to * 16 + lr) * LD + ks * 32 + lk];
-            const bf16x8 b = *(const bf16x8 *)&sHT[(ti * 16 + lr) * LD + ks * 32 + lk];
-            acc = mma16(a, b, acc);
-        }
+                for (int j = 0; j < kSlice / 8; ++j)
+                    v[j] = *(const bf16x8 *)&dz[(int64_t)o * ld + (k0 + k) * kSlice + 8 * j];
+                float s = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int o = to * 16 + (lane >> 4) * 4 + i, c = ti * 16 + lr;
-            out[o * kWidth + c] = acc[i];
+                for (int j = 0; j < kSlice; ++j) s += (float)v[j >> 3][j & 7];
+                part[k * LP + o] = s;
+            }
+            __syncthreads();
+            if (threadIdx.x < 16)
+#pragma unroll 8
+                for (int k = 0; k < nk; ++k) sum += part[k * LP + threadIdx.x];
+            __syncthreads();
         }
+        if (threadIdx.x < 16) finish(param_offset_b(l) + o0 + threadIdx.x, sum);
+        return;
     }
-}
-
-hipError_t launch_grad_w(const bf16 *dZ, const bf16 *H, int64_t n, float *part, hipStream_t s) {
-    const int64_t slices = (n + kSlice - 1) / kSlice;
-    hipLaunchKernelGGL(k_grad_w, dim3((unsigned)slices), dim3(256), 0, s, dZ, H, n, part);
-    return hipGetLastError();
-}
-
-// Deterministic sum over slices: out[e] = sum_s part[s][e].
-__global__ void k_reduce_slices(const float *__restrict__ part, int64_t slices, int64_t stride,
-                                int64_t count, float *__restrict__ out) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= count) return;
-    float s = 0.f;
-    for (int64_t k = 0; k < slices; ++k) s += part[k * stride + e];
-    out[e] = s;
-}
-
-hipError_t launch_reduce(const float *part, int64_t slices, int64_t stride, int64_t count, float *out,
-                         hipStream_t s) {
-    hipLaunchKernelGGL(k_reduce_slices, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, part,
-                       slices, stride, count, out);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------- output layer
-// pred[n][c] = sum_i H4[n][i] W5[c][i] + b5[c]; one thread per sample.
-__global__ void k_out_fwd(const bf16 *__restrict__ H, int64_t n, const float *__restrict__ W5,
-                          const float *__restrict__ b5, float *__restrict__ pred) {
-    __shared__ float sW[3 * kWidth + 3];
-    for (int e = threadIdx.x; e < 3 * kWidth; e += blockDim.x) sW[e] = (float)(bf16)W5[e];
-    if (threadIdx.x < 3) sW[3 * kWidth + threadIdx.x] = b5[threadIdx.x];
-    __syncthreads();
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    float a0 = 0.f, a1 = 0.f, a2 = 0.f;
-    for (int i = 0; i < kWidth; i += 8) {
-        const bf16x8 h = *(const bf16x8 *)&H[p * kWidth + i];
+    const int64_t oslices = (n + kOutSlice - 1) / kOutSlice;
+    if (blockIdx.x < kGradOut) {
+        // dW5[c][i] = sum of d[c] H4[i] over the samples
+        constexpr int NC = kGradOutCols;
+        const int i0 = NC * (int)(blockIdx.x - kGradBias);
+        const bf16 *h4 = T.act + kDepth * plane;
+        float sum = 0.f;
+        for (int64_t k0 = 0; k0 < oslices; k0 += kGradChunk) {
+            const int nk = (int)(oslices - k0 < kGradChunk ? oslices - k0 : kGradChunk);
+            for (int t = threadIdx.x; t < 3 * NC * nk; t += kGradThreads) {
+                const int e = t % (3 * NC), k = t / (3 * NC), c = e / NC;
+                const int64_t r0 = (k0 + k) * kOutSlice;
+                const bf16 *hp = h4 + (int64_t)(i0 + e % NC) * ld;
+                const float *dp = T.dout + c * ld;
+                float s = 0.f;
+                // 32 samples' loads together (ld is a multiple of 64, zeros from n on)
+                for (int r = 0; r < kOutSlice && r0 + r < ld; r += 32) {
+                    bf16x8 v[4];
+                    floatx4 d[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float x = (float)h[j];
-            a0 += x * sW[i + j];
-            a1 += x * sW[kWidth + i + j];
-            a2 += x * sW[2 * kWidth + i + j];
+                    for (int j = 0; j < 4; ++j) v[j] = *(const bf16x8 *)&hp[r0 + r + 8 * j];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) d[j] = *(const floatx4 *)&dp[r0 + r + 4 * j];
+#pragma unroll
+                    for (int j = 0; j < 32; ++j) s += d[j >> 2][j & 3] * (float)v[j >> 3][j & 7];
+                }
+                part[k * LP + e] = s;
+            }
+            __syncthreads();
+            if (threadIdx.x < 3 * NC)
+#pragma unroll 8
+                for (int k = 0; k < nk; ++k) sum += part[k * LP + threadIdx.x];
+            __syncthreads();
         }
+        if (threadIdx.x < 3 * NC) finish(kOffW5 + threadIdx.x / NC * kWidth + i0 + threadIdx.x % NC, sum);
+        return;
     }
-    pred[3 * p] = a0 + sW[3 * kWidth];
-    pred[3 * p + 1] = a1 + sW[3 * kWidth + 1];
-    pred[3 * p + 2] = a2 + sW[3 * kWidth + 2];
+    if (blockIdx.x == kGradOut) {
+        // sums of the rows of dout: the three output biases, then the loss
+        const int rows = loss ? 4 : 3;
+        float sum = 0.f;
+        for (int64_t k0 = 0; k0 < oslices; k0 += kGradChunk) {
+            const int nk = (int)(oslices - k0 < kGradChunk ? oslices - k0 : kGradChunk);
+            for (int t = threadIdx.x; t < rows * nk; t += kGradThreads) {
+                const int c = t % rows, k = t / rows;
+                const int64_t r0 = (k0 + k) * kOutSlice;
+                float s = 0.f;
+                for (int r = 0; r < kOutSlice && r0 + r < ld; r += 64) {
+                    floatx4 v[16];
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) v[j] = *(const floatx4 *)&T.dout[c * ld + r0 + r + 4 * j];
+#pragma unroll
+                    for (int j = 0; j < 64; ++j) s += v[j >> 2][j & 3];
+                }
+                part[k * LP + c] = s;
+            }
+            __syncthreads();
+            if (threadIdx.x < rows)
+                for (int k = 0; k < nk; ++k) sum += part[k * LP + threadIdx.x];
+            __syncthreads();
+        }
+        if (threadIdx.x < 3) finish(kOffB5 + threadIdx.x, sum);
+        else if (threadIdx.x == 3 && loss) *loss = sum;
+        return;
+    }
+    if constexpr (ADAM) {
+        const int64_t j = (int64_t)(blockIdx.x - kGradRest) * kGradThreads + threadIdx.x;
+        if (j < n) gather_sample(S, next, j, T.q, T.target);
+    }
 }
 
-hipError_t launch_out_fwd(const bf16 *H, int64_t n, const float *W5, const float *b5, float *pred,
-                          hipStream_t s) {
-    hipLaunchKernelGGL(k_out_fwd, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, H, n, W5, b5,
-                       pred);
+hipError_t launch_train_grads(const TrainNet &T, int64_t n, float *grad, float *loss, hipStream_t s) {
+    hipLaunchKernelGGL(k_train_grads<false>, dim3(kGradRest), dim3(kGradThreads), 0, s, T, n, train_rows(n), AdamStep{},
+                       grad, loss, BatchSource{}, (uint64_t)0);
     return hipGetLastError();
 }
 
-// Loss terms and the output-layer backward, per block of 256 samples:
-//   d = 2 (pred - target) / n,  dZ4[p][i] = (sum_c d[c] W5[c][i]) GELU'(Z4[p][i]),
-//   part[blk] = {sum |pred - target|^2, dW5 partial (3 x 128), db5 partial (3)}.
-constexpr int kOutBlk = 256;
-__global__ void __launch_bounds__(kOutBlk) k_out_bwd(const float *__restrict__ pred,
-                                                     const float *__restrict__ target, int64_t n,
-                                                     const bf16 *__restrict__ H, const float *__restrict__ Z,
-                                                     const float *__restrict__ W5,
-                                                     bf16 *__restrict__ dZ, float *__restrict__ part) {
-    __shared__ float sW[3 * kWidth];
-    __shared__ float sd[kOutBlk * 3];
-    __shared__ float sl[kOutBlk];
-    for (int e = threadIdx.x; e < 3 * kWidth; e += blockDim.x) sW[e] = (float)(bf16)W5[e];
-    const int64_t p = (int64_t)blockIdx.x * kOutBlk + threadIdx.x;
-    float d0 = 0.f, d1 = 0.f, d2 = 0.f, l = 0.f;
-    if (p < n) {
-        const float e0 = pred[3 * p] - target[3 * p];
-        const float e1 = pred[3 * p + 1] - target[3 * p + 1];
-        const float e2 = pred[3 * p + 2] - target[3 * p + 2];
-        l = e0 * e0 + e1 * e1 + e2 * e2;
-        const float sc = 2.0f / (float)n;
-        d0 = sc * e0; d1 = sc * e1; d2 = sc * e2;
-    }
-    sd[3 * threadIdx.x] = d0;
-    sd[3 * threadIdx.x + 1] = d1;
-    sd[3 * threadIdx.x + 2] = d2;
-    sl[threadIdx.x] = l;
-    __syncthreads();
-    if (p < n) {
-        for (int i = 0; i < kWidth; ++i) {
-            const float g = d0 * sW[i] + d1 * sW[kWidth + i] + d2 * sW[2 * kWidth + i];
-            dZ[p * kWidth + i] = (bf16)(g * gelu_grad(Z[p * kWidth + i]));
-        }
-    }
-    // partial dW5[c][i] = sum over the block's samples of d[c] H[p][i]
-    float *out = part + (size_t)blockIdx.x * kOutPart;
-    const int64_t p0 = (int64_t)blockIdx.x * kOutBlk;
-    for (int e = threadIdx.x; e < 3 * kWidth; e += blockDim.x) {
-        const int c = e / kWidth, i = e % kWidth;
-        float s = 0.f;
-        for (int r = 0; r < kOutBlk; ++r) {
-            if (p0 + r >= n) break;
-            s += sd[3 * r + c] * (float)H[(p0 + r) * kWidth + i];
-        }
-        out[1 + e] = s;
-    }
-    if (threadIdx.x < 3) {
-        float s = 0.f;
-        for (int r = 0; r < kOutBlk; ++r) s += sd[3 * r + threadIdx.x];
-        out[1 + 3 * kWidth + threadIdx.x] = s;
-    }
-    if (threadIdx.x == 0) {
-        float s = 0.f;
-        for (int r = 0; r < kOutBlk; ++r) s += sl[r];
-        out[0] = s;
-    }
-}
-
-hipError_t launch_out_bwd(const float *pred, const float *target, int64_t n, const bf16 *H,
-                          const float *Z, const float *W5, bf16 *dZ, float *part, hipStream_t s) {
-    hipLaunchKernelGGL(k_out_bwd, dim3((unsigned)((n + kOutBlk - 1) / kOutBlk)), dim3(kOutBlk), 0, s,
-                       pred, target, n, H, Z, W5, dZ, part);
+hipError_t launch_train_update(const TrainNet &T, int64_t n, const AdamStep &A, float *loss, const BatchSource &S,
+                               uint64_t next, hipStream_t s) {
+    const int64_t more = next ? (n + kGradThreads - 1) / kGradThreads : 0;
+    hipLaunchKernelGGL(k_train_grads<true>, dim3((unsigned)(kGradRest + more)), dim3(kGradThreads), 0, s, T, n,
+                       train_rows(n), A, (float *)nullptr, loss, S, next);
     return hipGetLastError();
 }
-
-int64_t out_blocks(int64_t n) { return (n + kOutBlk - 1) / kOutBlk; }
 
 // ----------------------------------------------------------------- Adam
-// In-place Adam on the FP32 master parameters (bias-corrected, step t >= 1).
 // a1 = 1 - b1, a2 = 1 - b2 and the bias corrections c = 1 - b^t come from
 // the host in FP64: in FP32 each difference cancels several digits (with
 // b2 = 0.999, 1 - b2^t at small t keeps only about 4 of them)
+AdamStep adam_step(double lr, double b1, double b2, double eps, int t) {
+    const double c1 = 1.0 - std::pow(b1, (double)t), c2 = 1.0 - std::pow(b2, (double)t);
+    return AdamStep{(float)lr, (float)b1, (float)(1.0 - b1), (float)b2, (float)(1.0 - b2), (float)eps, (float)c1,
+                    (float)c2};
+}
+
+// In-place Adam on FP32 master parameters (bias-corrected, step t >= 1).
 __global__ void k_adam(float *__restrict__ w, float *__restrict__ m, float *__restrict__ v,
-                       const float *__restrict__ g, int64_t count, float lr, float b1, float a1, float b2,
-                       float a2, float eps, float c1, float c2) {
+                       const float *__restrict__ g, int64_t count, AdamStep A) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= count) return;
     const float gi = g[e];
-    const float mi = b1 * m[e] + a1 * gi;
-    const float vi = b2 * v[e] + a2 * gi * gi;
+    const float mi = A.b1 * m[e] + A.a1 * gi;
+    const float vi = A.b2 * v[e] + A.a2 * gi * gi;
     m[e] = mi;
     v[e] = vi;
-    w[e] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    w[e] -= A.lr * (mi / A.c1) / (sqrtf(vi / A.c2) + A.eps);
 }
 
-hipError_t launch_adam(float *w, float *m, float *v, const float *g, int64_t count, double lr, double b1,
-                       double b2, double eps, int t, hipStream_t s) {
-    const double c1 = 1.0 - std::pow(b1, (double)t), c2 = 1.0 - std::pow(b2, (double)t);
-    hipLaunchKernelGGL(k_adam, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, w, m, v, g, count,
-                       (float)lr, (float)b1, (float)(1.0 - b1), (float)b2, (float)(1.0 - b2), (float)eps,
-                       (float)c1, (float)c2);
+hipError_t launch_adam(float *w, float *m, float *v, const float *g, int64_t count, const AdamStep &A,
+                       hipStream_t s) {
+    hipLaunchKernelGGL(k_adam, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, w, m, v, g, count, A);
     return hipGetLastError();
 }
 
@@ -487,44 +636,6 @@ namespace tess {
 namespace mlp {
 
 // ------------------------------------------------------ refinement glue
-// SplitMix64 (Steele, Lea & Flood 2014): counter-based 64-bit mixer.
-__host__ __device__ inline uint64_t splitmix64(uint64_t x) {
-    uint64_t z = x + 0x9E3779B97F4A7C15ull;
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    return z ^ (z >> 31);
-}
-
-__device__ inline double min_image(double d, double L) { return d - L * ceil(d / L - 0.5); }
-
-// Minibatch of `nb` coarse vertices drawn with replacement by a counter hash:
-// q (unit torus) and the target displacement s = (x - q L) / L, minimal image.
-__global__ void k_gather_batch(const float *__restrict__ x, const float *__restrict__ y,
-                               const float *__restrict__ z, int d0, int d1, int d2, double L0,
-                               double L1, double L2, uint64_t seed, uint64_t step, int64_t nb,
-                               float *__restrict__ q, float *__restrict__ target) {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= nb) return;
-    const int64_t n = (int64_t)d0 * d1 * d2;
-    const int64_t id = (int64_t)(splitmix64(seed ^ (step * 0x100000001B3ull + (uint64_t)j)) % (uint64_t)n);
-    const int i = (int)(id % d0), jj = (int)((id / d0) % d1), k = (int)(id / ((int64_t)d0 * d1));
-    const double qu[3] = {(double)i / d0, (double)jj / d1, (double)k / d2};
-    q[3 * j] = (float)qu[0];
-    q[3 * j + 1] = (float)qu[1];
-    q[3 * j + 2] = (float)qu[2];
-    target[3 * j] = (float)(min_image((double)x[id] - qu[0] * L0, L0) / L0);
-    target[3 * j + 1] = (float)(min_image((double)y[id] - qu[1] * L1, L1) / L1);
-    target[3 * j + 2] = (float)(min_image((double)z[id] - qu[2] * L2, L2) / L2);
-}
-
-hipError_t launch_gather_batch(const float *x, const float *y, const float *z, const int dims[3],
-                               const double box[3], uint64_t seed, uint64_t step, int64_t nb, float *q,
-                               float *target, hipStream_t s) {
-    hipLaunchKernelGGL(k_gather_batch, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, x, y, z,
-                       dims[0], dims[1], dims[2], box[0], box[1], box[2], seed, step, nb, q, target);
-    return hipGetLastError();
-}
-
 // Unit-torus coordinates of fine vertices first .. first + n - 1 (id order).
 __global__ void k_fine_q(int64_t first, int64_t n, int f0, int f1, int f2, float *__restrict__ q) {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

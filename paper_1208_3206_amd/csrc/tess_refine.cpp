@@ -34,26 +34,24 @@ double normal(uint64_t seed, uint64_t ctr) {  // Box-Muller
 }
 
 // Device state of one network: parameters, optimiser moments, bf16 copies and
-// the activations of one batch of up to `cap` samples.
+// the activations of one batch.
 struct Net {
     DevBuf<float> master, m, v, grad, B;
-    DevBuf<__bf16> Wb, WTb;
-    DevBuf<float> q, target, pred, part, outpart;
-    DevBuf<__bf16> X, H[kDepth], dZ[2];
-    DevBuf<float> Z[kDepth];
-    int64_t cap = 0;
+    DevBuf<__bf16> Wb, WTb, act, err;
+    DevBuf<float> q, target, pred, dout;
     ~Net() {
         master.release(); m.release(); v.release(); grad.release(); B.release();
-        Wb.release(); WTb.release(); q.release(); target.release(); pred.release();
-        part.release(); outpart.release(); X.release(); dZ[0].release(); dZ[1].release();
-        for (int l = 0; l < kDepth; ++l) { H[l].release(); Z[l].release(); }
+        Wb.release(); WTb.release(); act.release(); err.release();
+        q.release(); target.release(); pred.release(); dout.release();
+    }
+    TrainNet train() {
+        return TrainNet{master.p, m.p, v.p, B.p, q.p, target.p, pred.p, Wb.p, WTb.p, act.p, err.p, dout.p};
     }
 };
 
-// Training buffers (activations, gradient partials) for batches of up to
-// `batch` samples when `train`; the sample and prediction buffers hold the
-// larger of that and `infer_cap`, the chunk of the fused inference, which
-// needs nothing else.
+// Training buffers (activations, moments) for batches of `batch` samples when
+// `train`; the sample and prediction buffers hold the larger of that and
+// `infer_cap`, the chunk of the fused inference, which needs nothing else.
 tess_status net_alloc(Net &net, int64_t batch, bool train, int64_t infer_cap = 0) {
     const int64_t cap = std::max(train ? batch : (int64_t)0, infer_cap);
     TESS_HIP(net.master.ensure(kParams));
@@ -61,63 +59,17 @@ tess_status net_alloc(Net &net, int64_t batch, bool train, int64_t infer_cap = 0
     TESS_HIP(net.q.ensure((size_t)3 * cap));
     TESS_HIP(net.pred.ensure((size_t)3 * cap));
     if (train) {
+        const size_t ld = (size_t)train_rows(batch);
         TESS_HIP(net.grad.ensure(kParams));
         TESS_HIP(net.m.ensure(kParams));
         TESS_HIP(net.v.ensure(kParams));
         TESS_HIP(net.Wb.ensure((size_t)kDepth * kWidth * kWidth));
         TESS_HIP(net.WTb.ensure((size_t)kDepth * kWidth * kWidth));
         TESS_HIP(net.target.ensure((size_t)3 * batch));
-        TESS_HIP(net.X.ensure((size_t)kWidth * batch));
-        for (int l = 0; l < kDepth; ++l) {
-            TESS_HIP(net.H[l].ensure((size_t)kWidth * batch));
-            TESS_HIP(net.Z[l].ensure((size_t)kWidth * batch));
-        }
-        TESS_HIP(net.dZ[0].ensure((size_t)kWidth * batch));
-        TESS_HIP(net.dZ[1].ensure((size_t)kWidth * batch));
-        const int64_t slices = (batch + kSlice - 1) / kSlice;
-        TESS_HIP(net.part.ensure((size_t)slices * (kWidth * kWidth + kWidth)));
-        TESS_HIP(net.outpart.ensure((size_t)out_blocks(batch) * kOutPart));
+        TESS_HIP(net.act.ensure((size_t)(kDepth + 1) * kWidth * ld));
+        TESS_HIP(net.err.ensure((size_t)kDepth * kWidth * ld));
+        TESS_HIP(net.dout.ensure(4 * ld));
     }
-    net.cap = cap;
-    return TESS_OK;
-}
-
-// Forward pass over net.q[0 .. n); with `train` the pre-activations are kept.
-tess_status net_forward(Net &net, int64_t n, bool train, hipStream_t s) {
-    TESS_HIP(launch_rff(net.q.p, n, net.B.p, net.X.p, s));
-    for (int l = 0; l < kDepth; ++l) {
-        const __bf16 *in = l == 0 ? net.X.p : net.H[l - 1].p;
-        TESS_HIP(launch_layer_fwd(in, n, net.Wb.p + (size_t)l * kWidth * kWidth,
-                                  net.master.p + param_offset_b(l), train ? net.Z[l].p : nullptr,
-                                  net.H[l].p, s));
-    }
-    TESS_HIP(launch_out_fwd(net.H[kDepth - 1].p, n, net.master.p + kOffW5, net.master.p + kOffB5,
-                            net.pred.p, s));
-    return TESS_OK;
-}
-
-// Backward pass after net_forward(train): fills net.grad; the summed squared
-// error lands in net.grad's scratch tail read by the caller (see loss_sum).
-tess_status net_backward(Net &net, int64_t n, float *loss_sum, hipStream_t s) {
-    TESS_HIP(launch_out_bwd(net.pred.p, net.target.p, n, net.H[kDepth - 1].p, net.Z[kDepth - 1].p,
-                            net.master.p + kOffW5, net.dZ[0].p, net.outpart.p, s));
-    int cur = 0;
-    const int64_t slices = (n + kSlice - 1) / kSlice;
-    for (int l = kDepth - 1; l >= 0; --l) {
-        const __bf16 *hin = l == 0 ? net.X.p : net.H[l - 1].p;
-        TESS_HIP(launch_grad_w(net.dZ[cur].p, hin, n, net.part.p, s));
-        TESS_HIP(launch_reduce(net.part.p, slices, kLayerParams, kLayerParams,
-                               net.grad.p + param_offset_W(l), s));
-        if (l > 0) {
-            TESS_HIP(launch_layer_bwd_data(net.dZ[cur].p, n, net.WTb.p + (size_t)l * kWidth * kWidth,
-                                           net.Z[l - 1].p, net.dZ[1 - cur].p, s));
-            cur = 1 - cur;
-        }
-    }
-    // output layer: [loss, dW5, db5] summed over blocks; dW5/db5 land in grad
-    const int64_t ob = out_blocks(n);
-    TESS_HIP(launch_reduce(net.outpart.p + 1, ob, kOutPart, kOutPart - 1, net.grad.p + kOffW5, s));
-    if (loss_sum) TESS_HIP(launch_reduce(net.outpart.p, ob, kOutPart, 1, loss_sum, s));
     return TESS_OK;
 }
 
@@ -175,11 +127,10 @@ extern "C" tess_status tess_mlp_loss_grad(const float *params, const float *rff_
     TESS_HIP(hipMemcpyAsync(net.q.p, q, sizeof(float) * 3 * n, hipMemcpyDeviceToDevice, s));
     TESS_HIP(hipMemcpyAsync(net.target.p, target, sizeof(float) * 3 * n, hipMemcpyDeviceToDevice, s));
     TESS_HIP(launch_cast_weights(net.master.p, net.Wb.p, net.WTb.p, s));
-    st = net_forward(net, n, true, s);
-    if (st != TESS_OK) return st;
+    const TrainNet T = net.train();
     float *dloss = net.m.p;  // scratch: one float
-    st = net_backward(net, n, dloss, s);
-    if (st != TESS_OK) return st;
+    TESS_HIP(launch_train_pass(T, n, s));
+    TESS_HIP(launch_train_grads(T, n, net.grad.p, dloss, s));
     float lsum = 0.f;
     TESS_HIP(hipMemcpyAsync(&lsum, dloss, sizeof(float), hipMemcpyDeviceToHost, s));
     if (grad) TESS_HIP(hipMemcpyAsync(grad, net.grad.p, sizeof(float) * kParams, hipMemcpyDeviceToHost, s));
@@ -223,7 +174,7 @@ extern "C" tess_status tess_mlp_adam(float *params, float *m, float *v, const fl
         TESS_HIP(hipMemcpyAsync(dm, m, sizeof(float) * kParams, hipMemcpyHostToDevice, s));
         TESS_HIP(hipMemcpyAsync(dv, v, sizeof(float) * kParams, hipMemcpyHostToDevice, s));
         TESS_HIP(hipMemcpyAsync(dg, grad, sizeof(float) * kParams, hipMemcpyHostToDevice, s));
-        TESS_HIP(launch_adam(dp, dm, dv, dg, kParams, lr, beta1, beta2, eps, step, s));
+        TESS_HIP(launch_adam(dp, dm, dv, dg, kParams, adam_step(lr, beta1, beta2, eps, step), s));
         TESS_HIP(hipMemcpyAsync(params, dp, sizeof(float) * kParams, hipMemcpyDeviceToHost, s));
         TESS_HIP(hipMemcpyAsync(m, dm, sizeof(float) * kParams, hipMemcpyDeviceToHost, s));
         TESS_HIP(hipMemcpyAsync(v, dv, sizeof(float) * kParams, hipMemcpyDeviceToHost, s));
@@ -311,26 +262,30 @@ extern "C" tess_status tess_refine(tess_lattice coarse, const tess_refine_desc *
         auto t0 = std::chrono::steady_clock::now();
         float lsum = 0.f;
         const int64_t nb = d->batch;
+        BatchSource src{coarse->x, coarse->y, coarse->z, {cd[0], cd[1], cd[2]}, {box[0], box[1], box[2]}, d->seed + 1};
+        if (train && launch_gather_batch(src, 1, nb, net.q.p, net.target.p, s) != hipSuccess) {
+            (void)hipFree(dloss);
+            return fail_free(fail(TESS_EHIP, "batch gather failed"));
+        }
         for (int step = 1; step <= d->steps; ++step) {
-            if (launch_gather_batch(coarse->x, coarse->y, coarse->z, cd, box, d->seed + 1, (uint64_t)step, nb,
-                                    net.q.p, net.target.p, s) != hipSuccess)
-                return fail_free(fail(TESS_EHIP, "batch gather failed"));
-            st = net_forward(net, nb, true, s);
-            if (st == TESS_OK) st = net_backward(net, nb, (step == 1 || step == d->steps) ? dloss : nullptr, s);
-            if (st != TESS_OK) {
-                (void)hipFree(dloss);
-                return fail_free(st);
-            }
-            if (step == 1 || step == d->steps) {
-                TESS_HIP(hipMemcpyAsync(&lsum, dloss, sizeof(float), hipMemcpyDeviceToHost, s));
-                TESS_HIP(hipStreamSynchronize(s));
+            const bool report = step == 1 || step == d->steps;
+            const double c = 0.5 * (1.0 + std::cos(3.141592653589793 * (double)(step - 1) / std::max(1, d->steps - 1)));
+            const double lr = d->lr1 + (d->lr0 - d->lr1) * c;
+            const TrainNet T = net.train();
+            hipError_t e = launch_train_pass(T, nb, s);
+            if (e == hipSuccess)
+                e = launch_train_update(T, nb, adam_step(lr, 0.9, 0.999, 1e-8, step), report ? dloss : nullptr, src,
+                                        step < d->steps ? (uint64_t)step + 1 : 0, s);
+            if (e == hipSuccess && report) {
+                e = hipMemcpyAsync(&lsum, dloss, sizeof(float), hipMemcpyDeviceToHost, s);
+                if (e == hipSuccess) e = hipStreamSynchronize(s);
                 if (step == 1) rep.loss_first = lsum / (double)nb;
                 rep.loss_last = lsum / (double)nb;
             }
-            const double c = 0.5 * (1.0 + std::cos(3.141592653589793 * (double)(step - 1) / std::max(1, d->steps - 1)));
-            const double lr = d->lr1 + (d->lr0 - d->lr1) * c;
-            TESS_HIP(launch_adam(net.master.p, net.m.p, net.v.p, net.grad.p, kParams, lr, 0.9, 0.999, 1e-8, step, s));
-            TESS_HIP(launch_cast_weights(net.master.p, net.Wb.p, net.WTb.p, s));
+            if (e != hipSuccess) {
+                (void)hipFree(dloss);
+                return fail_free(fail(TESS_EHIP, "training step %d: %s", step, hipGetErrorString(e)));
+            }
         }
         TESS_HIP(hipStreamSynchronize(s));
         (void)hipFree(dloss);
