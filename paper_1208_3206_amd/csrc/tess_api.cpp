@@ -517,6 +517,7 @@ tess_status make_geometry(const tess_lattice_s *L, const tess_view *v, const Pla
     B.first_edge = (uint32_t)g.stored;
     B.seam = g.vp.edges && v->wrap ? 1 : 0;
     B.groups = nullptr;
+    B.rays = g.vp.persp && !g.vp.splat && !g.vp.hybrid;
     g.nmat = g.ntiles * B.nseg;
     g.npix = (int64_t)B.W * B.H;
     return TESS_OK;

@@ -90,6 +90,7 @@ struct BinParams {
     int32_t seam;            // 1: edge form under wrap (tiles carry a seam line per row)
     int32_t seam_copies;     // the raster's copies of each tile row's seam line (set at launch)
     const double *groups;    // edge form: slope changes by period offset, [3][edges] (EdgePayload)
+    int32_t rays;            // perspective without billboards: the raster multiplies a tile's sums by the rays' lengths
 };
 
 // Pair-list entries: the record id, with the pair's work class (0..31) in
@@ -169,7 +170,8 @@ constexpr uint32_t REC_FACE_TYPE_SHIFT = 10;  // face g: 2 bits at 10 + 2 g
 constexpr uint32_t REC_FACE_TIE_SHIFT = 18;   // face g's wall keeps pixels on its line
 constexpr uint32_t REC_FACE_FRONT = 1u, REC_FACE_BACK = 2u, REC_FACE_WALL = 3u;
 constexpr uint32_t REC_SPLAT = 1u << 22;      // payload is a centroid splat
-constexpr uint32_t REC_PERSP = 1u << 23;      // payload: camera-frame vertices and q
+constexpr uint32_t REC_PERSP = 1u << 23;      // payload: inverse-depth planes (or camera-frame vertices) and q
+constexpr uint32_t REC_PERSP_SHIFT = 26;      // planes: how many bound the inverse depth from below (3 bits; 0: vertices)
 constexpr uint32_t REC_EDGE = 1u << 24;       // a mesh edge: its summed crease (edge form)
 constexpr uint32_t REC_EDGED = 1u << 25;      // a tetrahedron whose creases went to its edges
 

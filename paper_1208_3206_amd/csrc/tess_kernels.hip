@@ -805,20 +805,25 @@ __global__ void __launch_bounds__(TPB) k_raster(const RecHead *__restrict__ head
     const uint32_t per = (it.count + TPB - 1) / TPB;
     const uint32_t e0 = threadIdx.x * per, e1 = min(it.count, e0 + per);
     if constexpr (FORM == kFormPersp) {
-        // per pixel, and a footprint may fill the tile: each wavefront takes
-        // its share of the list one pair at a time, its 64 lanes striding over
-        // the pair's pixels
-        const uint32_t nw = TPB / 64, lane = threadIdx.x & 63u;
-        const uint32_t wper = (it.count + nw - 1) / nw;
-        const uint32_t w0 = (threadIdx.x >> 6) * wper, w1 = min(it.count, w0 + wper);
-        for (uint32_t e = w0; e < w1; ++e) {
-            const uint32_t id = pairs[it.first + e];
+        // per pixel, and a footprint may fill the tile: a wavefront takes one
+        // pair at a time, its 64 lanes side by side over rows and columns,
+        // the next pair from a counter in LDS (footprints next to the camera
+        // are thousands of times larger than the rest).  The record is the
+        // same for all lanes and read into scalar registers.
+        for (;;) {
+            uint32_t e = 0u;
+            if ((threadIdx.x & 63u) == 0u) e = atomicAdd(&s_next, 1u);
+            e = (uint32_t)__builtin_amdgcn_readfirstlane((int)e);
+            if (e >= it.count) break;
+            const uint32_t id = (uint32_t)__builtin_amdgcn_readfirstlane((int)pairs[it.first + e]);
             if (id >= B.ntet) continue;
             const RecHead h = coef[id].h;
             if (!(h.flags & REC_VALID)) continue;
-            frags += persp_pair(h, coef[id].c, B, tx0, ty0, n, rows, (int)lane, 64,
-                                [&](int row, int j, double v) { atomicAdd(&sA[cell(row, j)], v); },
-                                spans, kinks);
+            auto dep = [&](int row, int j, double v) { atomicAdd(&sA[cell(row, j)], v); };
+            if (B.rays)
+                frags += persp_pair<false>(h, coef[id].c, B, tx0, ty0, n, rows, (int)(threadIdx.x & 63u), 64, dep, spans, kinks);
+            else
+                frags += persp_pair<true>(h, coef[id].c, B, tx0, ty0, n, rows, (int)(threadIdx.x & 63u), 64, dep, spans, kinks);
         }
     } else if (FORM == kFormPyramid && sorted) {
         // The wavefront takes the next kSortPer entries of each of its lanes'
@@ -1028,7 +1033,13 @@ __global__ void __launch_bounds__(TPB) k_raster(const RecHead *__restrict__ head
     __syncthreads();
     for (int i = threadIdx.x; i < rows * B.Tw; i += TPB) {
         const int r = i / B.Tw, c = i - r * B.Tw;
-        const double v = sA[cell(r, c)];
+        double v = sA[cell(r, c)];
+        if constexpr (FORM == kFormPersp)
+            if (B.rays) {
+                const double pu = ((double)(tx0 + c) + 0.5) * (B.ext_u / (double)B.W) - 0.5 * B.ext_u;
+                const double pv = ((double)(ty0 + r) + 0.5) * (B.ext_v / (double)B.H) - 0.5 * B.ext_v;
+                v *= sqrt(pu * pu + pv * pv + 1.0);
+            }
         if (c < n && v != 0.0) unsafeAtomicAdd(&acc[(int64_t)(ty0 + r) * B.W + tx0 + c], v);
     }
     // the seam lines: a at column 0 and b - a at column 1 of the second

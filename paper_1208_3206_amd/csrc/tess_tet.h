@@ -436,6 +436,86 @@ TESS_HD inline bool face_payload(const double qx[4], const double qy[4], const d
     return true;
 }
 
+// Inverse-depth planes of a perspective tetrahedron (vertices vtx in the
+// camera frame).  Along the half-line s (pu, pv, 1) of a pixel, w = 1 / s is
+// linear over the image on every plane not through the camera, so in (X, Y,
+// w), pixel coordinates relative to the record's box corner (bx0, by0) with
+// centres at whole numbers + 1/2, the tetrahedron is a polyhedron with plane
+// faces: out[3 f ..] = a, b, c of w = a + b X + c Y, the na faces that bound w
+// from below (the far side, where the half-line leaves) first, then those
+// that bound it from above.  With every vertex in front of the camera (and
+// projected within 1000 window units) a face's plane is that through its
+// vertices' (X, Y, 1 / z), which keeps the thickness of a sliver: its faces
+// differ by their slopes from a shared vertex.  Otherwise the plane is
+// (n . d) / h of the face n . y = h, d = (pu, pv, 1), from below when the
+// camera is on the tetrahedron's side of it.  Returns na, or 0 where a face
+// is seen edge-on (its plane contains the camera) or coefficients leave the
+// range whose products stay finite.
+TESS_HD inline int persp_planes(const double vtx[12], const ViewParams &V, int bx0, int by0, double out[12]) {
+    double X[4], Y[4], w[4];
+    bool front = true;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        w[m] = 1.0 / vtx[3 * m + 2];
+        const double pu = vtx[3 * m] * w[m], pv = vtx[3 * m + 1] * w[m];
+        front = front && vtx[3 * m + 2] > 0.0 && fabs(pu) < 1.0e3 && fabs(pv) < 1.0e3;
+        X[m] = (pu - V.u_left) * V.inv_du - (double)bx0;
+        Y[m] = (pv - V.v_bottom) * V.inv_dv - (double)by0;
+    }
+    double g[4][3];
+    bool below[4], ok = true;
+    int na = 0;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+        const int b = kFace[f][0], c = kFace[f][1], d = kFace[f][2];
+        if (front) {
+            const double ex = X[c] - X[b], ey = Y[c] - Y[b], et = w[c] - w[b];
+            const double fx = X[d] - X[b], fy = Y[d] - Y[b], ft = w[d] - w[b];
+            const double D = ex * fy - ey * fx;
+            g[f][1] = (et * fy - ey * ft) / D;
+            g[f][2] = (ex * ft - et * fx) / D;
+            g[f][0] = w[b] - g[f][1] * X[b] - g[f][2] * Y[b];
+            const double side = w[f] - (g[f][0] + g[f][1] * X[f] + g[f][2] * Y[f]);
+            below[f] = side > 0.0;
+            ok = ok && side != 0.0;
+        } else {
+            double e1[3], e2[3], ea[3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                e1[q] = vtx[3 * c + q] - vtx[3 * b + q];
+                e2[q] = vtx[3 * d + q] - vtx[3 * b + q];
+                ea[q] = vtx[3 * f + q] - vtx[3 * b + q];
+            }
+            const double n0 = e1[1] * e2[2] - e1[2] * e2[1], n1 = e1[2] * e2[0] - e1[0] * e2[2],
+                         n2 = e1[0] * e2[1] - e1[1] * e2[0];
+            const double h = n0 * vtx[3 * b] + n1 * vtx[3 * b + 1] + n2 * vtx[3 * b + 2];
+            // the outward normal points away from the opposite vertex (its
+            // sign cancels in n / h)
+            below[f] = (n0 * ea[0] + n1 * ea[1] + n2 * ea[2] > 0.0) == (h < 0.0);
+            g[f][1] = n0 / V.inv_du / h;
+            g[f][2] = n1 / V.inv_dv / h;
+            g[f][0] = (n0 * V.u_left + n1 * V.v_bottom + n2) / h + g[f][1] * (double)bx0 + g[f][2] * (double)by0;
+        }
+        na += below[f] ? 1 : 0;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) ok = ok && fabs(g[f][q]) < 1e120;  // (false for a NaN)
+    }
+    if (!ok) return 0;
+    int k = 0, m = na;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+        const int to = below[f] ? k++ : m++;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)  // (by constant slots: no scratch)
+            if (t == to) {
+                out[3 * t] = g[f][0];
+                out[3 * t + 1] = g[f][1];
+                out[3 * t + 2] = g[f][2];
+            }
+    }
+    return na;
+}
+
 // Counters of one lattice cube's setup.
 struct CubeCounts {
     unsigned n_tets = 0, n_zero = 0, n_inv = 0, n_dets = 0, n_deg = 0;
@@ -1088,6 +1168,18 @@ TESS_HD inline void setup_cube(const LatticeParams &L, const ViewParams &V, int6
                 R.bx = pack_range(ix0, ix1);
                 R.by = pack_range(iy0, iy1);
                 R.flags = REC_PERSP | REC_VALID;
+                // the inverse-depth planes, except for slivers: their density
+                // multiplies the rounding of the two depths (2^-53 each), and
+                // below a thousandth of the mean volume the vertices' form,
+                // whose rounding the depths' difference largely cancels, is
+                // kept (a few tetrahedra in ten thousand)
+                double planes[12];
+                const int na = fabs(det6) >= 6e-3 * L.v0 ? persp_planes(pc, V, ix0, iy0, planes) : 0;
+                if (na > 0) {
+                    R.flags |= (uint32_t)na << REC_PERSP_SHIFT;
+#pragma unroll
+                    for (int g = 0; g < 12; ++g) pc[g] = planes[g];
+                }
                 return;
             }
             // ---- screen footprint (FP64)
@@ -2116,19 +2208,104 @@ TESS_HD inline uint32_t splat_pair(const RecHead &h, const double *cf, const Bin
 }
 
 // ---------------------------------------------------- perspective camera
+// A row of a perspective record in its inverse-depth planes (NA of them
+// bounding w = 1 / s from below, the others from above): the chord is
+// 1 / w_lo - 1 / w_hi.
+template <int NA>
+TESS_HD inline void persp_bounds(const double g[4], const double *cf, double X, double &wlo, double &whi) {
+    double w[4];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) w[f] = fma(cf[3 * f + 1], X, g[f]);
+    wlo = w[0];
+#pragma unroll
+    for (int f = 1; f < NA; ++f) wlo = fmax(wlo, w[f]);
+    whi = w[3];
+#pragma unroll
+    for (int f = NA; f < 3; ++f) whi = fmin(whi, w[f]);
+}
+
+// The record's rows [y0, y1] and columns [x0, x1], shared out over nlanes
+// lanes, lpr of them (a power of two) side by side in a row.  A row's columns
+// are first cut to those between its crossings with the silhouette, which are
+// the crossings of a lower with an upper plane (a column to spare each side:
+// the per-pixel test decides).  RAY: the values carry the ray's length per
+// unit depth; without it the caller multiplies each pixel's sum by it.
+template <int NA, bool RAY, typename Dep>
+TESS_HD inline uint32_t persp_rows(const RecHead &h, const double *cf, const BinParams &B, int tx0, int ty0, int x0,
+                                   int x1, int y0, int y1, int lane0, int nlanes, int lpr, Dep &&dep,
+                                   uint32_t &kinks) {
+    const double q = cf[12];
+    const int bx0 = range_lo(h.bx), by0 = range_lo(h.by);
+    // silhouette: column t0 + t1 Y where plane a meets plane b, a bound from
+    // the left or the right, or none (an edge almost along the row)
+    constexpr int NB = 4 - NA, NP = NA * NB;
+    double t0[NP ? NP : 1], t1[NP ? NP : 1];
+    bool left[NP ? NP : 1];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        const int a = k / (NB ? NB : 1), b = NA + k % (NB ? NB : 1);
+        const double d0 = cf[3 * b] - cf[3 * a], dx = cf[3 * b + 1] - cf[3 * a + 1], dy = cf[3 * b + 2] - cf[3 * a + 2];
+        const double r = -fast_rcp(dx);
+        t0[k] = d0 * r;
+        t1[k] = dy * r;
+        left[k] = dx > 0.0;
+        if (!(fabs(t0[k]) < 1e10 && fabs(t1[k]) < 1e10)) {  // (rounding stays below a column within the bound)
+            t0[k] = left[k] ? -1e10 : 1e10;
+            t1[k] = 0.0;
+        }
+    }
+    uint32_t frags = 0;
+    const int lq = lane0 & (lpr - 1), step = nlanes / lpr;
+    for (int y = y0 + lane0 / lpr; y <= y1; y += step) {
+        const double Y = (double)(y - by0) + 0.5;
+        double xl = (double)(x0 - bx0), xr = (double)(x1 - bx0) + 1.0;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const double t = fma(t1[k], Y, t0[k]);
+            xl = fmax(xl, left[k] ? t : xl);
+            xr = fmin(xr, left[k] ? xr : t);
+        }
+        if (!(xl <= xr + 2.0)) continue;
+        const int xa = max((int)xl - 1, x0 - bx0), xb = min((int)xr + 1, x1 - bx0);
+        double g[4];
+#pragma unroll
+        for (int f = 0; f < 4; ++f) g[f] = fma(cf[3 * f + 2], Y, cf[3 * f]);
+        const int shift = bx0 - tx0;
+        double X = (double)(xa + lq) + 0.5;
+        for (int x = xa + lq; x <= xb; x += lpr, X += (double)lpr) {
+            double wlo, whi;
+            persp_bounds<NA>(g, cf, X, wlo, whi);
+            ++kinks;
+            if (NA == 4 ? wlo > 0.0 : wlo > 0.0 && whi > wlo) {
+                double v = NA == 4 ? q * fast_rcp(wlo) : (q * (whi - wlo)) * fast_rcp(whi * wlo);
+                if (RAY) {
+                    const double pu = (X + (double)bx0) * (B.ext_u / (double)B.W) - 0.5 * B.ext_u;
+                    const double pv = (Y + (double)by0) * (B.ext_v / (double)B.H) - 0.5 * B.ext_v;
+                    v *= sqrt(pu * pu + pv * pv + 1.0);
+                }
+                dep(y - ty0, x + shift, v);
+                ++frags;
+            }
+        }
+    }
+    return frags;
+}
+
 // A perspective record's chords at the tile's pixel centres, added as values:
 // dep(row, u, q dl) for the tile column u.  The pixel at (pu, pv) on the
-// window sees the half-line s (pu, pv, 1), s >= 0, in the camera frame; it is
+// window sees the half-line s (pu, pv, 1), s >= 0, in the camera frame, and
+// dl is its length |(pu, pv, 1)| (s_out - s_in) inside the tetrahedron.  The
+// record holds the faces' inverse-depth planes (persp_planes); where one of
+// them passes through the camera, and for slivers, it holds the vertices, and the half-line is
 // clipped against the four outward face planes n . y <= h (n . d == 0: the
 // ray is out when h < 0, and on the plane by the orthographic raster's
-// half-open rule), and dl = |(pu, pv, 1)| (s_out - s_in).  Footprints range
-// from a pixel to whole tiles (next to the camera), so the pixels of the
-// record's box in the tile are shared out: this call takes those with
-// row-major index k = lane0, lane0 + nlanes, ...  Returns the pixels with
+// half-open rule).  Footprints range from a pixel to whole tiles (next to
+// the camera), so the pixels of the record's box in the tile are shared out
+// over nlanes lanes, of which this call is lane0.  Returns the pixels with
 // dl > 0; kinks counts the pixels evaluated.  A billboard record (the
 // centroid method, or beyond the hybrid's sphere) adds q |V| W(r, h) instead,
 // r = z_c |(pu, pv) - (u_c, v_c)| where the ray crosses the billboard's plane.
-template <typename Dep>
+template <bool RAY = true, typename Dep>
 TESS_HD inline uint32_t persp_pair(const RecHead &h, const double *cf, const BinParams &B, int tx0, int ty0,
                                    int n, int rows, int lane0, int nlanes, Dep &&dep, uint32_t &spans,
                                    uint32_t &kinks) {
@@ -2162,6 +2339,17 @@ TESS_HD inline uint32_t persp_pair(const RecHead &h, const double *cf, const Bin
             }
         }
         return frags;
+    }
+    const uint32_t na = (h.flags >> REC_PERSP_SHIFT) & 7u;
+    if (na) {
+        // lanes of a row: 16, or 8 where 16 would be half empty
+        const int lpr = nlanes < 64 ? 1 : (bw <= 8 ? 8 : 16);
+        switch (na) {
+            case 1: return persp_rows<1, RAY>(h, cf, B, tx0, ty0, x0, x1, y0, y1, lane0, nlanes, lpr, dep, kinks);
+            case 2: return persp_rows<2, RAY>(h, cf, B, tx0, ty0, x0, x1, y0, y1, lane0, nlanes, lpr, dep, kinks);
+            case 3: return persp_rows<3, RAY>(h, cf, B, tx0, ty0, x0, x1, y0, y1, lane0, nlanes, lpr, dep, kinks);
+            default: return persp_rows<4, RAY>(h, cf, B, tx0, ty0, x0, x1, y0, y1, lane0, nlanes, lpr, dep, kinks);
+        }
     }
     double nrm[4][3], off[4];
 #pragma unroll
@@ -2207,59 +2395,10 @@ TESS_HD inline uint32_t persp_pair(const RecHead &h, const double *cf, const Bin
             }
         }
         if (!out && hi > lo && hi < 1e300) {
-            dep(y - ty0, x - tx0, q * ((hi - lo) * sqrt(pu * pu + pv * pv + 1.0)));
+            dep(y - ty0, x - tx0, q * (RAY ? (hi - lo) * sqrt(pu * pu + pv * pv + 1.0) : hi - lo));
             ++frags;
         }
     };
-    // (FP32: the spans only bound the columns to test, with a pixel to spare,
-    // and projections within 1000 window units round to well under a pixel)
-    float ex[4], ey[4];
-    bool spans_ok = nlanes == 64;
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        const double z = cf[3 * m + 2];
-        const double px = cf[3 * m] / z, py = cf[3 * m + 1] / z;
-        spans_ok = spans_ok && z > 0.0 && fabs(px) < 1.0e3 && fabs(py) < 1.0e3;
-        ex[m] = (float)px;
-        ey[m] = (float)py;
-    }
-    if (spans_ok) {
-        // all four vertices in front of the camera (and not near its plane):
-        // the tetrahedron covers the convex hull of their projections, so a
-        // row needs only the columns between its crossings with the six
-        // projected edges (one pixel wider each side; the per-pixel test
-        // decides).  A 16-lane group takes every fourth row of the box, its
-        // lanes the row's columns (the box holds three samples per covered
-        // pixel at the perspective workload).
-        float sl[6];  // edge (i, j)'s x step per unit of height (a level edge: 0)
-        int k = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = i + 1; j < 4; ++j, ++k) sl[k] = ey[j] != ey[i] ? (ex[j] - ex[i]) / (ey[j] - ey[i]) : 0.0f;
-        const int g = lane0 >> 4, lq = lane0 & 15;
-        for (int y = y0 + g; y <= y1; y += 4) {
-            const float pv = (float)(-0.5 * B.ext_v + ((double)y + 0.5) * dv);
-            float xl = 1e30f, xr = -1e30f;
-            k = 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = i + 1; j < 4; ++j, ++k) {
-                    if (pv < fminf(ey[i], ey[j]) || pv > fmaxf(ey[i], ey[j])) continue;
-                    const bool level = ey[j] == ey[i];
-                    const float xa = level ? fminf(ex[i], ex[j]) : fmaf(pv - ey[i], sl[k], ex[i]);
-                    const float xb = level ? fmaxf(ex[i], ex[j]) : xa;
-                    xl = fminf(xl, xa);
-                    xr = fmaxf(xr, xb);
-                }
-            if (!(xl <= xr)) continue;
-            const double fa = ((double)xl + 0.5 * B.ext_u) / du - 0.5, fb = ((double)xr + 0.5 * B.ext_u) / du - 0.5;
-            const int xa = max((int)floor(fa) - 1, x0), xb = min((int)ceil(fb) + 1, x1);
-            for (int x = xa + lq; x <= xb; x += 16) sample(x, y);
-        }
-        return frags;
-    }
     // row-major walk of the box: k -> (y, x), stepping nlanes at a time
     int y = y0 + lane0 / bw, x = x0 + lane0 % bw;
     for (int k = lane0; k < npix; k += nlanes) {
