@@ -82,6 +82,7 @@ struct Workspace {
     DevBuf<PlanOut> plan;               // one per image of a batch
     DevBuf<DevCounters> counters;
     DevBuf<unsigned int> overflow;
+    DevBuf<double> stack;               // slabs of a stack (t0, t1)
     PlanOut *host_plan = nullptr;       // pinned, host_plan_cap entries
     size_t host_plan_cap = 0;
     DevCounters *host_counters = nullptr;
@@ -421,6 +422,8 @@ void make_params(const tess_lattice_s *L, const tess_view *v, int form, LatticeP
     vp.edges = (view_form(vp) == kFormPyramid && !force_tet && (force_edges || cell_px >= min_cell_px)) ? 1 : 0;
     vp.kinks = nullptr;
     vp.sil = nullptr;
+    vp.stack = nullptr;
+    vp.nstack = 0;
 }
 
 struct Plan {
@@ -465,16 +468,19 @@ struct Geometry {
     LatticeParams lp;
     ViewParams vp;
     BinParams B;
-    int64_t ntet, ntiles, nmat, npix;
+    int64_t ntet, ntiles, nmat, npix;  // (a stack: lists and pixels of all its slabs)
     int64_t stored;  // tetrahedron payloads: all (6 ncubes), or (edge form) own_cap
     int64_t spill;   // edge form: 32-bit words of the spill bit set (one spare)
 };
 
 // own_cap: edge form, the payloads for the tetrahedra that keep their own
 // record (< 0: one per tetrahedron)
+// nstack: the view is the first of so many that differ in their slabs, set up
+// as one (v's slab holds all of theirs); 0: a single image
 tess_status make_geometry(const tess_lattice_s *L, const tess_view *v, const Plan &plan, Geometry &g,
-                          int64_t own_cap = -1) {
+                          int64_t own_cap = -1, int nstack = 0) {
     make_params(L, v, plan.form, g.lp, g.vp);
+    g.vp.nstack = nstack;
     // records: the tetrahedra (edge form: the few that keep their own record,
     // own_cap of them), then (edge form) seven edges per lattice vertex; the
     // edge form only while all ids fit in 32 bits
@@ -501,6 +507,10 @@ tess_status make_geometry(const tess_lattice_s *L, const tess_view *v, const Pla
                     (long long)g.ntiles, plan.Th, plan.Tw, kMaxTiles);
     // pair ids carry a work class (pyramid records, ids below the class bits)
     B.nkey = (view_form(g.vp) == kFormPyramid && !g.vp.edges && g.ntet < (int64_t)kIdMask) ? 32 : 1;
+    B.stack = nullptr;
+    B.nstack = nstack;
+    g.ntiles *= std::max(nstack, 1);  // lists
+    B.nbins = (int32_t)g.ntiles;
     // binning segments: enough for the device, few enough to keep the count matrix small
     int64_t seg_len = 4096;
     while ((g.ntet + seg_len - 1) / seg_len * g.ntiles > (int64_t)64 << 20) seg_len *= 2;
@@ -509,7 +519,7 @@ tess_status make_geometry(const tess_lattice_s *L, const tess_view *v, const Pla
     B.ntet = (uint32_t)g.ntet;
     B.slab_t[0] = g.vp.slab_t[0];
     B.slab_t[1] = g.vp.slab_t[1];
-    B.direct = g.vp.splat || g.vp.persp;
+    B.direct = g.vp.splat || g.vp.persp || g.vp.slab;
     B.ext_u = v->extent[0];
     B.ext_v = v->extent[1];
     B.form = view_form(g.vp);
@@ -519,7 +529,7 @@ tess_status make_geometry(const tess_lattice_s *L, const tess_view *v, const Pla
     B.groups = nullptr;
     B.rays = g.vp.persp && !g.vp.splat && !g.vp.hybrid;
     g.nmat = g.ntiles * B.nseg;
-    g.npix = (int64_t)B.W * B.H;
+    g.npix = (int64_t)B.W * B.H * std::max(nstack, 1);
     return TESS_OK;
 }
 
@@ -1092,11 +1102,158 @@ std::string graph_key(const tess_lattice *snaps, int n_snaps, const tess_view *v
     return k;
 }
 
+// ------------------------------------------------------ stacks of slabs
+// A batch whose views differ only in their depth slabs (resampling to a grid)
+// is drawn per snapshot as one image of many layers: the tetrahedra are set up
+// once instead of once per slab, binned into (slab, tile) lists, and one
+// raster launch holds the work of all slabs (a slab of a 64^2 image fills a
+// tenth of the chip).  Taken when neither end of the slabs decreases along
+// the views (a tetrahedron's slabs are then consecutive), without an explicit
+// pair capacity (a count per image) or workspace limit (the layers' lists and
+// accumulators need more than one image's), and in groups whose accumulators
+// stay within kStackBytes; other batches take the general path, as does one
+// whose stacks find no memory.
+constexpr size_t kStackBytes = (size_t)1 << 30;
+constexpr int kMaxStack = 4096;
+
+// Slabs per stack, or 0: not a stack.
+int stack_size(const tess_view *views, int n_views, const tess_tune *tune) {
+    const tess_view &a = views[0];
+    if (n_views < 2 || !a.slab || a.projection != TESS_PROJECTION_ORTHOGRAPHIC ||
+        a.method != TESS_METHOD_TESSELLATION || (tune && (tune->pair_capacity || tune->workspace_limit)))
+        return 0;
+    for (int i = 1; i < n_views; ++i) {
+        const tess_view &b = views[i], &c = views[i - 1];
+        if (std::memcmp(a.rot, b.rot, sizeof(a.rot)) || std::memcmp(a.center, b.center, sizeof(a.center)) ||
+            std::memcmp(a.extent, b.extent, sizeof(a.extent)) || a.width != b.width || a.height != b.height ||
+            a.wrap != b.wrap || a.quantity != b.quantity || b.slab != 1 || b.projection != a.projection ||
+            b.method != a.method || b.slab_t[0] < c.slab_t[0] || b.slab_t[1] < c.slab_t[1])
+            return 0;
+    }
+    const Plan p = choose_plan(&a, tune);
+    const int64_t tiles = (int64_t)((a.width + p.Tw - 1) / p.Tw) * ((a.height + p.Th - 1) / p.Th);
+    const int64_t most = std::min<int64_t>(
+        {(int64_t)kMaxStack, (int64_t)kMaxTiles / tiles, (int64_t)(kStackBytes / sizeof(double)) / ((int64_t)a.width * a.height)});
+    if (most < 2) return 0;
+    const int groups = (int)((n_views + most - 1) / most);
+    return (n_views + groups - 1) / groups;
+}
+
+// The batch as stacks of up to `per` slabs; *taken = false (and nothing
+// drawn) when they find no memory.
+tess_status project_stacks(const tess_lattice *snaps, int n_snaps, const tess_view *views, int n_views, int per,
+                           const tess_tune *tune, float *images, tess_stats *stats, hipStream_t s, Workspace &ws,
+                           bool *taken) {
+    *taken = true;
+    const Plan plan = choose_plan(&views[0], tune);
+    const size_t img = (size_t)views[0].width * views[0].height;
+    const int groups = (n_views + per - 1) / per, n_st = n_snaps * groups;
+    const std::string key = "stack " + std::to_string(per) + "|" + shape_key(snaps[0], &views[0], n_snaps, n_views, tune);
+    auto slabs = [&](int g) { return std::min(per, n_views - g * per); };
+    auto geometry = [&](int i, int g, Geometry &G) {
+        tess_view v = views[g * per];
+        v.slab_t[1] = views[g * per + slabs(g) - 1].slab_t[1];
+        tess_status st = make_geometry(snaps[i], &v, plan, G, -1, slabs(g));
+        G.vp.stack = G.B.stack = ws.stack.p + 2 * (size_t)g * per;
+        return st;
+    };
+    Sizes z;
+    for (int i = 0; i < n_snaps; ++i)
+        for (int g = 0; g < groups; ++g) {
+            Geometry G;
+            tess_status st = geometry(i, g, G);
+            if (st != TESS_OK) return st;
+            z.add(G);
+        }
+    take_feedback(ws, s);
+    auto it = ws.learned.find(key);
+    unsigned long long most = it != ws.learned.end() ? it->second : 0;
+    tess_status st = ensure_front(ws, z);
+    if (st != TESS_OK) {
+        *taken = st != TESS_ENOMEM;
+        return st;
+    }
+    TESS_HIP(ws.stack.ensure(2 * (size_t)n_views));
+    TESS_HIP(ws.plan.ensure((size_t)n_st));
+    if (ws.host_plan_cap < (size_t)n_st) {
+        TESS_HIP(hipHostFree(ws.host_plan));
+        ws.host_plan = nullptr;
+        ws.host_plan_cap = 0;
+        TESS_HIP(hipHostMalloc((void **)&ws.host_plan, sizeof(PlanOut) * (size_t)n_st, hipHostMallocDefault));
+        ws.host_plan_cap = (size_t)n_st;
+    }
+    std::vector<double> t(2 * (size_t)n_views);
+    for (int v = 0; v < n_views; ++v) {
+        t[2 * v] = views[v].slab_t[0];
+        t[2 * v + 1] = views[v].slab_t[1];
+    }
+    TESS_HIP(launch_stack_table(t.data(), n_views, ws.stack.p, s));
+    const Bufs front = bufs_of(ws);
+    if (it == ws.learned.end()) {
+        // the first call of a shape counts its pairs
+        for (int k = 0; k < n_st; ++k) {
+            Geometry G;
+            st = geometry(k / groups, k % groups, G);
+            if (st == TESS_OK) st = enqueue_front(G, front, ws.plan.p + k, ~0ull, nullptr, s);
+            if (st != TESS_OK) return st;
+        }
+        TESS_HIP(hipMemcpyAsync(ws.host_plan, ws.plan.p, sizeof(PlanOut) * (size_t)n_st, hipMemcpyDeviceToHost, s));
+        TESS_HIP(hipStreamSynchronize(s));
+        for (int k = 0; k < n_st; ++k) most = std::max<unsigned long long>(most, ws.host_plan[k].total_pairs);
+        ws.learned[key] = most;
+    }
+    const unsigned long long cap = capacity_for(most);
+    const int chunk = plan.chunk ? plan.chunk : auto_chunk(most);
+    st = ensure_back(ws, z.ntiles, chunk, cap);
+    if (st != TESS_OK) {
+        *taken = st != TESS_ENOMEM;
+        return st;
+    }
+    if (stats) TESS_HIP(hipEventRecord(ws.ev[0], s));
+    TESS_HIP(launch_zero((double *)ws.counters.p, sizeof(DevCounters) / sizeof(double), s));
+    const Bufs b = bufs_of(ws);
+    for (int k = 0; k < n_st; ++k) {
+        Geometry G;
+        st = geometry(k / groups, k % groups, G);
+        if (st == TESS_OK) st = enqueue_front(G, b, ws.plan.p + k, cap, nullptr, s);
+        if (st == TESS_OK)
+            st = enqueue_back(G, plan, chunk, cap, true, b, ws.plan.p + k,
+                              images + ((size_t)(k / groups) * n_views + (size_t)(k % groups) * per) * img, s, nullptr,
+                              nullptr);
+        if (st != TESS_OK) return st;
+    }
+    if (!stats) return give_feedback(ws, ws.plan.p, n_st, key, s);
+    TESS_HIP(hipEventRecord(ws.ev[4], s));
+    TESS_HIP(hipMemcpyAsync(ws.host_plan, ws.plan.p, sizeof(PlanOut) * (size_t)n_st, hipMemcpyDeviceToHost, s));
+    TESS_HIP(hipMemcpyAsync(ws.host_counters, ws.counters.p, sizeof(DevCounters), hipMemcpyDeviceToHost, s));
+    TESS_HIP(hipStreamSynchronize(s));
+    float ms = 0;
+    TESS_HIP(hipEventElapsedTime(&ms, ws.ev[0], ws.ev[4]));
+    fill_stats(stats, *ws.host_counters, plan, chunk);
+    stats->ms = ms;
+    for (int k = 0; k < n_st; ++k) {
+        const PlanOut &P = ws.host_plan[k];
+        stats->bin_pairs += P.total_pairs;
+        stats->max_bin =
+            std::max<uint32_t>(stats->max_bin, (uint32_t)std::min<unsigned long long>(P.max_bin, 0xffffffffull));
+        stats->work_items += (uint32_t)P.n_items;
+        stats->overflow += P.total_pairs > cap ? (uint32_t)slabs(k % groups) : 0u;
+        most = std::max<unsigned long long>(most, P.total_pairs);
+    }
+    ws.learned[key] = most;
+    return TESS_OK;
+}
+
 tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tess_view *views, int n_views,
                                const tess_tune *tune, float *images, tess_stats *stats, hipStream_t s,
                                Workspace &ws) {
     const size_t img = (size_t)views[0].width * views[0].height;
     const int n_img = n_snaps * n_views;
+    if (const int per = stack_size(views, n_views, tune)) {
+        bool taken = false;
+        const tess_status st = project_stacks(snaps, n_snaps, views, n_views, per, tune, images, stats, s, ws, &taken);
+        if (taken) return st;
+    }
     const std::string key = shape_key(snaps[0], &views[0], n_snaps, n_views, tune);
     const std::string count_key = "batch|" + key;
     // raster parameters and capacity: this process's, the cache file's, or tuned now

@@ -60,6 +60,10 @@ struct ViewParams {
     uint64_t own_cap;
     unsigned long long *own;
     uint32_t *spill;
+    // a stack of depth slabs set up at once (kFormStack): nstack slabs, t0 and
+    // t1 of slab k at stack[2 k] (device), neither decreasing with k
+    const double *stack;
+    int32_t nstack;
 };
 
 // Record kinds of a launch (one per view): the pyramid (crease and line
@@ -67,8 +71,13 @@ struct ViewParams {
 constexpr int kFormPyramid = 0, kFormFace = 1, kFormSplat = 2, kFormPersp = 3;
 // the raster's instantiation for pyramids whose lists also hold edge records
 constexpr int kFormEdge = 4;
+// face-form records of a stack of slabs (ViewParams::nstack > 0): the head's
+// spare word holds the first and last slab that the tetrahedron meets (16
+// bits each), and the lists are per (slab, tile)
+constexpr int kFormStack = 5;
 __host__ __device__ inline int view_form(const ViewParams &V) {
-    return V.persp ? kFormPersp : V.splat ? kFormSplat : (V.slab ? kFormFace : kFormPyramid);
+    return V.persp ? kFormPersp : V.splat ? kFormSplat
+           : V.slab ? (V.nstack ? kFormStack : kFormFace) : kFormPyramid;
 }
 
 // Screen tiling: tiles of Th rows x Tw columns (a row band when Tw >= W).
@@ -82,14 +91,17 @@ struct BinParams {
     int32_t nkey;            // work classes carried by pair ids (32), or 1: plain ids
     uint32_t ntet;           // number of records
     double slab_t[2];        // depth slab of face-form records (the view's)
-    int32_t direct;          // 1: the accumulator holds values (splats, perspective), not second differences
-    int32_t form;            // the records' kind (kFormPyramid, kFormFace, kFormSplat, kFormPersp)
+    int32_t direct;          // 1: the accumulator holds values (splats, perspective, slabs), not second differences
+    int32_t form;            // the records' kind (view_form)
     double ext_u, ext_v;     // the view's window (perspective: pixel rays)
     int32_t edges;           // 1: edge form (the lists hold edge records)
     uint32_t first_edge;     // edge form: id of the first edge record (6 cubes)
     int32_t seam;            // 1: edge form under wrap (tiles carry a seam line per row)
     int32_t seam_copies;     // the raster's copies of each tile row's seam line (set at launch)
     const double *groups;    // edge form: slope changes by period offset, [3][edges] (EdgePayload)
+    const double *stack;     // stack of slabs: as ViewParams
+    int32_t nstack;          // number of its slabs, 0 for a single image
+    int32_t nbins;           // lists: tiles, per slab of a stack (slab-major)
     int32_t rays;            // perspective without billboards: the raster multiplies a tile's sums by the rays' lengths
 };
 
@@ -121,7 +133,7 @@ struct PlanOut {
 struct WorkItem {
     uint64_t first;          // offset into the pair array
     uint32_t count;          // entries
-    uint32_t tile;           // tile index ty * ntx + tx
+    uint32_t tile;           // list: tile index ty * ntx + tx (+ slab * tiles)
 };
 
 // Per-tetrahedron raster record, stored as two arrays: the head (box and
@@ -138,7 +150,9 @@ struct WorkItem {
 //    hold its depth plane t = c0 + c1 x + c2 y (world depth over pixel
 //    coordinates; front or back face) or, for a wall, its half-plane as in
 //    the line form; c[12] the projected value q. The record's f(p) is q
-//    times the chord inside the tetrahedron and the slab;
+//    times the chord inside the tetrahedron and the slab.  Without walls the
+//    front faces come first, their number at REC_PLANES_SHIFT; deposited as
+//    values;
 //  - edge form (REC_EDGE): one segment of the tetrahedral mesh, in an
 //    EdgePayload (below); the head's spare word counts, by period offset, the
 //    tetrahedra for which it is an entering and a leaving silhouette edge
@@ -171,7 +185,8 @@ constexpr uint32_t REC_FACE_TIE_SHIFT = 18;   // face g's wall keeps pixels on i
 constexpr uint32_t REC_FACE_FRONT = 1u, REC_FACE_BACK = 2u, REC_FACE_WALL = 3u;
 constexpr uint32_t REC_SPLAT = 1u << 22;      // payload is a centroid splat
 constexpr uint32_t REC_PERSP = 1u << 23;      // payload: inverse-depth planes (or camera-frame vertices) and q
-constexpr uint32_t REC_PERSP_SHIFT = 26;      // planes: how many bound the inverse depth from below (3 bits; 0: vertices)
+constexpr uint32_t REC_PLANES_SHIFT = 26;     // perspective, slab: how many of the four planes bound the
+                                              // (inverse) depth from below, these first (3 bits; 0: vertices, walls)
 constexpr uint32_t REC_EDGE = 1u << 24;       // a mesh edge: its summed crease (edge form)
 constexpr uint32_t REC_EDGED = 1u << 25;      // a tetrahedron whose creases went to its edges
 
@@ -269,7 +284,12 @@ hipError_t launch_raster_direct(const LatticeParams &L, const ViewParams &V, con
                                 unsigned long long cap, const BinParams &B, double *acc, DevCounters *counters,
                                 hipStream_t stream);
 
-// Row-wise double prefix sum of acc -> image (FP32).
+// Writes the n slabs' t0, t1 to table[2 n] (from kernel arguments, so that
+// the call can sit in a captured graph and holds no host memory).
+hipError_t launch_stack_table(const double *t, int n, double *table, hipStream_t stream);
+
+// Row-wise double prefix sum of acc -> image (FP32); a stack's slabs are
+// rows after rows.
 hipError_t launch_finalize(const double *acc, const BinParams &B, float *image, hipStream_t stream);
 
 // Bytes of the allocation-free projection's scratch, a file-scope device

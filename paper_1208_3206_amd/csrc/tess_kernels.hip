@@ -122,9 +122,11 @@ __global__ void __launch_bounds__(256, 2) k_setup(LatticeParams L, ViewParams V,
             __syncthreads();
         }
     }
-    const unsigned long long n_tets = wave_sum(cnt.n_tets), n_zero = wave_sum(cnt.n_zero),
-                             n_inv = wave_sum(cnt.n_inv), n_dets = wave_sum(cnt.n_dets),
-                             n_deg = wave_sum(cnt.n_deg);
+    // (a stack's setup serves all its slabs' images)
+    const unsigned long long per = FORM == kFormStack ? (unsigned long long)V.nstack : 1ull;
+    const unsigned long long n_tets = wave_sum(cnt.n_tets) * per, n_zero = wave_sum(cnt.n_zero) * per,
+                             n_inv = wave_sum(cnt.n_inv) * per, n_dets = wave_sum(cnt.n_dets) * per,
+                             n_deg = wave_sum(cnt.n_deg) * per;
     if (lane == 0) {
         if (n_tets) atomicAdd(&counters->tets, n_tets);
         if (n_zero) atomicAdd(&counters->zero_volume, n_zero);
@@ -237,6 +239,9 @@ hipError_t launch_setup(const LatticeParams &L, const ViewParams &V, RecHead *he
         case kFormFace:
             hipLaunchKernelGGL((k_setup<kFormFace, false>), dim3(blocks), dim3(256), 0, stream, L, V, head, coef, counters);
             break;
+        case kFormStack:
+            hipLaunchKernelGGL((k_setup<kFormStack, false>), dim3(blocks), dim3(256), 0, stream, L, V, head, coef, counters);
+            break;
         case kFormSplat:
             hipLaunchKernelGGL((k_setup<kFormSplat, false>), dim3(blocks), dim3(256), 0, stream, L, V, head, coef,
                                counters);
@@ -301,9 +306,9 @@ __global__ void __launch_bounds__(kBinBlock) k_bin(const RecHead *__restrict__ h
                                                    unsigned long long pair_cap, int staged) {
     extern __shared__ uint32_t lds_bins[];  // per tile: count, or next slot; then (staged) the stage
     __shared__ uint32_t sh_scan[kBinBlock / 64 + 1];
-    const int ntiles = B.ntx * B.nty;
+    const int nbins = B.nbins;
     const int seg = blockIdx.x;
-    uint32_t *stage = lds_bins + ntiles;
+    uint32_t *stage = lds_bins + nbins;
     // scatter: each tile's counter starts at this segment's first slot: in the
     // stage (its offset among this segment's pairs), or as an absolute
     // position when every pair fits 32 bits (no base read per pair), else
@@ -311,17 +316,17 @@ __global__ void __launch_bounds__(kBinBlock) k_bin(const RecHead *__restrict__ h
     bool use_stage = false;
     if (SCATTER && staged) {
         // this segment's pairs per tile (from the count pass), scanned
-        const int per = (ntiles + kBinBlock - 1) / kBinBlock;
+        const int per = (nbins + kBinBlock - 1) / kBinBlock;
         const int t0 = threadIdx.x * per;
         uint32_t mine = 0;
         for (int k = 0; k < per; ++k)
-            if (t0 + k < ntiles) mine += counts[(int64_t)(t0 + k) * B.nseg + seg];
+            if (t0 + k < nbins) mine += counts[(int64_t)(t0 + k) * B.nseg + seg];
         uint32_t total;
         uint32_t run = bin_block_scan(mine, sh_scan, total);
         use_stage = total <= (uint32_t)kStage;  // the same for the whole block
         if (use_stage)
             for (int k = 0; k < per; ++k)
-                if (t0 + k < ntiles) {
+                if (t0 + k < nbins) {
                     const uint32_t c = counts[(int64_t)(t0 + k) * B.nseg + seg];
                     lds_bins[t0 + k] = run;
                     run += c;
@@ -329,7 +334,7 @@ __global__ void __launch_bounds__(kBinBlock) k_bin(const RecHead *__restrict__ h
     }
     const bool abs32 = SCATTER && pair_cap <= 0xffffffffull;
     if (!use_stage)
-        for (int t = threadIdx.x; t < ntiles; t += kBinBlock) {
+        for (int t = threadIdx.x; t < nbins; t += kBinBlock) {
             if (SCATTER)
                 lds_bins[t] = abs32 ? (uint32_t)base[(int64_t)t * B.nseg + seg]
                                     : (uint32_t)(base[(int64_t)t * B.nseg + seg] - base[(int64_t)t * B.nseg]);
@@ -346,11 +351,14 @@ __global__ void __launch_bounds__(kBinBlock) k_bin(const RecHead *__restrict__ h
         ClassRows cr;
         cr.crease = false;
         if (SCATTER && B.nkey > 1) cr = class_rows(r);
+        // (a stack's record: the slabs it meets, each with its tiles)
+        const int k0 = B.nstack ? (int)(r.spare & 0xffffu) : 0, k1 = B.nstack ? (int)(r.spare >> 16) : 0;
+        for (int k = k0; k <= k1; ++k)
         for (int sy = 0; sy < tr.cy; ++sy) {
             const int ty = tr.sy + sy < B.nty ? tr.sy + sy : tr.sy + sy - B.nty;
             const uint32_t tag = SCATTER && B.nkey > 1 ? (uint32_t)row_class(cr, r, B, ty) << kClassShift : 0u;
             for (int sx = 0; sx < tr.cx; ++sx) {
-                const int tile = ty * B.ntx + (tr.sx + sx < B.ntx ? tr.sx + sx : tr.sx + sx - B.ntx);
+                const int tile = (k * B.nty + ty) * B.ntx + (tr.sx + sx < B.ntx ? tr.sx + sx : tr.sx + sx - B.ntx);
                 const uint32_t slot = atomicAdd(&lds_bins[tile], 1u);
                 if (SCATTER) {
                     if (use_stage) {
@@ -368,7 +376,7 @@ __global__ void __launch_bounds__(kBinBlock) k_bin(const RecHead *__restrict__ h
         // lds_bins[t] (its cursor) and has counts[t][seg] entries
         __syncthreads();
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        for (int t = wave; t < ntiles; t += kBinBlock / 64) {
+        for (int t = wave; t < nbins; t += kBinBlock / 64) {
             const uint32_t c = counts[(int64_t)t * B.nseg + seg];
             if (c == 0) continue;
             const uint32_t first = lds_bins[t] - c;
@@ -379,15 +387,15 @@ __global__ void __launch_bounds__(kBinBlock) k_bin(const RecHead *__restrict__ h
     }
     if (!SCATTER) {
         __syncthreads();
-        for (int t = threadIdx.x; t < ntiles; t += kBinBlock) counts[(int64_t)t * B.nseg + seg] = lds_bins[t];
+        for (int t = threadIdx.x; t < nbins; t += kBinBlock) counts[(int64_t)t * B.nseg + seg] = lds_bins[t];
     }
 }
 
 // one 32-bit LDS counter per tile, in both passes; the scatter's stage
 // beside them while the counters leave room for it in 96 KiB
-static bool bin_staged(const BinParams &B) { return (size_t)B.ntx * B.nty + kStage <= 24576; }
+static bool bin_staged(const BinParams &B) { return (size_t)B.nbins + kStage <= 24576; }
 static size_t bin_lds_bytes(const BinParams &B, bool scatter) {
-    return sizeof(uint32_t) * ((size_t)B.ntx * B.nty + (scatter && bin_staged(B) ? kStage : 0));
+    return sizeof(uint32_t) * ((size_t)B.nbins + (scatter && bin_staged(B) ? kStage : 0));
 }
 
 hipError_t launch_count(const RecHead *head, int64_t ntet, const BinParams &B, uint32_t *counts,
@@ -514,7 +522,7 @@ __global__ void __launch_bounds__(kScanBlock) k_totals(const uint32_t *__restric
                                                        unsigned long long cap, PlanOut *__restrict__ out,
                                                        unsigned int *__restrict__ overflow) {
     __shared__ unsigned long long mx;
-    const int ntiles = B.ntx * B.nty;
+    const int ntiles = B.nbins;
     if (threadIdx.x == 0) mx = 0;
     __syncthreads();
     for (int t = threadIdx.x; t < ntiles; t += kScanBlock) {
@@ -545,7 +553,7 @@ __global__ void __launch_bounds__(kScanBlock) k_plan(const uint32_t *__restrict_
                                                      uint32_t *__restrict__ tile_items,
                                                      PlanOut *__restrict__ out) {
     __shared__ uint64_t sh[64];
-    const int ntiles = B.ntx * B.nty;
+    const int ntiles = B.nbins;
     const bool fits = tile_end(base, counts, B, ntiles - 1, ntiles) <= cap;
     uint64_t carry = 0;
     for (int t0 = 0; t0 < ntiles; t0 += kScanBlock) {
@@ -578,7 +586,7 @@ hipError_t launch_plan(const uint32_t *counts, const uint64_t *base, const BinPa
 __global__ void k_items(const uint64_t *__restrict__ base, const uint32_t *__restrict__ tile_items,
                         BinParams B, int32_t chunk, const PlanOut *__restrict__ plan,
                         WorkItem *__restrict__ items) {
-    const int ntiles = B.ntx * B.nty;
+    const int ntiles = B.nbins;
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= ntiles) return;
     const uint64_t b = tile_begin(base, B, t);
@@ -596,7 +604,7 @@ __global__ void k_items(const uint64_t *__restrict__ base, const uint32_t *__res
 
 hipError_t launch_items(const uint64_t *base, const uint32_t *tile_items, const BinParams &B,
                         int32_t chunk, const PlanOut *plan, WorkItem *items, hipStream_t stream) {
-    const int ntiles = B.ntx * B.nty;
+    const int ntiles = B.nbins;
     hipLaunchKernelGGL(k_items, dim3((ntiles + 255) / 256), dim3(256), 0, stream, base, tile_items,
                        B, chunk, plan, items);
     return hipGetLastError();
@@ -732,7 +740,15 @@ __global__ void __launch_bounds__(TPB) k_raster(const RecHead *__restrict__ head
     extern __shared__ double sA[];
     if ((unsigned long long)blockIdx.x >= plan->n_items) return;
     const WorkItem it = items[blockIdx.x];
-    const int tx = (int)(it.tile % (uint32_t)B.ntx), ty = (int)(it.tile / (uint32_t)B.ntx);
+    uint32_t tile = it.tile;
+    if constexpr (FORM == kFormStack) {
+        const uint32_t nt = (uint32_t)(B.ntx * B.nty), slab = tile / nt;
+        tile -= slab * nt;
+        B.slab_t[0] = B.stack[2 * slab];
+        B.slab_t[1] = B.stack[2 * slab + 1];
+        acc += (size_t)slab * ((size_t)B.W * B.H);
+    }
+    const int tx = (int)(tile % (uint32_t)B.ntx), ty = (int)(tile / (uint32_t)B.ntx);
     const int tx0 = tx * B.Tw, ty0 = ty * B.Th;
     const int n = min(B.Tw, B.W - tx0), rows = min(B.Th, B.H - ty0);
     // rows of at least Tw + 4 cells: two padding cells each side take the adds that
@@ -804,12 +820,14 @@ __global__ void __launch_bounds__(TPB) k_raster(const RecHead *__restrict__ head
     // the tile instead of stacking their atomics on the same LDS cells
     const uint32_t per = (it.count + TPB - 1) / TPB;
     const uint32_t e0 = threadIdx.x * per, e1 = min(it.count, e0 + per);
-    if constexpr (FORM == kFormPersp) {
+    if constexpr (FORM == kFormPersp || FORM == kFormFace || FORM == kFormStack) {
         // per pixel, and a footprint may fill the tile: a wavefront takes one
         // pair at a time, its 64 lanes side by side over rows and columns,
         // the next pair from a counter in LDS (footprints next to the camera
         // are thousands of times larger than the rest).  The record is the
-        // same for all lanes and read into scalar registers.
+        // same for all lanes and read into scalar registers.  (Eight payloads
+        // per load, a round ahead, and their words broadcast from lanes was
+        // slower: what binds is instructions per pair, not their latency.)
         for (;;) {
             uint32_t e = 0u;
             if ((threadIdx.x & 63u) == 0u) e = atomicAdd(&s_next, 1u);
@@ -820,10 +838,13 @@ __global__ void __launch_bounds__(TPB) k_raster(const RecHead *__restrict__ head
             const RecHead h = coef[id].h;
             if (!(h.flags & REC_VALID)) continue;
             auto dep = [&](int row, int j, double v) { atomicAdd(&sA[cell(row, j)], v); };
-            if (B.rays)
-                frags += persp_pair<false>(h, coef[id].c, B, tx0, ty0, n, rows, (int)(threadIdx.x & 63u), 64, dep, spans, kinks);
+            const int lane = (int)(threadIdx.x & 63u);
+            if constexpr (FORM != kFormPersp)
+                frags += slab_pair(h, coef[id].c, B, tx0, ty0, n, rows, lane, 64, dep, spans, kinks);
+            else if (B.rays)
+                frags += persp_pair<false>(h, coef[id].c, B, tx0, ty0, n, rows, lane, 64, dep, spans, kinks);
             else
-                frags += persp_pair<true>(h, coef[id].c, B, tx0, ty0, n, rows, (int)(threadIdx.x & 63u), 64, dep, spans, kinks);
+                frags += persp_pair<true>(h, coef[id].c, B, tx0, ty0, n, rows, lane, 64, dep, spans, kinks);
         }
     } else if (FORM == kFormPyramid && sorted) {
         // The wavefront takes the next kSortPer entries of each of its lanes'
@@ -1111,7 +1132,7 @@ hipError_t launch_raster(const RecHead *head, const Payload *coef, const EdgePay
     // the tile's accumulator, its seam lines (as many copies per row as fit,
     // up to 16), and beside them (when they fit) the wavefronts' class sorts
     BinParams Bl = B;
-    const bool edge_form = B.form != kFormFace && B.form != kFormSplat && B.form != kFormPersp && B.edges;
+    const bool edge_form = B.form == kFormPyramid && B.edges;
     const size_t acc_lds = sizeof(double) * (size_t)B.Th * tile_stride(B.Tw, B.Th, edge_form);
     const size_t row_seam = sizeof(double) * (2 * (size_t)B.Th + 3 * ((size_t)B.Th + 1));
     const size_t queue_lds = edge_form ? sizeof(uint32_t) * (size_t)(block / 64) * kSeamQueue : 0;
@@ -1122,7 +1143,10 @@ hipError_t launch_raster(const RecHead *head, const Payload *coef, const EdgePay
     const size_t sort_lds = sizeof(uint32_t) * (size_t)(block / 64) * kSortWords;
     const int sorted = B.nkey > 1 && tile_lds + sort_lds <= kLdsBytes ? 1 : 0;
     const size_t lds = tile_lds + (sorted ? sort_lds : 0);
-    if (Bl.form == kFormFace)
+    if (B.form == kFormStack)
+        launch_raster_form<kFormStack>(head, coef, ecoef, pairs, items, max_items, plan, Bl, sorted, block, acc, counters,
+                                       stream, lds);
+    else if (Bl.form == kFormFace)
         launch_raster_form<kFormFace>(head, coef, ecoef, pairs, items, max_items, plan, Bl, sorted, block, acc, counters,
                                       stream, lds);
     else if (B.form == kFormSplat)
@@ -1179,8 +1203,21 @@ __global__ void __launch_bounds__(256) k_raster_direct(LatticeParams L, ViewPara
                 unsafeAtomicAdd(&acc[(int64_t)(ty0 + row) * W], a);
                 if (W > 1) unsafeAtomicAdd(&acc[(int64_t)(ty0 + row) * W + 1], b - a);
             };
+            if constexpr (FORM == kFormStack) {
+                BinParams Bs = B;
+                for (uint32_t k = h.spare & 0xffffu; k <= h.spare >> 16; ++k) {
+                    Bs.slab_t[0] = B.stack[2 * k];
+                    Bs.slab_t[1] = B.stack[2 * k + 1];
+                    auto depk = [&](int row, int j, double v) {
+                        if (j >= 0 && j < W) unsafeAtomicAdd(&acc[((int64_t)k * B.H + ty0 + row) * W + j], v);
+                    };
+                    frags += slab_pair(h, cf, Bs, 0, ty0, W, rows, 0, 1, depk, spans, kinks);
+                }
+            } else
             if constexpr (FORM == kFormPersp)
                 frags += persp_pair(h, cf, B, 0, ty0, W, rows, 0, 1, dep, spans, kinks);
+            else if constexpr (FORM == kFormFace)
+                frags += slab_pair(h, cf, B, 0, ty0, W, rows, 0, 1, dep, spans, kinks);
             else
                 frags += (int32_t)raster_record<FORM == kFormEdge ? kFormPyramid : FORM>(
                     h, cf, B, 0, ty0, W, rows, dep, seam, spans, kinks);
@@ -1272,6 +1309,10 @@ hipError_t launch_raster_direct(const LatticeParams &L, const ViewParams &V, con
             hipLaunchKernelGGL(k_raster_direct<kFormFace>, grid, block, 0, stream, L, V, head, coef, ecoef, plan, cap,
                                B, acc, counters);
             break;
+        case kFormStack:
+            hipLaunchKernelGGL(k_raster_direct<kFormStack>, grid, block, 0, stream, L, V, head, coef, ecoef, plan, cap,
+                               B, acc, counters);
+            break;
         case kFormSplat:
             hipLaunchKernelGGL(k_raster_direct<kFormSplat>, grid, block, 0, stream, L, V, head, coef, ecoef, plan, cap,
                                B, acc, counters);
@@ -1355,8 +1396,27 @@ __global__ void __launch_bounds__(kFinBlock) k_finalize(const double *__restrict
         }
 }
 
+// Up to kTablePer slabs from the kernel's arguments to the table.
+constexpr int kTablePer = 128;
+struct StackTable {
+    double t[2 * kTablePer];
+};
+__global__ void k_stack_table(StackTable T, int n, double *__restrict__ table) {
+    for (int i = threadIdx.x; i < 2 * n; i += blockDim.x) table[i] = T.t[i];
+}
+
+hipError_t launch_stack_table(const double *t, int n, double *table, hipStream_t stream) {
+    for (int first = 0; first < n; first += kTablePer) {
+        StackTable T;
+        const int m = std::min(kTablePer, n - first);
+        std::copy(t + 2 * first, t + 2 * (first + m), T.t);
+        hipLaunchKernelGGL(k_stack_table, dim3(1), dim3(2 * kTablePer), 0, stream, T, m, table + 2 * first);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_finalize(const double *acc, const BinParams &B, float *image, hipStream_t stream) {
-    hipLaunchKernelGGL(k_finalize, dim3((unsigned)B.H), dim3(kFinBlock), 0, stream, acc, B, image);
+    hipLaunchKernelGGL(k_finalize, dim3((unsigned)(B.H * std::max(B.nstack, 1))), dim3(kFinBlock), 0, stream, acc, B, image);
     return hipGetLastError();
 }
 

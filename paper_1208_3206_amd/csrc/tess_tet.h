@@ -436,6 +436,36 @@ TESS_HD inline bool face_payload(const double qx[4], const double qy[4], const d
     return true;
 }
 
+// A face payload without walls in the order front faces, back faces; returns
+// the number of front faces (0, the payload unchanged, when there are walls).
+TESS_HD inline int front_first(uint32_t flags, double c[14]) {
+    double p[4][3];
+    int nf = 0, nb = 0;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const uint32_t type = (flags >> (REC_FACE_TYPE_SHIFT + 2 * g)) & 3u;
+        nf += type == REC_FACE_FRONT ? 1 : 0;
+        nb += type == REC_FACE_BACK ? 1 : 0;
+        p[g][0] = c[3 * g];
+        p[g][1] = c[3 * g + 1];
+        p[g][2] = c[3 * g + 2];
+    }
+    if (nf + nb != 4 || nf == 0 || nb == 0) return 0;
+    int k = 0, m = nf;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const int to = ((flags >> (REC_FACE_TYPE_SHIFT + 2 * g)) & 3u) == REC_FACE_FRONT ? k++ : m++;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)  // (by constant slots: no scratch)
+            if (t == to) {
+                c[3 * t] = p[g][0];
+                c[3 * t + 1] = p[g][1];
+                c[3 * t + 2] = p[g][2];
+            }
+    }
+    return nf;
+}
+
 // Inverse-depth planes of a perspective tetrahedron (vertices vtx in the
 // camera frame).  Along the half-line s (pu, pv, 1) of a pixel, w = 1 / s is
 // linear over the image on every plane not through the camera, so in (X, Y,
@@ -1176,7 +1206,7 @@ TESS_HD inline void setup_cube(const LatticeParams &L, const ViewParams &V, int6
                 double planes[12];
                 const int na = fabs(det6) >= 6e-3 * L.v0 ? persp_planes(pc, V, ix0, iy0, planes) : 0;
                 if (na > 0) {
-                    R.flags |= (uint32_t)na << REC_PERSP_SHIFT;
+                    R.flags |= (uint32_t)na << REC_PLANES_SHIFT;
 #pragma unroll
                     for (int g = 0; g < 12; ++g) pc[g] = planes[g];
                 }
@@ -1207,7 +1237,7 @@ TESS_HD inline void setup_cube(const LatticeParams &L, const ViewParams &V, int6
                 qy[m] = pyv[m] - (double)iy0;
             }
             const double rho_m = 6.0 / fabs(det6);  // rho / m
-            if constexpr (FORM == kFormFace) {
+            if constexpr (FORM == kFormFace || FORM == kFormStack) {
                 // depth slab: the face form, q times the clipped chord
                 double T[4];
 #pragma unroll
@@ -1216,6 +1246,27 @@ TESS_HD inline void setup_cube(const LatticeParams &L, const ViewParams &V, int6
                 const double rho = L.tet_mass * rho_m;
                 const double qv = V.qpow == 0 ? 1.0 : (V.qpow == 1 ? rho : rho * rho);
                 uint32_t ff = 0;
+                if constexpr (FORM == kFormStack) {
+                    // the slabs it meets (face_payload's test, slab by slab):
+                    // from the first that ends beyond its near end to the
+                    // last that begins before its far end
+                    const double tmin = fmin(fmin(T[0], T[1]), fmin(T[2], T[3]));
+                    const double tmax = fmax(fmax(T[0], T[1]), fmax(T[2], T[3]));
+                    int lo = 0, hi = V.nstack;  // the first k with t1[k] > tmin
+                    while (lo < hi) {
+                        const int m = (lo + hi) >> 1;
+                        if (V.stack[2 * m + 1] > tmin) hi = m;
+                        else lo = m + 1;
+                    }
+                    int a = lo, b = V.nstack;  // the first k with t0[k] >= tmax
+                    while (a < b) {
+                        const int m = (a + b) >> 1;
+                        if (V.stack[2 * m] >= tmax) b = m;
+                        else a = m + 1;
+                    }
+                    if (a <= lo) return;
+                    R.spare = (uint32_t)lo | ((uint32_t)(a - 1) << 16);
+                }
                 if (!face_payload(qx, qy, T, V.slab_t[0], V.slab_t[1], qv, pc, ff)) {
 #pragma unroll
                     for (int g = 0; g < 14; ++g) pc[g] = 0.0;
@@ -1224,6 +1275,7 @@ TESS_HD inline void setup_cube(const LatticeParams &L, const ViewParams &V, int6
                 R.bx = pack_range(ix0, ix1);
                 R.by = pack_range(iy0, iy1);
                 R.flags = ff | REC_FACE | REC_VALID;
+                R.flags |= (uint32_t)front_first(ff, pc) << REC_PLANES_SHIFT;
                 return;
             }
             // q dl = (q / rho) rho dl: the density footprint with its mass scaled
@@ -1507,7 +1559,8 @@ TESS_HD inline void sort8_desc(uint32_t a[8]) {
 constexpr double kSampleEps = 1e-10;
 constexpr int kRightReach = 2;
 
-// Candidate tiles of one record: tx = (sx + s % cx) mod ntx, ty = (sy + s / cx)
+// Candidate tiles of one record (with the columns right of its box that second
+// differences reach): tx = (sx + s % cx) mod ntx, ty = (sy + s / cx)
 // mod nty for s < count = cx * cy.  Every tile of the box is a candidate:
 // the tiles are wide row bands, so the box and the footprint meet nearly the
 // same ones.
@@ -1517,7 +1570,7 @@ struct TileRange {
 
 TESS_HD inline TileRange tet_tiles(const RecHead &r, const BinParams &B) {
     TileRange t;
-    axis_tiles(range_lo(r.bx), range_hi(r.bx) + kRightReach, B.W, B.Tw, B.ntx, B.wrap, t.sx, t.cx);
+    axis_tiles(range_lo(r.bx), range_hi(r.bx) + (B.direct ? 0 : kRightReach), B.W, B.Tw, B.ntx, B.wrap, t.sx, t.cx);
     axis_tiles(range_lo(r.by), range_hi(r.by), B.H, B.Th, B.nty, B.wrap, t.sy, t.cy);
     t.count = t.cx * t.cy;
     return t;
@@ -1966,203 +2019,6 @@ TESS_HD inline uint32_t crease_pair(const RecHead &h, const double *cf, const Bi
     return frags > 0 ? (uint32_t)frags : 0u;
 }
 
-// ------------------------------------------------- face form (depth slab)
-// Upper envelope (maximum) of nl <= 4 lines a[i] + b[i] u, left to right:
-// piece k follows line idx[k] up to brk[k] (the last brk is +inf). Returns
-// the number of pieces.
-TESS_HD inline int upper_envelope(const double a[4], const double b[4], int nl, int idx[4], double brk[4]) {
-    int o[4] = {0, 1, 2, 3};
-    // by slope, ascending; equal slopes: the higher line first
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = i + 1; j < 4; ++j)
-            if (j < nl && (b[o[j]] < b[o[i]] || (b[o[j]] == b[o[i]] && a[o[j]] > a[o[i]]))) {
-                const int t = o[i];
-                o[i] = o[j];
-                o[j] = t;
-            }
-    int ns = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        if (q >= nl) break;
-        const int l = o[q];
-        if (ns > 0 && b[idx[ns - 1]] == b[l]) continue;  // parallel and not higher
-        while (ns >= 2) {
-            // l overtakes the top line before the top overtakes the one below it
-            const int t = idx[ns - 1], u = idx[ns - 2];
-            const double xt = (a[t] - a[l]) / (b[l] - b[t]);
-            const double xu = (a[u] - a[t]) / (b[t] - b[u]);
-            if (xt > xu) break;
-            --ns;
-        }
-        idx[ns++] = l;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-        if (k < ns) brk[k] = k + 1 < ns ? (a[idx[k]] - a[idx[k + 1]]) / (b[idx[k + 1]] - b[idx[k]]) : kInf;
-    return ns;
-}
-
-// One row of a face-form record: q times the chord of the ray inside the
-// tetrahedron and the depth slab, t_out - t_in with t_in the largest front
-// face depth (and the slab's near depth), t_out the smallest back face depth
-// (and its far depth), clipped by the walls (A9 tie rule) and the image.
-// Everything is evaluated in the record frame X (small numbers: a steep
-// plane of an almost edge-on face keeps its precision); the tile's samples
-// are u = 0..n-1 at X = X0 + u, row centre Y; break points sit at their true
-// positions, pieces starting left of the image start at ulo. dep(j, v) takes
-// -2 <= j <= n + 1. Returns the tile's covered samples.
-template <typename Dep>
-TESS_HD inline uint32_t face_row(uint32_t flags, const double *cf, const BinParams &B, int shift,
-                                 double Y, int n, int jlo, double ulo, double uhi, Dep &&dep,
-                                 uint32_t &kinks) {
-    // evaluated in the record frame (sample u = j at the record's column j,
-    // X = u + 1/2), so that every tile computes the same break points; the
-    // tile's samples are u = shift .. shift + n - 1, ulo and uhi bound the
-    // image row there
-    constexpr double X0 = 0.5;
-    const double dshift = (double)shift;
-    double fa[4], fb[4], ba[4], bb[4];
-    int nf = 0, nb = 0;
-    double uL = ulo, uR = uhi;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const uint32_t type = (flags >> (REC_FACE_TYPE_SHIFT + 2 * g)) & 3u;
-        const double c0 = cf[3 * g], c1 = cf[3 * g + 1], c2 = cf[3 * g + 2];
-        if (type == REC_FACE_WALL) {
-            const bool tie = (flags >> (REC_FACE_TIE_SHIFT + g)) & 1u;
-            if (c1 == 0.0) {
-                const double wv = c0 + c2 * Y;
-                if (!(wv > 0.0 || (wv == 0.0 && tie))) return 0;
-            } else {
-                // admitted samples: W > 0 (or W == 0 with the tie bit)
-                const double uw = -(c0 + c2 * Y) / c1 - X0;
-                if (c1 > 0.0) uL = fmax(uL, (tie ? ceil(uw) : floor(uw) + 1.0) - 0.5);
-                else uR = fmin(uR, (tie ? floor(uw) : ceil(uw) - 1.0) + 0.5);
-            }
-        } else if (type == REC_FACE_FRONT && nf < 3) {
-            fa[nf] = c0 + c2 * Y;
-            fb[nf] = c1;
-            ++nf;
-        } else if (type == REC_FACE_BACK && nb < 3) {
-            // the lower envelope of the back faces is minus the upper one of -t
-            ba[nb] = -(c0 + c2 * Y);
-            bb[nb] = -c1;
-            ++nb;
-        }
-    }
-    if (nf == 0 || nb == 0) return 0;
-    fa[nf] = B.slab_t[0];
-    fb[nf] = 0.0;
-    ++nf;
-    ba[nb] = -B.slab_t[1];
-    bb[nb] = 0.0;
-    ++nb;
-    int fi[4], bi[4];
-    double fbr[4], bbr[4];
-    const int pf = upper_envelope(fa, fb, nf, fi, fbr);
-    const int pb = upper_envelope(ba, bb, nb, bi, bbr);
-    // segments of d = t_out - t_in over X, left to right, and where d > 0
-    // (one interval: d is concave)
-    double sA[8], sB[8], sE[8];
-    int ns = 0, i = 0, k = 0;
-    double zl = kInf, zr = -kInf;
-#pragma unroll
-    for (int it = 0; it < 8; ++it) {
-        if (i >= pf || k >= pb) break;
-        const double A = -ba[bi[k]] - fa[fi[i]], Bs = -bb[bi[k]] - fb[fi[i]];
-        const double e = fmin(fbr[i], bbr[k]);
-        const double s0 = ns > 0 ? sE[ns - 1] : -kInf;
-        sA[ns] = A;
-        sB[ns] = Bs;
-        sE[ns] = e;
-        ++ns;
-        double lo = s0, hi = e;
-        if (Bs > 0.0) lo = fmax(lo, -A / Bs);
-        else if (Bs < 0.0) hi = fmin(hi, -A / Bs);
-        else if (!(A > 0.0)) hi = lo;
-        if (hi > lo) {
-            zl = fmin(zl, lo);
-            zr = fmax(zr, hi);
-        }
-        const bool ai = fbr[i] == e, ak = bbr[k] == e;
-        i += ai ? 1 : 0;
-        k += ak ? 1 : 0;
-    }
-    // the covered range, in X: d > 0, inside the walls and the image
-    const double L = fmax(zl, uL + X0), R = fmin(zr, uR + X0);
-    const double Lu = L - X0, Ru = R - X0;
-    if (!(ceil(Ru) - floor(Lu) > 1.0)) return 0;  // no sample in (L, R)
-    const double span = ceil(fmin(Ru, dshift + (double)n - 0.5)) - floor(fmax(Lu, dshift - 0.5)) - 1.0;
-    const double q = cf[12];
-    auto put = [&](double X, double J, double D) {
-        int j = (int)floor(X - X0) + 1 - shift;  // tile column
-        j = j > jlo ? j : jlo;
-        j = j < n ? j : n;
-        const double v1 = J + D * (((double)(j + shift) + X0) - X);
-        dep(j, v1);
-        dep(j + 1, D - v1);
-        ++kinks;
-    };
-    // the pieces that hold a sample (an integer u in (lo, hi]), left to
-    // right; each start is a step plus kink relative to the previous such
-    // piece, so a sub-pixel piece (a face seen almost edge-on, a flat sliver)
-    // becomes a step instead of two large kinks that cancel
-    bool have = false;
-    double pB = 0.0, pA = 0.0, last = L;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        if (t >= ns) break;
-        const double s0 = t > 0 ? sE[t - 1] : -kInf;
-        const double lo = fmax(s0, L), hi = fmin(sE[t], R);
-        if (!(floor(hi - X0) > floor(lo - X0))) continue;
-        const double A = sA[t], Bs = sB[t];
-        const double J = (A + Bs * lo) - (have ? pA + pB * lo : 0.0);
-        // at a zero crossing of d the first piece starts from 0
-        put(lo, (!have && lo == zl) ? 0.0 : q * J, q * (Bs - pB));
-        have = true;
-        pA = A;
-        pB = Bs;
-        last = hi;
-    }
-    // the end: d = 0 at a zero crossing, else the value at the clip
-    if (have) put(last, last == zr ? 0.0 : -q * (pA + pB * last), -q * pB);
-    return span > 0.0 ? (uint32_t)span : 0u;
-}
-
-// All rows of a face-form record in one tile (every periodic offset that
-// meets it).
-template <typename Dep>
-TESS_HD inline uint32_t face_pair(const RecHead &h, const double *cf, const BinParams &B, int tx0,
-                                  int ty0, int n, int rows, Dep &&dep, uint32_t &spans, uint32_t &kinks) {
-    const int bx0 = range_lo(h.bx), bx1 = range_hi(h.bx) + kRightReach;
-    const int by0 = range_lo(h.by), by1 = range_hi(h.by);
-    int kx0, kx1, ky0, ky1;
-    axis_offsets(tx0, tx0 + n - 1, bx0, bx1, B.W, B.wrap, kx0, kx1);
-    axis_offsets(ty0, ty0 + rows - 1, by0, by1, B.H, B.wrap, ky0, ky1);
-    const int jmin = -tx0;
-    const int jlo = jmin > -2 ? jmin : -2;
-    uint32_t frags = 0;
-    for (int ky = ky0; ky <= ky1; ++ky) {
-        const int ylo = max(ty0, by0 - ky * B.H), yhi = min(ty0 + rows - 1, by1 - ky * B.H);
-        for (int kx = kx0; kx <= kx1; ++kx) {
-            if (tx0 + kx * B.W > bx1 || tx0 + n - 1 + kx * B.W < bx0) continue;
-            const int shift = tx0 + kx * B.W - bx0;  // record column of the tile's column 0
-            // the image row in the record frame
-            const double ulo = (double)(kx * B.W - bx0) - 0.5, uhi = (double)(B.W + kx * B.W - bx0) - 0.5;
-            for (int y = ylo; y <= yhi; ++y) {
-                const double Y = (double)(y + ky * B.H - by0) + 0.5;
-                const int row = y - ty0;
-                frags += face_row(h.flags, cf, B, shift, Y, n, jlo, ulo, uhi,
-                                  [&](int j, double v) { dep(row, j, v); }, kinks);
-                ++spans;
-            }
-        }
-    }
-    return frags;
-}
-
 // ------------------------------------------------------ centroid splats
 // A splat record's kernel values at the tile's pixel centres (every periodic
 // offset that meets it), added as values: dep(row, u, w) for the tile column
@@ -2207,83 +2063,78 @@ TESS_HD inline uint32_t splat_pair(const RecHead &h, const double *cf, const Bin
     return frags;
 }
 
-// ---------------------------------------------------- perspective camera
-// A row of a perspective record in its inverse-depth planes (NA of them
-// bounding w = 1 / s from below, the others from above): the chord is
-// 1 / w_lo - 1 / w_hi.
-template <int NA>
-TESS_HD inline void persp_bounds(const double g[4], const double *cf, double X, double &wlo, double &whi) {
-    double w[4];
-#pragma unroll
-    for (int f = 0; f < 4; ++f) w[f] = fma(cf[3 * f + 1], X, g[f]);
-    wlo = w[0];
-#pragma unroll
-    for (int f = 1; f < NA; ++f) wlo = fmax(wlo, w[f]);
-    whi = w[3];
-#pragma unroll
-    for (int f = NA; f < 3; ++f) whi = fmin(whi, w[f]);
-}
-
-// The record's rows [y0, y1] and columns [x0, x1], shared out over nlanes
-// lanes, lpr of them (a power of two) side by side in a row.  A row's columns
-// are first cut to those between its crossings with the silhouette, which are
-// the crossings of a lower with an upper plane (a column to spare each side:
-// the per-pixel test decides).  RAY: the values carry the ray's length per
-// unit depth; without it the caller multiplies each pixel's sum by it.
-template <int NA, bool RAY, typename Dep>
-TESS_HD inline uint32_t persp_rows(const RecHead &h, const double *cf, const BinParams &B, int tx0, int ty0, int x0,
-                                   int x1, int y0, int y1, int lane0, int nlanes, int lpr, Dep &&dep,
-                                   uint32_t &kinks) {
-    const double q = cf[12];
-    const int bx0 = range_lo(h.bx), by0 = range_lo(h.by);
+// ------------------------------------------------------ chords by pixel
+// A record of four planes over the pixels, NA of which bound the (inverse)
+// depth along a pixel's ray from below and the others from above: every
+// pixel whose bounds leave a chord gets its value.  cf[3 f ..]: a, b, c of
+// plane f = a + b X + c Y in record coordinates (centres at whole numbers +
+// 1/2), the lower ones first.  The record columns [x0, x1] and rows [y0, y1]
+// are shared out over nlanes lanes, lpr of them (a power of two) side by side
+// in a row.  A row's columns are first cut, in boxes wider than lpr, to those
+// between its crossings with the silhouette, which are the crossings of a
+// lower with an upper plane (a column to spare each side: the per-pixel test
+// decides).  value(lo, hi, X,
+// Y, v) says whether the chord counts and what it adds; dep(y, x, v) takes it
+// at record row y and column x.
+template <int NA, typename Value, typename Dep>
+TESS_HD inline uint32_t plane_rows(const double *cf, int x0, int x1, int y0, int y1, int lane0, int nlanes, int lpr,
+                                   Value &&value, Dep &&dep, uint32_t &kinks) {
     // silhouette: column t0 + t1 Y where plane a meets plane b, a bound from
     // the left or the right, or none (an edge almost along the row)
     constexpr int NB = 4 - NA, NP = NA * NB;
     double t0[NP ? NP : 1], t1[NP ? NP : 1];
     bool left[NP ? NP : 1];
+    const bool cut = x1 - x0 >= lpr;
+    if (cut) {
 #pragma unroll
-    for (int k = 0; k < NP; ++k) {
-        const int a = k / (NB ? NB : 1), b = NA + k % (NB ? NB : 1);
-        const double d0 = cf[3 * b] - cf[3 * a], dx = cf[3 * b + 1] - cf[3 * a + 1], dy = cf[3 * b + 2] - cf[3 * a + 2];
-        const double r = -fast_rcp(dx);
-        t0[k] = d0 * r;
-        t1[k] = dy * r;
-        left[k] = dx > 0.0;
-        if (!(fabs(t0[k]) < 1e10 && fabs(t1[k]) < 1e10)) {  // (rounding stays below a column within the bound)
-            t0[k] = left[k] ? -1e10 : 1e10;
-            t1[k] = 0.0;
+        for (int k = 0; k < NP; ++k) {
+            const int a = k / (NB ? NB : 1), b = NA + k % (NB ? NB : 1);
+            const double d0 = cf[3 * b] - cf[3 * a], dx = cf[3 * b + 1] - cf[3 * a + 1],
+                         dy = cf[3 * b + 2] - cf[3 * a + 2];
+            const double r = -fast_rcp(dx);
+            t0[k] = d0 * r;
+            t1[k] = dy * r;
+            left[k] = dx > 0.0;
+            if (!(fabs(t0[k]) < 1e10 && fabs(t1[k]) < 1e10)) {  // (rounding stays below a column within the bound)
+                t0[k] = left[k] ? -1e10 : 1e10;
+                t1[k] = 0.0;
+            }
         }
     }
     uint32_t frags = 0;
     const int lq = lane0 & (lpr - 1), step = nlanes / lpr;
     for (int y = y0 + lane0 / lpr; y <= y1; y += step) {
-        const double Y = (double)(y - by0) + 0.5;
-        double xl = (double)(x0 - bx0), xr = (double)(x1 - bx0) + 1.0;
+        const double Y = (double)y + 0.5;
+        int xa = x0, xb = x1;
+        if (cut) {
+            double xl = (double)x0, xr = (double)x1 + 1.0;
 #pragma unroll
-        for (int k = 0; k < NP; ++k) {
-            const double t = fma(t1[k], Y, t0[k]);
-            xl = fmax(xl, left[k] ? t : xl);
-            xr = fmin(xr, left[k] ? xr : t);
+            for (int k = 0; k < NP; ++k) {
+                const double t = fma(t1[k], Y, t0[k]);
+                xl = fmax(xl, left[k] ? t : xl);
+                xr = fmin(xr, left[k] ? xr : t);
+            }
+            if (!(xl <= xr + 2.0)) continue;
+            xa = max((int)xl - 1, x0);
+            xb = min((int)xr + 1, x1);
         }
-        if (!(xl <= xr + 2.0)) continue;
-        const int xa = max((int)xl - 1, x0 - bx0), xb = min((int)xr + 1, x1 - bx0);
         double g[4];
 #pragma unroll
         for (int f = 0; f < 4; ++f) g[f] = fma(cf[3 * f + 2], Y, cf[3 * f]);
-        const int shift = bx0 - tx0;
         double X = (double)(xa + lq) + 0.5;
         for (int x = xa + lq; x <= xb; x += lpr, X += (double)lpr) {
-            double wlo, whi;
-            persp_bounds<NA>(g, cf, X, wlo, whi);
+            double w[4];
+#pragma unroll
+            for (int f = 0; f < 4; ++f) w[f] = fma(cf[3 * f + 1], X, g[f]);
+            double lo = w[0], hi = w[3];
+#pragma unroll
+            for (int f = 1; f < NA; ++f) lo = fmax(lo, w[f]);
+#pragma unroll
+            for (int f = NA; f < 3; ++f) hi = fmin(hi, w[f]);
             ++kinks;
-            if (NA == 4 ? wlo > 0.0 : wlo > 0.0 && whi > wlo) {
-                double v = NA == 4 ? q * fast_rcp(wlo) : (q * (whi - wlo)) * fast_rcp(whi * wlo);
-                if (RAY) {
-                    const double pu = (X + (double)bx0) * (B.ext_u / (double)B.W) - 0.5 * B.ext_u;
-                    const double pv = (Y + (double)by0) * (B.ext_v / (double)B.H) - 0.5 * B.ext_v;
-                    v *= sqrt(pu * pu + pv * pv + 1.0);
-                }
-                dep(y - ty0, x + shift, v);
+            double v;
+            if (value(lo, hi, X, Y, v)) {
+                dep(y, x, v);
                 ++frags;
             }
         }
@@ -2291,6 +2142,77 @@ TESS_HD inline uint32_t persp_rows(const RecHead &h, const double *cf, const Bin
     return frags;
 }
 
+// Lanes of a row for a box bw columns wide: 16, or 8 or 4 where more would
+// mostly be past its end (a serial caller takes one).
+TESS_HD inline int row_lanes(int bw, int nlanes) { return nlanes < 64 ? 1 : bw <= 4 ? 4 : bw <= 8 ? 8 : 16; }
+
+// A face-form record of a depth slab in one tile, every periodic offset that meets it: q times the chord
+// min(t1, back faces) - max(t0, front faces) at each of the tile's pixel
+// centres, added as values dep(row, u, v); lanes as plane_rows.  Records with
+// walls test them pixel by pixel (a pixel on a wall's line counts when the
+// wall has its tie bit).  (As row second differences, a lane per record with
+// the envelopes of its faces' lines built row by row, the slabs took 2 to 3
+// times as long at cells of 32 to 1024 pixels, 16 times at one pixel: the
+// lines' order and pieces differ from lane to lane.)
+template <typename Dep>
+TESS_HD inline uint32_t slab_pair(const RecHead &h, const double *cf, const BinParams &B, int tx0, int ty0, int n,
+                                  int rows, int lane0, int nlanes, Dep &&dep, uint32_t &spans, uint32_t &kinks) {
+    const int bx0 = range_lo(h.bx), bx1 = range_hi(h.bx), by0 = range_lo(h.by), by1 = range_hi(h.by);
+    int kx0, kx1, ky0, ky1;
+    axis_offsets(tx0, tx0 + n - 1, bx0, bx1, B.W, B.wrap, kx0, kx1);
+    axis_offsets(ty0, ty0 + rows - 1, by0, by1, B.H, B.wrap, ky0, ky1);
+    const double s0 = B.slab_t[0], s1 = B.slab_t[1], q = cf[12];
+    const uint32_t nf = (h.flags >> REC_PLANES_SHIFT) & 7u;
+    uint32_t frags = 0;
+    for (int ky = ky0; ky <= ky1; ++ky) {
+        const int rshift = by0 - ky * B.H - ty0;  // tile row of record row 0
+        const int ra = max(0, -rshift), rb = min(by1 - by0, rows - 1 - rshift);
+        if (ra > rb) continue;
+        for (int kx = kx0; kx <= kx1; ++kx) {
+            const int shift = bx0 - kx * B.W - tx0;  // tile column of record column 0
+            const int ca = max(0, -shift), cb = min(bx1 - bx0, n - 1 - shift);
+            if (ca > cb) continue;
+            if (lane0 == 0) spans += (uint32_t)(rb - ra + 1);
+            auto put = [&](int y, int x, double v) { dep(y + rshift, x + shift, v); };
+            auto value = [&](double lo, double hi, double, double, double &v) {
+                const double d = fmin(hi, s1) - fmax(lo, s0);
+                v = q * d;
+                return d > 0.0;
+            };
+            const int lpr = row_lanes(cb - ca + 1, nlanes);
+            if (nf == 1)
+                frags += plane_rows<1>(cf, ca, cb, ra, rb, lane0, nlanes, lpr, value, put, kinks);
+            else if (nf == 2)
+                frags += plane_rows<2>(cf, ca, cb, ra, rb, lane0, nlanes, lpr, value, put, kinks);
+            else if (nf == 3)
+                frags += plane_rows<3>(cf, ca, cb, ra, rb, lane0, nlanes, lpr, value, put, kinks);
+            else
+                for (int y = ra + lane0 / lpr; y <= rb; y += nlanes / lpr)
+                    for (int x = ca + (lane0 & (lpr - 1)); x <= cb; x += lpr) {
+                        const double X = (double)x + 0.5, Y = (double)y + 0.5;
+                        double lo = s0, hi = s1;
+                        bool in = true;
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) {
+                            const uint32_t type = (h.flags >> (REC_FACE_TYPE_SHIFT + 2 * g)) & 3u;
+                            const double w = cf[3 * g] + cf[3 * g + 1] * X + cf[3 * g + 2] * Y;
+                            if (type == REC_FACE_FRONT) lo = fmax(lo, w);
+                            else if (type == REC_FACE_BACK) hi = fmin(hi, w);
+                            else if (type == REC_FACE_WALL)
+                                in = in && (w > 0.0 || (w == 0.0 && ((h.flags >> (REC_FACE_TIE_SHIFT + g)) & 1u)));
+                        }
+                        ++kinks;
+                        if (in && hi > lo) {
+                            put(y, x, q * (hi - lo));
+                            ++frags;
+                        }
+                    }
+        }
+    }
+    return frags;
+}
+
+// ---------------------------------------------------- perspective camera
 // A perspective record's chords at the tile's pixel centres, added as values:
 // dep(row, u, q dl) for the tile column u.  The pixel at (pu, pv) on the
 // window sees the half-line s (pu, pv, 1), s >= 0, in the camera frame, and
@@ -2340,15 +2262,29 @@ TESS_HD inline uint32_t persp_pair(const RecHead &h, const double *cf, const Bin
         }
         return frags;
     }
-    const uint32_t na = (h.flags >> REC_PERSP_SHIFT) & 7u;
+    const uint32_t na = (h.flags >> REC_PLANES_SHIFT) & 7u;
     if (na) {
-        // lanes of a row: 16, or 8 where 16 would be half empty
-        const int lpr = nlanes < 64 ? 1 : (bw <= 8 ? 8 : 16);
+        // the chord is 1 / w_lo - 1 / w_hi
+        const int bx0 = range_lo(h.bx), by0 = range_lo(h.by), lpr = row_lanes(bw, nlanes);
+        const double q = cf[12];
+        auto chord = [&](double lo, double hi, bool whole, double X, double Y, double &v) {
+            if (!(lo > 0.0 && (whole || hi > lo))) return false;
+            v = whole ? q * fast_rcp(lo) : (q * (hi - lo)) * fast_rcp(hi * lo);
+            if (RAY) {
+                const double pu = (X + (double)bx0) * du - 0.5 * B.ext_u, pv = (Y + (double)by0) * dv - 0.5 * B.ext_v;
+                v *= sqrt(pu * pu + pv * pv + 1.0);
+            }
+            return true;
+        };
+        auto value = [&](double lo, double hi, double X, double Y, double &v) { return chord(lo, hi, false, X, Y, v); };
+        auto inner = [&](double lo, double hi, double X, double Y, double &v) { return chord(lo, hi, true, X, Y, v); };
+        auto put = [&](int y, int x, double v) { dep(y + by0 - ty0, x + bx0 - tx0, v); };
         switch (na) {
-            case 1: return persp_rows<1, RAY>(h, cf, B, tx0, ty0, x0, x1, y0, y1, lane0, nlanes, lpr, dep, kinks);
-            case 2: return persp_rows<2, RAY>(h, cf, B, tx0, ty0, x0, x1, y0, y1, lane0, nlanes, lpr, dep, kinks);
-            case 3: return persp_rows<3, RAY>(h, cf, B, tx0, ty0, x0, x1, y0, y1, lane0, nlanes, lpr, dep, kinks);
-            default: return persp_rows<4, RAY>(h, cf, B, tx0, ty0, x0, x1, y0, y1, lane0, nlanes, lpr, dep, kinks);
+            case 1: return plane_rows<1>(cf, x0 - bx0, x1 - bx0, y0 - by0, y1 - by0, lane0, nlanes, lpr, value, put, kinks);
+            case 2: return plane_rows<2>(cf, x0 - bx0, x1 - bx0, y0 - by0, y1 - by0, lane0, nlanes, lpr, value, put, kinks);
+            case 3: return plane_rows<3>(cf, x0 - bx0, x1 - bx0, y0 - by0, y1 - by0, lane0, nlanes, lpr, value, put, kinks);
+            default:  // the camera inside the tetrahedron
+                return plane_rows<4>(cf, x0 - bx0, x1 - bx0, y0 - by0, y1 - by0, lane0, nlanes, lpr, inner, put, kinks);
         }
     }
     double nrm[4][3], off[4];
@@ -2717,7 +2653,19 @@ TESS_HD inline uint32_t raster_record(const RecHead &h, const double *cf, const 
                                       int ty0, int n, int rows, Dep &&dep, Seam &&seam, uint32_t &spans,
                                       uint32_t &kinks) {
     if constexpr (FORM == kFormFace) {
-        return face_pair(h, cf, B, tx0, ty0, n, rows, dep, spans, kinks);
+        // as second differences, for a caller that sums the rows: the pixels
+        // of the tile and of the two columns left of it
+        const int left = min(2, tx0);
+        uint32_t frags = 0;
+        slab_pair(h, cf, B, tx0 - left, ty0, n + left, rows, 0, 1,
+                  [&](int row, int u, double v) {
+                      const int j = u - left;
+                      frags += j >= 0 ? 1u : 0u;
+                      for (int d = 0; d < 3; ++d)
+                          if (j + d >= 0 && j + d < n) dep(row, j + d, d == 1 ? -2.0 * v : v);
+                  },
+                  spans, kinks);
+        return frags;
     } else if constexpr (FORM == kFormSplat) {
         return splat_pair(h, cf, B, tx0, ty0, n, rows, dep, spans, kinks);
     } else if constexpr (FORM == kFormPersp) {
