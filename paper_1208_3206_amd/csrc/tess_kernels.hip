@@ -50,6 +50,28 @@ __device__ inline unsigned long long wave_sum(unsigned long long v) {
     return v;
 }
 
+// Adds a block's counts (times `per`) to the call's counters: one set of
+// atomics per block.  (All blocks add to the same few addresses, where the
+// atomics queue: a set per wavefront took longer than the setup of a 128^3
+// lattice.)  Every thread of the block calls it.
+__device__ inline void add_counts(const CubeCounts &cnt, unsigned long long per, DevCounters *__restrict__ counters) {
+    __shared__ unsigned int sum[5];
+    if (threadIdx.x < 5) sum[threadIdx.x] = 0u;
+    __syncthreads();
+    const unsigned int v[5] = {cnt.n_tets, cnt.n_zero, cnt.n_inv, cnt.n_dets, cnt.n_deg};
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        const unsigned int w = (unsigned int)wave_sum(v[k]);
+        if ((threadIdx.x & 63) == 0 && w) atomicAdd(&sum[k], w);
+    }
+    __syncthreads();
+    unsigned long long *const out[5] = {&counters->tets, &counters->zero_volume, &counters->inverted,
+                                        &counters->fp64_dets, &counters->degenerate};
+#pragma unroll
+    for (int k = 0; k < 5; ++k)
+        if (threadIdx.x == (unsigned)k && sum[k]) atomicAdd(out[k], (unsigned long long)sum[k] * per);
+}
+
 // One thread per lattice cube; writes the six records 6*cube .. 6*cube+5
 // (edge form: the edge slots of the tetrahedra that edge_tet_fast settles,
 // the others left to k_setup_rest).  Two wavefronts per SIMD at least: the
@@ -63,7 +85,6 @@ __global__ void __launch_bounds__(256, 2) k_setup(LatticeParams L, ViewParams V,
                                                DevCounters *__restrict__ counters) {
     CubeCounts cnt;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int lane = threadIdx.x & 63;
     if constexpr (EDGES) {
         // edge form, the common cases of every tetrahedron (its creases to
         // the edge slots, or a line-form record of its own, stored compactly
@@ -123,17 +144,7 @@ __global__ void __launch_bounds__(256, 2) k_setup(LatticeParams L, ViewParams V,
         }
     }
     // (a stack's setup serves all its slabs' images)
-    const unsigned long long per = FORM == kFormStack ? (unsigned long long)V.nstack : 1ull;
-    const unsigned long long n_tets = wave_sum(cnt.n_tets) * per, n_zero = wave_sum(cnt.n_zero) * per,
-                             n_inv = wave_sum(cnt.n_inv) * per, n_dets = wave_sum(cnt.n_dets) * per,
-                             n_deg = wave_sum(cnt.n_deg) * per;
-    if (lane == 0) {
-        if (n_tets) atomicAdd(&counters->tets, n_tets);
-        if (n_zero) atomicAdd(&counters->zero_volume, n_zero);
-        if (n_inv) atomicAdd(&counters->inverted, n_inv);
-        if (n_dets) atomicAdd(&counters->fp64_dets, n_dets);
-        if (n_deg) atomicAdd(&counters->degenerate, n_deg);
-    }
+    add_counts(cnt, FORM == kFormStack ? (unsigned long long)V.nstack : 1ull, counters);
 }
 
 // Edge form, after k_setup: the tetrahedra it left to the general code, one
@@ -172,16 +183,7 @@ __global__ void __launch_bounds__(256) k_setup_rest(LatticeParams L, ViewParams 
                 cnt, &todo);
         }
     }
-    const unsigned long long n_tets = wave_sum(cnt.n_tets), n_zero = wave_sum(cnt.n_zero),
-                             n_inv = wave_sum(cnt.n_inv), n_dets = wave_sum(cnt.n_dets),
-                             n_deg = wave_sum(cnt.n_deg);
-    if ((threadIdx.x & 63) == 0) {
-        if (n_tets) atomicAdd(&counters->tets, n_tets);
-        if (n_zero) atomicAdd(&counters->zero_volume, n_zero);
-        if (n_inv) atomicAdd(&counters->inverted, n_inv);
-        if (n_dets) atomicAdd(&counters->fp64_dets, n_dets);
-        if (n_deg) atomicAdd(&counters->degenerate, n_deg);
-    }
+    add_counts(cnt, 1ull, counters);
 }
 
 // Edge form: one thread per lattice vertex, its seven edge records after
@@ -212,14 +214,22 @@ __global__ void __launch_bounds__(256) k_qsum(LatticeParams L, ViewParams V, dou
     for (int64_t cube = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; cube < L.ncubes; cube += stride)
         sum += cube_qvol(L, V, cube);
     for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-    if ((threadIdx.x & 63) == 0 && sum != 0.0) atomicAdd(qsum, sum);
+    __shared__ double part[4];
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        sum = part[0] + part[1] + part[2] + part[3];
+        if (sum != 0.0) atomicAdd(qsum, sum);
+    }
 }
 
 // Blocks of 256 threads for a grid-stride loop over n items: at most
-// kCubeBlocks, so that a thread takes several cubes.  One cube per thread
-// ran a quarter of a million short wavefronts per frame at 256^3, whose
-// start-up and end-of-wavefront counter atomics (all on the same few
-// addresses) took longer than the setup's arithmetic.
+// kCubeBlocks, so that a thread takes several cubes of a large lattice (one
+// cube per thread ran a quarter of a million short wavefronts per frame at
+// 256^3, whose start-up took longer than the setup's arithmetic; 512, 2048
+// and 8192 blocks measure alike).  With the counters added per block, edge
+// form: 128^3 892 -> 375 us, 256^3 2.72 -> 2.64 ms; per tetrahedron: 96^3 587
+// -> 279 us.
 constexpr int kCubeBlocks = 8192;
 inline int cube_blocks(int64_t n, int cap = kCubeBlocks) {
     const int64_t want = (n + 255) / 256;
