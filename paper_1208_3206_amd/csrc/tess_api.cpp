@@ -406,20 +406,17 @@ void make_params(const tess_lattice_s *L, const tess_view *v, int form, LatticeP
     // q / rho needs |V| to full precision (the face form stores q itself, a
     // splat q |V| and |V|^(1/3))
     if (vp.qpow != 1 || vp.slab || vp.splat || vp.persp) lp.det_cond_k = -1.0;
-    // Plain pyramids take the edge form when a lattice cell spans enough
-    // pixels: its cost per lattice vertex (the edge records) then buys a
-    // larger saving in the raster, whose work grows with the rows each
-    // tetrahedron covers.  Measured on Zel'dovich lattices (128^3, 256^3):
-    // periodic images favour the edge form from 1.5 pixels per cell up (1.1x
-    // to 5x faster at 1.5 to 5 pixels, more beyond); windows without wrap
-    // favour the per-tetrahedron form at 2 to 4 pixels per cell (rotated
-    // views, 2x) and the edge form from 8 up.  tess_tune.form forces either
-    // (the two give the same image up to rounding).
+    // Plain pyramids: periodic images take the edge form (measured from 0.3 to
+    // 16 pixels per lattice cell, lattices of 32^3 to 256^3, D = 1 to 8: 1.15x
+    // faster at 32^3 -> 24^2, 2 to 3x at 64^3 and up); windows without wrap
+    // from 6 pixels per cell, as the tetrahedra of cubes unwrapped across the
+    // box keep their own records there (at 2 to 4 pixels the two forms are
+    // within a fifth of each other).  tess_tune.form forces either (the two
+    // give the same image up to rounding).
     const double cell_px = std::cbrt(d.box[0] * d.box[1] * d.box[2] / (double)lp.ncubes) *
                            std::sqrt(vp.inv_du * vp.inv_dv);
     const bool force_tet = form == TESS_FORM_PER_TETRAHEDRON, force_edges = form == TESS_FORM_EDGES;
-    const double min_cell_px = vp.wrap ? 1.5 : 6.0;
-    vp.edges = (view_form(vp) == kFormPyramid && !force_tet && (force_edges || cell_px >= min_cell_px)) ? 1 : 0;
+    vp.edges = (view_form(vp) == kFormPyramid && !force_tet && (force_edges || vp.wrap || cell_px >= 6.0)) ? 1 : 0;
     vp.kinks = nullptr;
     vp.sil = nullptr;
     vp.stack = nullptr;
@@ -457,10 +454,23 @@ Plan choose_plan(const tess_view *v, const tess_tune *tune) {
     return p;
 }
 
-int auto_chunk(unsigned long long total_pairs) {
-    // work items: a few per CU at least, each long enough to amortise its tile flush
-    const unsigned long long want = total_pairs / 4096ull;
-    return (int)std::min<unsigned long long>(65536ull, std::max<unsigned long long>(1024ull, want));
+// Entries of a work item, one block each, from the pairs and lists expected.
+// An item costs its block a start and an end (the tile cleared and added to
+// the image, the slowest wavefront waited for; 50 to 100 us with a CU's LDS
+// all taken), so it should hold 7,000 entries or more, while four items per
+// CU keep the chip even; the lists' remainders are counted in, as a fifth
+// round for a few of them would cost a fourth more.  Measured, raster: 96^3
+// rotated to 400^2 2.44 ms at 1,780 entries, 1.64 at 7,120, 1.98 at 28,480;
+// 97 x 120 x 75 to 1000 x 707 1.10 ms at 2,379, 0.71 at 4,758 and 9,516;
+// 128^3 to 1024^2 1.83 ms at 8,422, 2.19 at 16,844.  Pairs drawn pixel by
+// pixel (`values`) vary most and are handed out one by one: sixteen items
+// per CU (66 slabs of 64^2: 4.38 ms at 2,000 entries, 4.68 at 8,192).
+int auto_chunk(unsigned long long total_pairs, int64_t lists, bool values) {
+    if (values)
+        return (int)std::min<unsigned long long>(65536ull, std::max<unsigned long long>(1024ull, total_pairs / 4096ull));
+    const unsigned long long four = total_pairs / (unsigned long long)(1024 - std::min<int64_t>(lists, 512)) + 1;
+    const unsigned long long many = std::min<unsigned long long>(65536ull, total_pairs / 4096ull);
+    return (int)std::max<unsigned long long>(1024ull, std::max(std::min<unsigned long long>(four, 8192ull), many));
 }
 
 // Sizes of one image's pipeline.
@@ -469,6 +479,7 @@ struct Geometry {
     ViewParams vp;
     BinParams B;
     int64_t ntet, ntiles, nmat, npix;  // (a stack: lists and pixels of all its slabs)
+    double cell_px;  // pixels per lattice cell
     int64_t stored;  // tetrahedron payloads: all (6 ncubes), or (edge form) own_cap
     int64_t spill;   // edge form: 32-bit words of the spill bit set (one spare)
 };
@@ -481,6 +492,8 @@ tess_status make_geometry(const tess_lattice_s *L, const tess_view *v, const Pla
                           int64_t own_cap = -1, int nstack = 0) {
     make_params(L, v, plan.form, g.lp, g.vp);
     g.vp.nstack = nstack;
+    g.cell_px = std::cbrt(g.lp.box[0] * g.lp.box[1] * g.lp.box[2] / (double)g.lp.ncubes) *
+                std::sqrt(g.vp.inv_du * g.vp.inv_dv);
     // records: the tetrahedra (edge form: the few that keep their own record,
     // own_cap of them), then (edge form) seven edges per lattice vertex; the
     // edge form only while all ids fit in 32 bits
@@ -655,7 +668,7 @@ tess_status enqueue_back(const Geometry &g, const Plan &plan, int chunk, unsigne
                          const Bufs &b, PlanOut *slot, float *image, hipStream_t s, hipEvent_t after_bin,
                          hipEvent_t after_raster) {
     TESS_HIP(launch_plan(b.counts, b.base, g.B, chunk, cap, b.tile_items, slot, s));
-    TESS_HIP(launch_items(b.base, b.tile_items, g.B, chunk, slot, b.items, s));
+    TESS_HIP(launch_items(b.base, b.tile_items, g.B, slot, b.items, s));
     TESS_HIP(launch_scatter(b.head, g.ntet, g.B, b.counts, b.base, b.pairs, cap, s));
     TESS_HIP(launch_zero(b.acc, g.npix, s));
     if (after_bin) TESS_HIP(hipEventRecord(after_bin, s));
@@ -707,13 +720,14 @@ unsigned long long capacity_for(unsigned long long most) { return most + most / 
 
 // Edge form: payloads for the tetrahedra that keep their own record (steep
 // or wide footprints): from the most seen for this shape, else a first guess
-// of one in 64 (measured: 0.2 % on a 64^3 lattice at 8 pixels per cell);
-// those beyond are drawn by the overflow raster and raise the next call's.
+// of one in 64 at 6 pixels per lattice cell and more (measured: 0.2 % on a
+// 64^3 lattice at 8), one in 4 below (2 to 27 % at 0.3 to 4 pixels); those
+// beyond are drawn by the overflow raster and raise the next call's.
 int64_t own_capacity(const Workspace &ws, const Geometry &g0, const std::string &key, const Plan &plan) {
     const int64_t ntets = 6 * g0.lp.ncubes;
     if (plan.own) return std::min<int64_t>((int64_t)plan.own, ntets);
     auto it = ws.learned_own.find(key);
-    const int64_t want = it != ws.learned_own.end() ? (int64_t)capacity_for(it->second) : ntets / 64 + 65536;
+    const int64_t want = it != ws.learned_own.end() ? (int64_t)capacity_for(it->second) : ntets / (g0.cell_px < 6.0 ? 4 : 64) + 65536;
     return std::min<int64_t>(want, ntets);
 }
 
@@ -786,7 +800,7 @@ tess_status project_impl(const tess_lattice_s *L, const tess_view *v, const Plan
     auto it = ws.learned.find(key);
     const bool known = it != ws.learned.end();
     const unsigned long long cap = plan.cap ? plan.cap : (known ? capacity_for(it->second) : first_guess(g));
-    const int chunk = plan.chunk ? plan.chunk : auto_chunk(known ? it->second : cap / 2);
+    const int chunk = plan.chunk ? plan.chunk : auto_chunk(known ? it->second : cap / 2, g.ntiles, g.B.direct);
     st = check_limit(ws, plan, z, chunk, cap, 1);
     if (st != TESS_OK) return st;
     st = ensure_front(ws, z);
@@ -1076,7 +1090,9 @@ tess_status tune_batch(const tess_lattice *snaps, int n_snaps, const tess_view *
         for (int k = 0; k < n_img; ++k) most = std::max<unsigned long long>(most, ws.host_plan[k].total_pairs);
     }
     out.plan = plan;
-    out.chunk = plan.chunk ? plan.chunk : auto_chunk(most);
+    const int64_t lists = (int64_t)((views[0].width + plan.Tw - 1) / plan.Tw) * ((views[0].height + plan.Th - 1) / plan.Th);
+    out.chunk = plan.chunk ? plan.chunk : auto_chunk(most, lists, views[0].slab || views[0].method != TESS_METHOD_TESSELLATION ||
+                                                                   views[0].projection != TESS_PROJECTION_ORTHOGRAPHIC);
     out.cap = plan.cap ? plan.cap : most + most / 16 + 4096;
     return TESS_OK;
 }
@@ -1203,7 +1219,7 @@ tess_status project_stacks(const tess_lattice *snaps, int n_snaps, const tess_vi
         ws.learned[key] = most;
     }
     const unsigned long long cap = capacity_for(most);
-    const int chunk = plan.chunk ? plan.chunk : auto_chunk(most);
+    const int chunk = plan.chunk ? plan.chunk : auto_chunk(most, z.ntiles, true);
     st = ensure_back(ws, z.ntiles, chunk, cap);
     if (st != TESS_OK) {
         *taken = st != TESS_ENOMEM;
@@ -1431,6 +1447,17 @@ struct Carve {
         return p;
     }
 };
+
+// The scratch an image takes before its pair list (records, slots, counts,
+// accumulator), to within the alignment.
+size_t noalloc_fixed_bytes(const Geometry &g) {
+    const size_t slots = g.vp.edges ? (size_t)36 * g.lp.d[0] * g.lp.d[1] * g.lp.d[2] : 0;
+    return sizeof(RecHead) * (size_t)g.ntet + sizeof(Payload) * (size_t)g.stored +
+           sizeof(EdgePayload) * (size_t)(g.ntet - g.stored) + (sizeof(double) + 1) * slots +
+           sizeof(uint32_t) * (size_t)g.spill + (sizeof(uint32_t) + sizeof(uint64_t)) * (size_t)g.nmat +
+           sizeof(uint64_t) * scan_scratch_elems(g.nmat) + sizeof(double) * (size_t)g.npix +
+           20 * ((size_t)g.ntiles + 1) + 16384;
+}
 }  // namespace
 
 extern "C" tess_status tess_project_noalloc(tess_lattice L, const tess_view *v, const tess_tune *tune,
@@ -1441,10 +1468,15 @@ extern "C" tess_status tess_project_noalloc(tess_lattice L, const tess_view *v, 
     TESS_HIP(hipGetDevice(&dev));
     if (dev != L->device) return fail(TESS_EINVAL, "lattice lives on device %d, current device is %d", L->device, dev);
     hipStream_t s = (hipStream_t)stream;
-    const Plan plan = choose_plan(v, tune);
+    Plan plan = choose_plan(v, tune);
     Geometry g;
     st = make_geometry(L, v, plan, g);
     if (st != TESS_OK) return st;
+    if (g.vp.edges && plan.form == TESS_FORM_AUTO && noalloc_fixed_bytes(g) > kScratchBytes) {
+        plan.form = TESS_FORM_PER_TETRAHEDRON;  // the smaller of the two
+        st = make_geometry(L, v, plan, g);
+        if (st != TESS_OK) return st;
+    }
     void *sp = nullptr;
     TESS_HIP(scratch_buffer(&sp));
     // what tess_project's workspace holds for this image, then the pair list

@@ -255,8 +255,8 @@ hipError_t launch_plan(const uint32_t *counts, const uint64_t *base, const BinPa
                        int32_t chunk, unsigned long long cap, uint32_t *tile_items, PlanOut *out,
                        hipStream_t stream);
 
-hipError_t launch_items(const uint64_t *base, const uint32_t *tile_items, const BinParams &B,
-                        int32_t chunk, const PlanOut *plan, WorkItem *items, hipStream_t stream);
+hipError_t launch_items(const uint64_t *base, const uint32_t *tile_items, const BinParams &B, const PlanOut *plan,
+                        WorkItem *items, hipStream_t stream);
 
 // Writes beyond pair_cap entries are dropped (memory safety if the count and
 // scatter passes ever disagreed).  counts: the count pass's matrix (read only).

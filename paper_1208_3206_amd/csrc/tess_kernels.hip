@@ -87,36 +87,20 @@ __global__ void __launch_bounds__(256, 2) k_setup(LatticeParams L, ViewParams V,
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     if constexpr (EDGES) {
         // edge form, the common cases of every tetrahedron (its creases to
-        // the edge slots, or a line-form record of its own, stored compactly
-        // as it comes); the others, and line-form records that found no
-        // room, are marked in the spill bit set, which k_setup_rest reads
-        // next
+        // the edge slots); the others, and those that keep their own record
+        // (steep along x), are marked in the spill bit set, which
+        // k_setup_rest reads next
         for (int64_t cube = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; cube < L.ncubes; cube += stride) {
             uint32_t todo = 0u;
             setup_cube<FORM, EDGES, 1>(
                 L, V, cube, [](int, const RecHead &, const Payload &) {}, cnt, &todo,
-                [&](int t, const RecHead &R) -> Payload * {
-                    // a line-form record: its slot first, then its values
-                    // straight to memory (held in registers they would cost
-                    // the kernel its occupancy)
-                    const unsigned long long slot = atomicAdd(V.own, 1ull);
-                    if (slot < V.own_cap) {
-                        head[slot] = R;
-                        return &coef[slot];
-                    }
-                    // no room: the count taken back (it stays at or above the
-                    // capacity, so no slot below it is handed out twice); the
-                    // tetrahedron is marked for k_setup_rest, which counts it
-                    // and marks it again
-                    atomicAdd(V.own, ~0ull);
-                    return nullptr;
-                },
-                [](int) {});
-            while (todo) {
-                const int t = __builtin_ctz(todo);
-                todo &= todo - 1u;
-                const int64_t tet = 6 * cube + t;
-                atomicOr(&V.spill[tet >> 5], 1u << (tet & 31));
+                [](int, const RecHead &) -> Payload * { return nullptr; }, [](int) {});
+            if (todo) {
+                // (the six bits lie in one word or two)
+                const int64_t tet = 6 * cube;
+                const uint64_t bits = (uint64_t)todo << (tet & 31);
+                if ((uint32_t)bits) atomicOr(&V.spill[tet >> 5], (uint32_t)bits);
+                if (bits >> 32) atomicOr(&V.spill[(tet >> 5) + 1], (uint32_t)(bits >> 32));
             }
         }
     } else {
@@ -147,41 +131,61 @@ __global__ void __launch_bounds__(256, 2) k_setup(LatticeParams L, ViewParams V,
     add_counts(cnt, FORM == kFormStack ? (unsigned long long)V.nstack : 1ull, counters);
 }
 
-// Edge form, after k_setup: the tetrahedra it left to the general code, one
-// thread per 32-bit word of the spill bit set (the bits k_setup marked).  A
-// word is cleared, then each of its tetrahedra set up; those whose own
-// record finds no room mark their bit again, the set's meaning for the
-// raster (every tetrahedron in one word belongs to this thread).
-__global__ void __launch_bounds__(256) k_setup_rest(LatticeParams L, ViewParams V, RecHead *__restrict__ head,
-                                                    Payload *__restrict__ coef, DevCounters *__restrict__ counters) {
+// Edge form, after k_setup: the tetrahedra it left to the general code.  A
+// wavefront (a block) takes `words` words of the spill bit set at a time,
+// clears them and deals their tetrahedra out to its lanes; the own records of
+// a round take their slots with one atomic (all slots come from one counter,
+// 8 ns an atomic, and a small image keeps a tenth to a quarter of its
+// tetrahedra as own records).  Those whose record finds no room mark their
+// bit again, the set's meaning for the raster (every tetrahedron of a word
+// belongs to this block).  Few words a wavefront, so that a lattice with few
+// marks, each a pass of the general code's latency, has one pass per
+// wavefront and all of them at once.
+constexpr int kRestWords = 128;  // at most
+
+__global__ void __launch_bounds__(64) k_setup_rest(LatticeParams L, ViewParams V, int words, RecHead *__restrict__ head,
+                                                   Payload *__restrict__ coef, DevCounters *__restrict__ counters) {
+    __shared__ uint16_t list[32 * kRestWords];
+    __shared__ uint32_t total;
     CubeCounts cnt;
     const int64_t nwords = (6 * L.ncubes + 31) / 32;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w < nwords; w += stride) {
-        uint32_t bits = V.spill[w];
-        if (bits == 0u) continue;
-        V.spill[w] = 0u;
-        while (bits) {
-            const int b = __builtin_ctz(bits);
-            bits &= bits - 1u;
-            const int64_t tet = 32 * w + b;
+    for (int64_t w0 = (int64_t)blockIdx.x * words; w0 < nwords; w0 += (int64_t)gridDim.x * words) {
+        if (threadIdx.x == 0) total = 0u;
+        __syncthreads();
+        for (int i = threadIdx.x; i < words && w0 + i < nwords; i += 64) {
+            const uint32_t bits = V.spill[w0 + i];
+            if (!bits) continue;
+            V.spill[w0 + i] = 0u;
+            uint32_t at = atomicAdd(&total, (uint32_t)__builtin_popcount(bits));
+            for (uint32_t b = bits; b; b &= b - 1u) list[at++] = (uint16_t)(32 * i + __builtin_ctz(b));
+        }
+        __syncthreads();
+        for (uint32_t k = threadIdx.x; k < total; k += 64) {
+            const int64_t tet = 32 * w0 + list[k];
             const int64_t cube = tet / 6;
             uint32_t todo = 1u << (int)(tet - 6 * cube);
-            setup_cube<kFormPyramid, true, 2>(
+            setup_cube<kFormPyramid, true, 3>(
                 L, V, cube,
-                [&](int t, const RecHead &R, const Payload &P) {
+                [&](int, const RecHead &R, const Payload &P) {
                     if (!(R.flags & REC_VALID)) return;
-                    const unsigned long long slot = atomicAdd(V.own, 1ull);
+                    const uint64_t act = __builtin_amdgcn_read_exec();
+                    const uint32_t rank =
+                        __builtin_amdgcn_mbcnt_hi((uint32_t)(act >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)act, 0u));
+                    unsigned long long slot = 0ull;
+                    if (rank == 0u) slot = atomicAdd(V.own, (unsigned long long)__builtin_popcountll(act));
+                    slot = (((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(slot >> 32)) << 32) |
+                            (uint32_t)__builtin_amdgcn_readfirstlane((int)slot)) +
+                           rank;
                     if (slot < V.own_cap) {
                         head[slot] = R;
                         coef[slot] = P;
                     } else {
-                        const int64_t id = 6 * cube + t;
-                        atomicOr(&V.spill[id >> 5], 1u << (id & 31));
+                        atomicOr(&V.spill[tet >> 5], 1u << (tet & 31));
                     }
                 },
                 cnt, &todo);
         }
+        __syncthreads();
     }
     add_counts(cnt, 1ull, counters);
 }
@@ -264,8 +268,11 @@ hipError_t launch_setup(const LatticeParams &L, const ViewParams &V, RecHead *he
             if (V.edges) {
                 hipLaunchKernelGGL((k_setup<kFormPyramid, true>), dim3(blocks), dim3(256), 0, stream, L, V, head,
                                    coef, counters);
-                hipLaunchKernelGGL(k_setup_rest, dim3(cube_blocks((6 * L.ncubes + 31) / 32, 1024)), dim3(256), 0,
-                                   stream, L, V, head, coef, counters);
+                const int64_t nwords = (6 * L.ncubes + 31) / 32;
+                const int words = (int)std::min<int64_t>(kRestWords, std::max<int64_t>(4, (nwords + 1023) / 1024));
+                const int64_t want = (nwords + words - 1) / words;
+                hipLaunchKernelGGL(k_setup_rest, dim3((unsigned)std::min<int64_t>(want, 8192)), dim3(64), 0, stream, L,
+                                   V, words, head, coef, counters);
             } else
                 hipLaunchKernelGGL((k_setup<kFormPyramid, false>), dim3(blocks), dim3(256), 0, stream, L, V, head,
                                    coef, counters);
@@ -593,30 +600,30 @@ hipError_t launch_plan(const uint32_t *counts, const uint64_t *base, const BinPa
     return hipGetLastError();
 }
 
+// A wavefront per list: its items, of even length.
 __global__ void k_items(const uint64_t *__restrict__ base, const uint32_t *__restrict__ tile_items,
-                        BinParams B, int32_t chunk, const PlanOut *__restrict__ plan,
-                        WorkItem *__restrict__ items) {
-    const int ntiles = B.nbins;
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= ntiles) return;
-    const uint64_t b = tile_begin(base, B, t);
-    const uint64_t e = t + 1 < ntiles ? tile_begin(base, B, t + 1) : plan->total_pairs;
-    const uint32_t first = tile_items[t], n = tile_items[t + 1] - first;
-    for (uint32_t c = 0; c < n; ++c) {
-        WorkItem w;
-        w.first = b + (uint64_t)c * chunk;
-        const uint64_t left = e - w.first;
-        w.count = (uint32_t)(left < (uint64_t)chunk ? left : (uint64_t)chunk);
-        w.tile = (uint32_t)t;
-        items[first + c] = w;
+                        BinParams B, const PlanOut *__restrict__ plan, WorkItem *__restrict__ items) {
+    for (int t = blockIdx.x; t < B.nbins; t += gridDim.x) {
+        const uint32_t first = tile_items[t], n = tile_items[t + 1] - first;
+        if (n == 0) continue;
+        const uint64_t b = tile_begin(base, B, t);
+        const uint64_t e = t + 1 < B.nbins ? tile_begin(base, B, t + 1) : plan->total_pairs;
+        const uint64_t per = (e - b + n - 1) / n;
+        for (uint32_t c = threadIdx.x; c < n; c += 64) {
+            WorkItem w;
+            w.first = b + (uint64_t)c * per;
+            const uint64_t left = e > w.first ? e - w.first : 0;
+            w.count = (uint32_t)(left < per ? left : per);
+            w.tile = (uint32_t)t;
+            items[first + c] = w;
+        }
     }
 }
 
-hipError_t launch_items(const uint64_t *base, const uint32_t *tile_items, const BinParams &B,
-                        int32_t chunk, const PlanOut *plan, WorkItem *items, hipStream_t stream) {
-    const int ntiles = B.nbins;
-    hipLaunchKernelGGL(k_items, dim3((ntiles + 255) / 256), dim3(256), 0, stream, base, tile_items,
-                       B, chunk, plan, items);
+hipError_t launch_items(const uint64_t *base, const uint32_t *tile_items, const BinParams &B, const PlanOut *plan,
+                        WorkItem *items, hipStream_t stream) {
+    hipLaunchKernelGGL(k_items, dim3((unsigned)std::min(B.nbins, 8192)), dim3(64), 0, stream, base, tile_items, B, plan,
+                       items);
     return hipGetLastError();
 }
 
@@ -1038,11 +1045,43 @@ __global__ void __launch_bounds__(TPB) k_raster(const RecHead *__restrict__ head
                 wave_sync();
                 seam_entries(0u, qn);
             }
-            const uint32_t g0 = g * C, g1 = min(it.count, g0 + C);
-            // then the tetrahedra that kept their own records
-            for (uint32_t e2 = g0 + q; e2 < g1; e2 += 16) {
-                const uint32_t id2 = pairs[it.first + e2];
-                if (id2 < B.first_edge) one(id2);
+            // then the tetrahedra that kept their own records.  Their ids come
+            // before the edges', so a list holds them at its front (it is in
+            // segment order), close together: a window of the list at a time,
+            // their places are collected in LDS and dealt out to the block,
+            // when they are few four or two lanes to a pair, which share its
+            // rows.  (Left to the stripes' own groups, a few lanes drew a
+            // hundred pairs one after another while the block waited: 0.4 of
+            // 1.8 ms at 128^3 -> 1024^2.)
+            uint32_t *own = reinterpret_cast<uint32_t *>(sA + tsize + nseam);  // the seam queues' LDS
+            constexpr uint32_t kWindow = (TPB / 64) * kSeamQueue;
+            const uint32_t last = B.first_edge ? (B.first_edge - 1u) / (uint32_t)B.seg_len : 0u;
+            for (uint32_t w0 = 0; w0 < it.count && B.first_edge; w0 += kWindow) {
+                // (segment order: nothing of the own records' segments follows)
+                if (pairs[it.first + w0] / (uint32_t)B.seg_len > last) break;
+                __syncthreads();
+                if (threadIdx.x == 0) s_next = 0u;
+                __syncthreads();
+                const uint32_t w1 = min(it.count, w0 + kWindow);
+                for (uint32_t e2 = w0 + threadIdx.x; e2 < w1; e2 += TPB) {
+                    const uint32_t id2 = pairs[it.first + e2];
+                    if (id2 < B.first_edge) own[atomicAdd(&s_next, 1u)] = id2;
+                }
+                __syncthreads();
+                const uint32_t nown = s_next;
+                const int lg = 4u * nown <= (uint32_t)TPB ? 2 : 2u * nown <= (uint32_t)TPB ? 1 : 0;
+                const int sub = (int)threadIdx.x & ((1 << lg) - 1);
+                for (uint32_t k = threadIdx.x >> lg; k < nown; k += (uint32_t)TPB >> lg) {
+                    const uint32_t id2 = own[k];
+                    const RecHead h = coef[id2].h;
+                    if (!(h.flags & REC_VALID)) continue;
+                    auto dep1 = [&](int row, int j, double v) { atomicAdd(&sA[cell(row, j)], v); };
+                    if (!(h.flags & REC_CREASE))
+                        frags += (int32_t)raster_pair(h, coef[id2].c, B, tx0, ty0, n, rows, dep1, spans, kinks, sub,
+                                                      1 << lg);
+                    else if (sub == 0)
+                        frags += (int32_t)crease_pair(h, coef[id2].c, B, tx0, ty0, n, rows, dep1, spans, kinks);
+                }
             }
         } else
         for (uint32_t e = e0; e < e1; e += kIdBurst) {

@@ -896,8 +896,8 @@ TESS_HD inline int edge_tet_fast(const LatticeParams &L, const ViewParams &V, in
 // Setup of the six tetrahedra of lattice cube `cube` (EDGES: the edge form's
 // code, used when V.edges is set; PASS 1 of it takes only the common cases,
 // edge_tet_fast, and returns the tetrahedra left over in *todo_io, bit t for
-// tetrahedron t, which PASS 2 then sets up by the general code; PASS 0 does
-// both): gather and unwrap the
+// tetrahedron t, which PASS 2 then sets up by the general code, PASS 3 the
+// same for a single one; PASS 0 does both): gather and unwrap the
 // corners, volume determinant with its FP64 fallback, footprint.  Each
 // tetrahedron t's record goes to emit(t, head, payload) (flags 0 when it can
 // cover no pixel centre; REC_EDGED when its creases went to its edges' slots,
@@ -1005,7 +1005,7 @@ TESS_HD inline void setup_cube(const LatticeParams &L, const ViewParams &V, int6
     };
     // the tetrahedra the general code below takes
     uint32_t todo = 0x3fu;
-    if constexpr (FORM == kFormPyramid && EDGES && PASS == 2) {
+    if constexpr (FORM == kFormPyramid && EDGES && PASS >= 2) {
         todo = *todo_io;
     } else if constexpr (FORM == kFormPyramid && EDGES) {
         // edge form (this instantiation runs only with V.edges set): the
@@ -1049,9 +1049,11 @@ TESS_HD inline void setup_cube(const LatticeParams &L, const ViewParams &V, int6
     // The general code, one copy of the body for the six tetrahedra (unrolled,
     // the setup kernels' code outgrew the instruction cache).
     auto general = [&](const double (&e)[8][3], const double (&PX)[8], const double (&PY)[8]) {
+    // (PASS 3: one tetrahedron, a different one per lane perhaps: no loop, in
+    // which the lanes of each number would take a turn of their own)
 #pragma unroll 1
-    for (int t = 0; t < 6; ++t) {
-        if (!((todo >> t) & 1u)) continue;
+    for (int t = PASS == 3 ? __builtin_ctz(todo) : 0; t < 6; ++t) {
+        if (PASS != 3 && !((todo >> t) & 1u)) continue;
         double kd[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // edge form: slope change per local edge
         double ev[4][3], pxv[4], pyv[4];                 // the tetrahedron's corners
         tet_corners(t, e, PX, PY, ev, pxv, pyv);
@@ -1346,6 +1348,7 @@ TESS_HD inline void setup_cube(const LatticeParams &L, const ViewParams &V, int6
             const bool edged = (R.flags & REC_EDGED) != 0u;
             edge_slots(t, kd, edged ? R.spare & 0xfffu : 0u, edged ? R.spare >> 12 : 0x555u);
         }
+        if (PASS == 3) break;
     }
     };
     general(e, PX, PY);
@@ -1848,11 +1851,12 @@ TESS_HD inline uint32_t row_span(const SpanGeom &G, const double *cf, int shift,
 // All spans of one record in one tile (every periodic offset that meets it):
 // tile pixels [tx0, tx0 + n) x [ty0, ty0 + rows).  dep(row, j, v) adds v to
 // the tile's A[row][j].  Returns the covered sample count; spans counts the
-// rows visited, kinks the break points placed.
+// rows visited, kinks the break points placed.  Of several callers that share
+// a pair's rows, this one takes every nsub-th from the sub-th.
 template <typename Dep>
 TESS_HD inline uint32_t raster_pair(const RecHead &h, const double *cf, const BinParams &B, int tx0,
                                     int ty0, int n, int rows, Dep &&dep, uint32_t &spans,
-                                    uint32_t &kinks) {
+                                    uint32_t &kinks, int sub = 0, int nsub = 1) {
     SpanGeom G;
     span_geom(h.flags, cf, G);
     const int bx0 = range_lo(h.bx), bx1 = range_hi(h.bx) + kRightReach;
@@ -1868,7 +1872,7 @@ TESS_HD inline uint32_t raster_pair(const RecHead &h, const double *cf, const Bi
             const int shift = tx0 + kx * B.W - bx0;  // record column of the tile's column 0
             // the image row in the record frame
             const double ulo = (double)(kx * B.W - bx0) - 0.5, uhi = (double)(B.W + kx * B.W - bx0) - 0.5;
-            for (int y = ylo; y <= yhi; ++y) {
+            for (int y = ylo + sub; y <= yhi; y += nsub) {
                 const double Y = (double)(y + ky * B.H - by0) + 0.5;
                 const int row = y - ty0;
                 frags += row_span(G, cf, shift, Y, n, ulo, uhi, [&](int j, double v) { dep(row, j, v); }, kinks);

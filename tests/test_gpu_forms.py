@@ -1,0 +1,75 @@
+"""The form and the work items chosen for an image, against the general
+per-tetrahedron form, over sizes where either could go wrong."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tess():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1208_3206_amd as t
+    return t
+
+
+def lattice(tess, n, growth, **kw):
+    import torch
+    if growth == 0.0:
+        xyz = W.undisplaced(n)
+    else:
+        xyz = W.zeldovich(n, min(4, (n - 1) // 2), growth, seed=17)
+    return tess.build(*[torch.from_numpy(a).cuda() for a in xyz], (n, n, n), **kw)
+
+
+def same(a, b):
+    # FP64 sums of the same terms in another order (4e-11 of the maximum
+    # between the forms), rounded once to FP32
+    a, b = a.double(), b.double()
+    return bool(((a - b).abs() <= 1.2e-7 * b.abs() + 1e-10 * b.max()).all())
+
+
+# periodic images from a pixel for many cells to many pixels a cell: one
+# pixel, a row, tetrahedra wider than the image, most of them steep (own
+# records), undisplaced walls; one tile and several
+@pytest.mark.parametrize("n,size,growth,quantity", [
+    (8, (1, 1), 3.0, "density"), (9, (17, 1), 2.0, "density"), (24, (7, 5), 8.0, "density"),
+    (33, (16, 16), 0.5, "density"), (40, (61, 33), 0.2, "unit"), (64, (100, 75), 6.0, "density2"),
+    (12, (40, 24), 0.0, "density"), (48, (600, 70), 1.0, "density"), (100, (150, 150), 0.3, "density")])
+def test_periodic_image_equals_the_per_tetrahedron_form(tess, n, size, growth, quantity):
+    lat = lattice(tess, n, growth)
+    view = dict(W.z_view(*size), quantity=quantity)
+    for _ in range(2):  # first guesses of the capacities, then learned ones
+        auto, st = tess.project(lat, view, stats=True)
+        ref, sr = tess.project(lat, view, tune=tess.make_tune(form="per_tetrahedron"), stats=True)
+        assert same(auto, ref)
+        assert same(tess.project(lat, view), ref)
+        for k in ("tets", "zero_volume", "inverted", "fp64_dets"):
+            assert st[k] == sr[k], k
+        assert abs(st["fragments"] - sr["fragments"]) <= 1e-6 * sr["fragments"] + 8
+
+
+# entries per work item: fewer than a lane each, one wavefront's, not a
+# multiple of anything, more than every list
+@pytest.mark.parametrize("form", ["edges", "per_tetrahedron"])
+@pytest.mark.parametrize("chunk", [64, 1000, 7177, 10 ** 6])
+def test_work_item_sizes(tess, form, chunk):
+    lat = lattice(tess, 40, 3.0)
+    view = W.z_view(333, 150)
+    ref = tess.project(lat, view, tune=tess.make_tune(form=form))
+    img, st = tess.project(lat, view, tune=tess.make_tune(form=form, chunk=chunk), stats=True)
+    assert same(img, ref) and st["overflow"] == 0
+
+
+def test_noalloc_keeps_its_largest_lattice(tess):
+    # 50^3 does not fit the allocation-free scratch in the edge form
+    import torch
+    lat = lattice(tess, 50, 1.0)
+    view = W.z_view(64)
+    out = torch.empty((64, 64), device="cuda")
+    tess.project_noalloc(lat, view, out)
+    assert same(out, tess.project(lat, view, tune=tess.make_tune(form="per_tetrahedron")))
