@@ -379,10 +379,15 @@ void make_params(const tess_lattice_s *L, const tess_view *v, int form, LatticeP
     vp.mass_px = 6.0 * lp.tet_mass * vp.inv_du * vp.inv_dv;
     // steepest x slope a crease-form footprint may have: a kink's rounding
     // (2^-53 of its slope change) grows by up to the image width along the
-    // row sums; 64 / width of the mean pixel value (all the mass in view)
-    // keeps that near 1e-14 of the mean
+    // row sums; 256 / width of the mean pixel value (all the mass in view)
+    // keeps a kink's at 3e-14 of the mean.  Measured in FP64 against the
+    // exact image (32^3, D = 1 and 4, widths 128 and 512), rms of the mean:
+    // rotated windows 6 to 9e-13 at 64 / width and at 256 / width, periodic
+    // images 2 to 8e-13 and 2 to 18e-13, 1e4 times below the FP32 output's
+    // rounding; the steep tetrahedra, which then keep their own record, fall
+    // from 6-9 to 2-3 % of a periodic image's and from 35 to 10 % of a window's
     vp.crease_bmax = vp.mass_px * (double)lp.ncubes / ((double)v->width * (double)v->height) *
-                     (64.0 / (double)v->width);
+                     (256.0 / (double)v->width);
     vp.W = v->width;
     vp.H = v->height;
     vp.wrap = v->wrap;
@@ -390,12 +395,12 @@ void make_params(const tess_lattice_s *L, const tess_view *v, int form, LatticeP
     // The crease threshold in the image's own scale. q = 1: the integral of q
     // over the tetrahedra, which setup reads from the device (k_qsum fills it;
     // with many streams it far exceeds the volume). q = rho^2: the density
-    // image's threshold times the mean density; the integral of rho^2 is
-    // dominated by the image's peaks, where the row sums are already at their
-    // noisiest, and would loosen the threshold there.
+    // image's threshold (at 64 / width) times the mean density; the integral of
+    // rho^2 is dominated by the image's peaks, where the row sums are already
+    // at their noisiest, and would loosen the threshold there.
     vp.qsum = nullptr;
     vp.bmax_per_q = vp.inv_du * vp.inv_dv / ((double)v->width * (double)v->height) * (64.0 / (double)v->width);
-    if (vp.qpow == 2) vp.crease_bmax *= lp.tet_mass / lp.v0;
+    if (vp.qpow == 2) vp.crease_bmax *= 0.25 * lp.tet_mass / lp.v0;
     vp.slab = v->slab;
     vp.slab_t[0] = v->slab ? v->slab_t[0] : 0.0;
     vp.slab_t[1] = v->slab ? v->slab_t[1] : 0.0;
@@ -406,17 +411,20 @@ void make_params(const tess_lattice_s *L, const tess_view *v, int form, LatticeP
     // q / rho needs |V| to full precision (the face form stores q itself, a
     // splat q |V| and |V|^(1/3))
     if (vp.qpow != 1 || vp.slab || vp.splat || vp.persp) lp.det_cond_k = -1.0;
-    // Plain pyramids: periodic images take the edge form (measured from 0.3 to
-    // 16 pixels per lattice cell, lattices of 32^3 to 256^3, D = 1 to 8: 1.15x
-    // faster at 32^3 -> 24^2, 2 to 3x at 64^3 and up); windows without wrap
-    // from 6 pixels per cell, as the tetrahedra of cubes unwrapped across the
-    // box keep their own records there (at 2 to 4 pixels the two forms are
-    // within a fifth of each other).  tess_tune.form forces either (the two
-    // give the same image up to rounding).
+    // Plain pyramids of periodic lattices take the edge form (measured on
+    // lattices of 16^3 to 256^3, D = 1 to 8: periodic images of 0.3 to 21
+    // pixels per lattice cell 1.15x faster at 32^3 -> 24^2, 2 to 3x at 64^3
+    // and up; rotated windows of 1 to 16 pixels per cell 1.0 to 1.3x, 64^3
+    // 0.93x, though the tetrahedra of cubes unwrapped across the box, a fifth
+    // of them, keep their own records there).  Lattices without periods from
+    // 6 pixels per cell: one cut from a periodic box has cubes stretched over
+    // it, whose tetrahedra all keep their own (128^3 at 2 pixels 5.2 ms per
+    // tetrahedron, 5.3 by edges).  tess_tune.form forces either (the two give
+    // the same image up to rounding).
     const double cell_px = std::cbrt(d.box[0] * d.box[1] * d.box[2] / (double)lp.ncubes) *
                            std::sqrt(vp.inv_du * vp.inv_dv);
     const bool force_tet = form == TESS_FORM_PER_TETRAHEDRON, force_edges = form == TESS_FORM_EDGES;
-    vp.edges = (view_form(vp) == kFormPyramid && !force_tet && (force_edges || vp.wrap || cell_px >= 6.0)) ? 1 : 0;
+    vp.edges = (view_form(vp) == kFormPyramid && !force_tet && (force_edges || d.periodic || cell_px >= 6.0)) ? 1 : 0;
     vp.kinks = nullptr;
     vp.sil = nullptr;
     vp.stack = nullptr;
@@ -436,9 +444,13 @@ struct Plan {
 // 128 KiB accumulator allows (at most 64). Taller tiles mean fewer (record,
 // tile) pairs, narrower ones fewer columns per pair; at 2048^2, 32 x 512
 // measured fastest among 8 x 1024, 16 x 1024, 32 x 512, 32 x 256 and 64 x 256.
+// Periodic images up to 512 wide take 64 x 128, half the LDS, so that two
+// blocks share a CU and one works while the other starts or ends: 64^3 ->
+// 256^2 0.42 -> 0.35 ms, 128^3 -> 512^2 2.20 -> 1.96 (windows of rotated views
+// gain nothing there: 128^3 -> 512^2 3.15 ms at 32 x 512, 3.26 at 64 x 128).
 Plan choose_plan(const tess_view *v, const tess_tune *tune) {
     Plan p;
-    int Tw = (tune && tune->tile_cols) ? tune->tile_cols : std::min(v->width, 512);
+    int Tw = (tune && tune->tile_cols) ? tune->tile_cols : std::min(v->width, v->wrap && v->width <= 512 ? 128 : 512);
     int Th = 1;
     while (Th < 64 && 2 * Th * Tw <= kMaxTileCells) Th *= 2;
     if (tune && tune->tile_rows) Th = tune->tile_rows;

@@ -1020,6 +1020,9 @@ TESS_HD inline void setup_cube(const LatticeParams &L, const ViewParams &V, int6
                 edge_tet_fast(L, V, t, e, PX, PY, crease_bmax, same_frame, qpack, kd, ksil, kshf, own_sink, cnt);
             if (fast < 0) {
                 todo |= 1u << t;
+                // (PASS 3 then writes only the slots of those whose creases
+                // go to their edges: here a wavefront's writes are whole lines)
+                if constexpr (PASS == 1) edge_slots(t, kd, 0u, 0x555u);
                 continue;
             }
             if (fast == 8) {  // its own record is written
@@ -1346,7 +1349,7 @@ TESS_HD inline void setup_cube(const LatticeParams &L, const ViewParams &V, int6
         emit(t, R, P);
         if constexpr (FORM == kFormPyramid && EDGES) {
             const bool edged = (R.flags & REC_EDGED) != 0u;
-            edge_slots(t, kd, edged ? R.spare & 0xfffu : 0u, edged ? R.spare >> 12 : 0x555u);
+            if (PASS != 3 || edged) edge_slots(t, kd, edged ? R.spare & 0xfffu : 0u, edged ? R.spare >> 12 : 0x555u);
         }
         if (PASS == 3) break;
     }
