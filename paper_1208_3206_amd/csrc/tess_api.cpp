@@ -444,15 +444,18 @@ struct Plan {
 // 128 KiB accumulator allows (at most 64). Taller tiles mean fewer (record,
 // tile) pairs, narrower ones fewer columns per pair; at 2048^2, 32 x 512
 // measured fastest among 8 x 1024, 16 x 1024, 32 x 512, 32 x 256 and 64 x 256.
-// Periodic images up to 512 wide take 64 x 128, half the LDS, so that two
-// blocks share a CU and one works while the other starts or ends: 64^3 ->
-// 256^2 0.42 -> 0.35 ms, 128^3 -> 512^2 2.20 -> 1.96 (windows of rotated views
-// gain nothing there: 128^3 -> 512^2 3.15 ms at 32 x 512, 3.26 at 64 x 128).
+// Periodic images up to 512 wide take 32 x 128, a quarter of the LDS, so that
+// two blocks share a CU and one works while the other starts or ends: raster
+// of 64^3 -> 512^2 0.23 -> 0.14 ms, 200^3 -> 256^2 2.9 (64 x 256) -> 2.0, 32^3
+// -> 256^2 91 -> 64 us (windows of rotated views gain nothing there: 128^3 ->
+// 512^2 1.30 ms at 32 x 512, 1.50 at 32 x 128).
 Plan choose_plan(const tess_view *v, const tess_tune *tune) {
     Plan p;
-    int Tw = (tune && tune->tile_cols) ? tune->tile_cols : std::min(v->width, v->wrap && v->width <= 512 ? 128 : 512);
+    const bool small = v->wrap && v->width <= 512 && !v->slab && v->method == TESS_METHOD_TESSELLATION;
+    int Tw = (tune && tune->tile_cols) ? tune->tile_cols : std::min(v->width, small ? 128 : 512);
     int Th = 1;
-    while (Th < 64 && 2 * Th * Tw <= kMaxTileCells) Th *= 2;
+    const int most_rows = small && !(tune && tune->tile_cols) ? 32 : 64;
+    while (Th < most_rows && 2 * Th * Tw <= kMaxTileCells) Th *= 2;
     if (tune && tune->tile_rows) Th = tune->tile_rows;
     p.Th = Th;
     p.Tw = Tw;
@@ -466,23 +469,28 @@ Plan choose_plan(const tess_view *v, const tess_tune *tune) {
     return p;
 }
 
-// Entries of a work item, one block each, from the pairs and lists expected.
-// An item costs its block a start and an end (the tile cleared and added to
-// the image, the slowest wavefront waited for; 50 to 100 us with a CU's LDS
-// all taken), so it should hold 7,000 entries or more, while four items per
-// CU keep the chip even; the lists' remainders are counted in, as a fifth
-// round for a few of them would cost a fourth more.  Measured, raster: 96^3
-// rotated to 400^2 2.44 ms at 1,780 entries, 1.64 at 7,120, 1.98 at 28,480;
-// 97 x 120 x 75 to 1000 x 707 1.10 ms at 2,379, 0.71 at 4,758 and 9,516;
-// 128^3 to 1024^2 1.83 ms at 8,422, 2.19 at 16,844.  Pairs drawn pixel by
-// pixel (`values`) vary most and are handed out one by one: sixteen items
-// per CU (66 slabs of 64^2: 4.38 ms at 2,000 entries, 4.68 at 8,192).
-int auto_chunk(unsigned long long total_pairs, int64_t lists, bool values) {
-    if (values)
-        return (int)std::min<unsigned long long>(65536ull, std::max<unsigned long long>(1024ull, total_pairs / 4096ull));
-    const unsigned long long four = total_pairs / (unsigned long long)(1024 - std::min<int64_t>(lists, 512)) + 1;
-    const unsigned long long many = std::min<unsigned long long>(65536ull, total_pairs / 4096ull);
-    return (int)std::max<unsigned long long>(1024ull, std::max(std::min<unsigned long long>(four, 8192ull), many));
+// Entries of a work item, one block each, from the pairs expected.  An item
+// costs its block a start and an end (the tile cleared and added to the
+// image, the slowest wavefront waited for), so it should be long, and the
+// items should be many and short enough to fill the chip evenly.  Measured
+// (raster ms at so many entries):
+//  - periodic images, whose pairs are nearly all edges and cost alike: 128^3
+//    -> 1024^2 1.61 at 4,096, 1.16 at 8,192, 1.09 at 32,768; 200^3 -> 256^2
+//    2.40 at 8,192, 1.96 at 32,768; 97x120x75 -> 1000x707 0.52 at 4,096, 0.38
+//    at 8,192 and 16,384; 64^3 -> 512^2 0.19 at 4,096, 0.17 at 16,384;
+//  - windows, with own records, ten times an edge's cost, at the front of the
+//    lists: 128^3 -> 512^2 1.37 at 2,048, 1.25 at 4,096, 1.54 at 16,384; 96^3
+//    -> 400^2 0.64 at 4,096, 0.94 at 16,384; 32^3 -> 512^2 0.12 at 512;
+//  - pairs drawn pixel by pixel, which vary most and are handed out to the
+//    wavefronts one by one: 128^3 in perspective 48.5 at 2,048, 51 at 7,400;
+//    64^3 1.44 at 256 to 512, 1.85 at 2,048.
+int auto_chunk(unsigned long long total_pairs, const BinParams &B) {
+    auto within = [](unsigned long long x, unsigned long long lo, unsigned long long hi) {
+        return (int)std::min(hi, std::max(lo, x));
+    };
+    if (B.direct) return within(total_pairs / 16384ull, 256ull, 65536ull);
+    if (B.wrap) return within(std::max(std::min(total_pairs / 128ull, 8192ull), total_pairs / 1024ull), 1024ull, 65536ull);
+    return within(std::max(std::min(total_pairs / 512ull, 4096ull), total_pairs / 4096ull), 512ull, 65536ull);
 }
 
 // Sizes of one image's pipeline.
@@ -812,7 +820,7 @@ tess_status project_impl(const tess_lattice_s *L, const tess_view *v, const Plan
     auto it = ws.learned.find(key);
     const bool known = it != ws.learned.end();
     const unsigned long long cap = plan.cap ? plan.cap : (known ? capacity_for(it->second) : first_guess(g));
-    const int chunk = plan.chunk ? plan.chunk : auto_chunk(known ? it->second : cap / 2, g.ntiles, g.B.direct);
+    const int chunk = plan.chunk ? plan.chunk : auto_chunk(known ? it->second : cap / 2, g.B);
     st = check_limit(ws, plan, z, chunk, cap, 1);
     if (st != TESS_OK) return st;
     st = ensure_front(ws, z);
@@ -1102,15 +1110,16 @@ tess_status tune_batch(const tess_lattice *snaps, int n_snaps, const tess_view *
         for (int k = 0; k < n_img; ++k) most = std::max<unsigned long long>(most, ws.host_plan[k].total_pairs);
     }
     out.plan = plan;
-    const int64_t lists = (int64_t)((views[0].width + plan.Tw - 1) / plan.Tw) * ((views[0].height + plan.Th - 1) / plan.Th);
-    out.chunk = plan.chunk ? plan.chunk : auto_chunk(most, lists, views[0].slab || views[0].method != TESS_METHOD_TESSELLATION ||
-                                                                   views[0].projection != TESS_PROJECTION_ORTHOGRAPHIC);
+    Geometry g0;
+    tess_status st = make_geometry(snaps[0], &views[0], plan, g0);
+    if (st != TESS_OK) return st;
+    out.chunk = plan.chunk ? plan.chunk : auto_chunk(most, g0.B);
     out.cap = plan.cap ? plan.cap : most + most / 16 + 4096;
     return TESS_OK;
 }
 
 std::string graph_key(const tess_lattice *snaps, int n_snaps, const tess_view *views, int n_views, float *images,
-                      const Tuned &t, int64_t own_cap, const Workspace &ws) {
+                      const Tuned &t, int64_t own_cap, bool count, const Workspace &ws) {
     std::string k;
     auto put = [&](const void *p, size_t n) { k.append((const char *)p, n); };
     for (int i = 0; i < n_snaps; ++i) {
@@ -1123,6 +1132,7 @@ std::string graph_key(const tess_lattice *snaps, int n_snaps, const tess_view *v
     put(&images, sizeof(images));
     put(&t, sizeof(t));
     put(&own_cap, sizeof(own_cap));
+    put(&count, sizeof(count));
     const void *bufs[] = {ws.head.p, ws.coef.p, ws.ecoef.p, ws.kinks.p, ws.sil.p, ws.spill.p, ws.counts.p, ws.base.p,
                           ws.scan.p, ws.tile_items.p, ws.items.p, ws.pairs.p, ws.acc.p, ws.plan.p, ws.counters.p,
                           ws.overflow.p};
@@ -1186,12 +1196,14 @@ tess_status project_stacks(const tess_lattice *snaps, int n_snaps, const tess_vi
         return st;
     };
     Sizes z;
+    BinParams bins{};
     for (int i = 0; i < n_snaps; ++i)
         for (int g = 0; g < groups; ++g) {
             Geometry G;
             tess_status st = geometry(i, g, G);
             if (st != TESS_OK) return st;
             z.add(G);
+            bins = G.B;
         }
     take_feedback(ws, s);
     auto it = ws.learned.find(key);
@@ -1231,7 +1243,7 @@ tess_status project_stacks(const tess_lattice *snaps, int n_snaps, const tess_vi
         ws.learned[key] = most;
     }
     const unsigned long long cap = capacity_for(most);
-    const int chunk = plan.chunk ? plan.chunk : auto_chunk(most, z.ntiles, true);
+    const int chunk = plan.chunk ? plan.chunk : auto_chunk(most, bins);
     st = ensure_back(ws, z.ntiles, chunk, cap);
     if (st != TESS_OK) {
         *taken = st != TESS_ENOMEM;
@@ -1354,7 +1366,7 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
         TESS_HIP(hipHostMalloc((void **)&ws.host_plan, sizeof(PlanOut) * (size_t)n_img, hipHostMallocDefault));
         ws.host_plan_cap = (size_t)n_img;
     }
-    const std::string gkey = graph_key(snaps, n_snaps, views, n_views, images, t, own_cap, ws);
+    const std::string gkey = graph_key(snaps, n_snaps, views, n_views, images, t, own_cap, stats != nullptr, ws);
     if (!ws.graph || ws.graph_key != gkey) {
         if (ws.graph) {
             TESS_HIP(hipGraphExecDestroy(ws.graph));
@@ -1372,8 +1384,7 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
                     if (r != TESS_OK) return r;
                     r = enqueue_front(g, bufs_of(ws), ws.plan.p + k, t.cap, nullptr, c);
                     if (r != TESS_OK) return r;
-                    // the graph serves calls with and without stats: it counts
-                    r = enqueue_back(g, t.plan, t.chunk, t.cap, true, bufs_of(ws), ws.plan.p + k, images + (size_t)k * img,
+                    r = enqueue_back(g, t.plan, t.chunk, t.cap, stats != nullptr, bufs_of(ws), ws.plan.p + k, images + (size_t)k * img,
                                      c, nullptr, nullptr);
                     if (r != TESS_OK) return r;
                 }

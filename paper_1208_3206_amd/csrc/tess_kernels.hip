@@ -649,7 +649,7 @@ constexpr int kPad = 2;
 constexpr int kIdBurst = 8;     // pair ids a lane loads at once
 constexpr int kSortPer = 7;     // pair ids per lane in one wavefront's class sort
 constexpr int kNumClasses = 32;
-constexpr size_t kLdsBytes = 160 * 1024 - 64;  // dynamic LDS: 64 bytes stay for the static counter
+constexpr size_t kLdsBytes = 160 * 1024 - 64;  // dynamic LDS: 64 bytes stay for the static counters
 // edge form: a wavefront's queue of pairs whose seam lines are still to draw
 // (at most 63 waiting plus 64 added in one round)
 constexpr int kSeamQueue = 128;
@@ -788,8 +788,10 @@ __global__ void __launch_bounds__(TPB) k_raster(const RecHead *__restrict__ head
     double *sDiff = sSeam + 2 * B.Th * nsc;
     const int dstride = (B.Th + 1) * nsc;  // one difference array (all copies)
     for (int i = threadIdx.x; i < tsize + nseam; i += TPB) sA[i] = 0.0;
-    __shared__ uint32_t s_next;  // edge form: chunks handed out so far
+    __shared__ uint32_t s_next;  // chunks or pairs handed out so far
+    __shared__ unsigned long long s_sum[3];
     if (threadIdx.x == 0) s_next = 0u;
+    if (threadIdx.x < 3) s_sum[threadIdx.x] = 0ull;
     __syncthreads();
     long long frags = 0;  // edge records add signed terms
     uint32_t spans = 0, kinks = 0;
@@ -837,7 +839,7 @@ __global__ void __launch_bounds__(TPB) k_raster(const RecHead *__restrict__ head
     // the tile instead of stacking their atomics on the same LDS cells
     const uint32_t per = (it.count + TPB - 1) / TPB;
     const uint32_t e0 = threadIdx.x * per, e1 = min(it.count, e0 + per);
-    if constexpr (FORM == kFormPersp || FORM == kFormFace || FORM == kFormStack) {
+    if constexpr (FORM == kFormPersp || FORM == kFormSplat || FORM == kFormFace || FORM == kFormStack) {
         // per pixel, and a footprint may fill the tile: a wavefront takes one
         // pair at a time, its 64 lanes side by side over rows and columns,
         // the next pair from a counter in LDS (footprints next to the camera
@@ -856,7 +858,9 @@ __global__ void __launch_bounds__(TPB) k_raster(const RecHead *__restrict__ head
             if (!(h.flags & REC_VALID)) continue;
             auto dep = [&](int row, int j, double v) { atomicAdd(&sA[cell(row, j)], v); };
             const int lane = (int)(threadIdx.x & 63u);
-            if constexpr (FORM != kFormPersp)
+            if constexpr (FORM == kFormSplat)
+                frags += splat_pair(h, coef[id].c, B, tx0, ty0, n, rows, lane, 64, dep, spans, kinks);
+            else if constexpr (FORM != kFormPersp)
                 frags += slab_pair(h, coef[id].c, B, tx0, ty0, n, rows, lane, 64, dep, spans, kinks);
             else if (B.rays)
                 frags += persp_pair<false>(h, coef[id].c, B, tx0, ty0, n, rows, lane, 64, dep, spans, kinks);
@@ -1141,13 +1145,22 @@ __global__ void __launch_bounds__(TPB) k_raster(const RecHead *__restrict__ head
             if (B.W > 1 && b - a != 0.0) unsafeAtomicAdd(&acc[(int64_t)(ty0 + r) * B.W + 1], b - a);
         }
     }
+    // the call's counters: one atomic each per block (all blocks' queue at the
+    // same addresses, 8 ns apiece; one each per wavefront was a third of the
+    // raster's time at 4,000 items)
     const unsigned long long f = wave_sum((unsigned long long)frags);
     const unsigned long long sp = wave_sum((unsigned long long)spans);
     const unsigned long long kk = wave_sum((unsigned long long)kinks);
     if ((threadIdx.x & 63) == 0) {
-        if (f) atomicAdd(&counters->fragments, f);
-        if (sp) atomicAdd(&counters->spans, sp);
-        if (kk) atomicAdd(&counters->kinks, kk);
+        if (f) atomicAdd(&s_sum[0], f);
+        if (sp) atomicAdd(&s_sum[1], sp);
+        if (kk) atomicAdd(&s_sum[2], kk);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (s_sum[0]) atomicAdd(&counters->fragments, s_sum[0]);
+        if (s_sum[1]) atomicAdd(&counters->spans, s_sum[1]);
+        if (s_sum[2]) atomicAdd(&counters->kinks, s_sum[2]);
     }
 }
 
