@@ -62,7 +62,8 @@ hipError_t launch_adam(float *w, float *m, float *v, const float *g, int64_t cou
 hipError_t launch_cast_weights(const float *master, __bf16 *Wb, __bf16 *WTb, hipStream_t s);
 // Inference: pred[n][3] from q[n][3] in one pass (features, hidden layers
 // and output layer per 16-sample tile in registers; bf16 operands rounded
-// from the FP32 master parameters, FP32 accumulation).
+// from the FP32 master parameters, FP32 accumulation).  `master` is read 16
+// bytes at a time: the start of an allocation.
 hipError_t launch_mlp_infer(const float *q, int64_t n, const float *B, const float *master, float *pred,
                             hipStream_t s);
 

@@ -499,7 +499,15 @@ hipError_t launch_adam(float *w, float *m, float *v, const float *g, int64_t cou
 // staged in LDS in that order, one 16-byte A fragment per lane per (layer,
 // ot, ks); the first layer takes the features in their natural order, which
 // the lanes compute for themselves.
-constexpr int kInferWaves = 8;            // 512 threads; the staged weights admit one block per CU
+//
+// What bounds it is the activations' vector instructions (128 GELUs a lane
+// and tile; the MFMAs are a seventh of that, the fragments' LDS reads a
+// third).  They come in dependent chains behind branches, so it takes the
+// four wavefronts per SIMD that 128 registers admit to fill them: 2^20
+// points 485 us with two per SIMD and a bias read per value, 417 us with
+// four biases per read, 343 us with four wavefronts.  (Two tiles per
+// wavefront, which halves the LDS reads, at two wavefronts: 394 us.)
+constexpr int kInferWaves = 16;           // 1024 threads; the staged weights admit one block per CU
 constexpr int kFragsHidden = kDepth * 8 * 4 * 64;  // 16-byte fragments of the four hidden layers
 constexpr int kFragsOut = 4 * 64;         // of the output layer (3 of its 16 rows are real)
 
@@ -513,25 +521,31 @@ __global__ void __launch_bounds__(64 * kInferWaves) k_mlp_infer(const float *__r
                                                                 const float *__restrict__ master,
                                                                 float *__restrict__ pred) {
     extern __shared__ bf16x8 sFrag[];                 // hidden, then output fragments
-    __shared__ float sBias[kDepth * kWidth + 4];
+    __shared__ __align__(16) float sBias[kDepth * kWidth + 4];
     __shared__ float sB[3 * kFreq];
-    // stage: fragment f of (layer, ot, ks, lane) holds W[o][perm or natural k .. +7]
+    // stage: fragment f of (layer, ot, ks, lane) holds W[o][perm or natural k .. +7]:
+    // two runs of four columns (16-byte loads: rows and layers start at
+    // multiples of four parameters of an allocation)
+#pragma unroll 3
     for (int f = threadIdx.x; f < kFragsHidden + kFragsOut; f += blockDim.x) {
         const int lane = f & 63, ks = (f >> 6) & 3;
         const bool out = f >= kFragsHidden;
         const int ot = out ? 0 : (f >> 8) & 7, l = out ? kDepth : f >> 11;
         const int o = 16 * ot + (lane & 15);
+        const int lq = lane >> 4;
+        const int k0 = l == 0 ? 32 * ks + 8 * lq : infer_perm(32 * ks + 8 * lq);
+        const int k1 = l == 0 ? k0 + 4 : infer_perm(32 * ks + 8 * lq + 4);
+        const float *row = master + param_offset_W(l) + (int64_t)o * kWidth;  // (the output layer's follow the hidden ones')
+        floatx4 w0 = {0.f, 0.f, 0.f, 0.f}, w1 = w0;
+        if (!out || o < 3) {
+            w0 = *(const floatx4 *)&row[k0];
+            w1 = *(const floatx4 *)&row[k1];
+        }
         bf16x8 v;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int k = 32 * ks + 8 * (lane >> 4) + j;
-            const int kin = l == 0 ? k : infer_perm(k);
-            float w = 0.f;
-            if (!out)
-                w = master[param_offset_W(l) + (int64_t)o * kWidth + kin];
-            else if (o < 3)
-                w = master[kOffW5 + (int64_t)o * kWidth + kin];
-            v[j] = (bf16)w;
+        for (int j = 0; j < 4; ++j) {
+            v[j] = (bf16)w0[j];
+            v[4 + j] = (bf16)w1[j];
         }
         sFrag[f] = v;
     }
@@ -542,7 +556,8 @@ __global__ void __launch_bounds__(64 * kInferWaves) k_mlp_infer(const float *__r
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lq = lane >> 4, lr = lane & 15;
     const int64_t ntile = (n + 15) / 16;
-    for (int64_t tile = (int64_t)blockIdx.x * kInferWaves + wave; tile < ntile;
+    // (neighbouring tiles on neighbouring CUs: a small call has a tile on each)
+    for (int64_t tile = (int64_t)wave * gridDim.x + blockIdx.x; tile < ntile;
          tile += (int64_t)gridDim.x * kInferWaves) {
         const int64_t row = tile * 16 + lr;
         const bool live = row < n;
@@ -552,6 +567,9 @@ __global__ void __launch_bounds__(64 * kInferWaves) k_mlp_infer(const float *__r
         // k + 64 sit in blocks ks and ks + 2 of the same lane)
         bf16x8 h[4];
         {
+            int own = 0;  // (opaque: the frequencies are read again for each tile, not kept in 48 registers)
+            asm volatile("" : "+v"(own));
+            const float *fB = sB + own;
             const float q0 = live ? q[3 * row] : 0.f, q1 = live ? q[3 * row + 1] : 0.f,
                         q2 = live ? q[3 * row + 2] : 0.f;
 #pragma unroll
@@ -559,7 +577,7 @@ __global__ void __launch_bounds__(64 * kInferWaves) k_mlp_infer(const float *__r
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     const int f = 32 * ks + 8 * lq + j;
-                    const float t = 2.0f * (sB[3 * f] * q0 + sB[3 * f + 1] * q1 + sB[3 * f + 2] * q2);
+                    const float t = 2.0f * (fB[3 * f] * q0 + fB[3 * f + 1] * q1 + fB[3 * f + 2] * q2);
                     float sv, cv;
                     sincospif(t, &sv, &cv);
                     h[ks][j] = (bf16)sv;
@@ -579,13 +597,15 @@ __global__ void __launch_bounds__(64 * kInferWaves) k_mlp_infer(const float *__r
             // bias, GELU, bf16: the next layer's operand (outputs 16 ot + 4 q + i
             // of this lane's sample, in the next layer's column order)
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
+            for (int ks = 0; ks < 4; ++ks) {
+                floatx4 bias[2];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int ot = 2 * ks + (j >> 2), i = j & 3;
-                    const float z = acc[ot][i] + sBias[l * kWidth + 16 * ot + 4 * lq + i];
-                    h[ks][j] = (bf16)gelu(z);
-                }
+                for (int e = 0; e < 2; ++e)
+                    bias[e] = *(const floatx4 *)&sBias[l * kWidth + 16 * (2 * ks + e) + 4 * lq];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    h[ks][j] = (bf16)gelu(acc[2 * ks + (j >> 2)][j & 3] + bias[j >> 2][j & 3]);
+            }
         }
         floatx4 out = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -605,8 +625,7 @@ hipError_t launch_mlp_infer(const float *q, int64_t n, const float *B, const flo
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     const int64_t tiles = (n + 15) / 16;
-    const int64_t want = (tiles + kInferWaves - 1) / kInferWaves;
-    const int blocks = (int)std::min<int64_t>(want, (int64_t)cus);
+    const int blocks = (int)std::min<int64_t>(tiles, (int64_t)cus);
     const size_t lds = sizeof(bf16x8) * (size_t)(kFragsHidden + kFragsOut);
     hipLaunchKernelGGL(k_mlp_infer, dim3((unsigned)blocks), dim3(64 * kInferWaves), lds, s, q, n, B, master, pred);
     return hipGetLastError();

@@ -28,3 +28,16 @@ def test_gradients_at_split_edges(tess, n):  # noqa: F811
         rel = np.linalg.norm(a - b) / np.linalg.norm(b)
         print(f"n={n} {k}: rel L2 {rel:.3e}", flush=True)
         assert rel <= 1e-2, k
+
+
+# The inference deals its 16-sample tiles to the CUs first (256 blocks: 4096
+# samples) and to a block's 16 wavefronts next (65536): a sample's output is
+# its own, so a call cut into pieces gives the same bits.
+@pytest.mark.parametrize("n", [4095, 4097, 65536, 65553])
+def test_inference_does_not_depend_on_the_cut(tess, n):  # noqa: F811
+    import torch
+    q, _, B, params = problem(n, 11 * n)
+    qd = torch.from_numpy(q).cuda()
+    whole = tess.mlp_forward(params, B, qd)
+    parts = [tess.mlp_forward(params, B, qd[a:a + 1013].contiguous()) for a in range(0, n, 1013)]
+    assert torch.equal(whole, torch.cat(parts))
