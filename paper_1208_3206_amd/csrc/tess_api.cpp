@@ -645,25 +645,32 @@ tess_status ensure_back(Workspace &ws, int64_t ntiles, int chunk, unsigned long 
 }
 
 // Setup of one image; for q = 1 first the integral of q into slot->qsum.
-tess_status enqueue_setup(const Geometry &g, const Bufs &b, PlanOut *slot, hipStream_t s) {
+// `draws`: the raster follows, into b.acc; `counters` (or null) start at zero.
+tess_status enqueue_setup(const Geometry &g, const Bufs &b, PlanOut *slot, bool draws, DevCounters *counters,
+                          hipStream_t s) {
     ViewParams vp = g.vp;
-    if (vp.qpow == 0 && !vp.slab && !vp.splat && !vp.persp) {
-        TESS_HIP(launch_zero(&slot->qsum, 1, s));
-        TESS_HIP(launch_qsum(g.lp, vp, &slot->qsum, s));
-        vp.qsum = &slot->qsum;
-    }
-    vp.kinks = b.kinks;
-    vp.sil = b.sil;
-    TESS_HIP(launch_zero((double *)&slot->own, 1, s));  // (+0.0: all bits zero)
+    const bool qsum = vp.qpow == 0 && !vp.slab && !vp.splat && !vp.persp;
+    ZeroList zero;  // (+0.0: all bits zero)
+    if (counters) zero.add(counters, sizeof(DevCounters) / sizeof(double));
+    if (draws) zero.add(b.acc, g.npix);
+    if (qsum) zero.add(&slot->qsum, 1);
+    zero.add(&slot->own, 1);
     if (vp.edges) {
         // the numbered records start invalid (setup fills as many as it
         // finds), the spill set empty
         vp.own = &slot->own;
         vp.spill = b.spill;
         static_assert(sizeof(RecHead) == 2 * sizeof(double), "head as two doubles");
-        TESS_HIP(launch_zero((double *)b.head, 2 * g.stored, s));
-        TESS_HIP(launch_zero((double *)b.spill, g.spill / 2, s));
+        zero.add(b.head, 2 * g.stored);
+        zero.add(b.spill, g.spill / 2);
     }
+    TESS_HIP(launch_zero(zero, s));
+    if (qsum) {
+        TESS_HIP(launch_qsum(g.lp, vp, &slot->qsum, s));
+        vp.qsum = &slot->qsum;
+    }
+    vp.kinks = b.kinks;
+    vp.sil = b.sil;
     TESS_HIP(launch_setup(g.lp, vp, b.head, b.coef, b.counters, s));
     if (vp.edges) TESS_HIP(launch_edges(g.lp, vp, b.head, b.ecoef, s));
     return TESS_OK;
@@ -672,8 +679,8 @@ tess_status enqueue_setup(const Geometry &g, const Bufs &b, PlanOut *slot, hipSt
 // Setup, count, scan and totals of one image (no host synchronisation);
 // the totals flag *overflow when the pairs exceed cap.
 tess_status enqueue_front(const Geometry &g, const Bufs &b, PlanOut *slot, unsigned long long cap,
-                          unsigned int *overflow, hipStream_t s) {
-    tess_status st = enqueue_setup(g, b, slot, s);
+                          bool draws, unsigned int *overflow, hipStream_t s) {
+    tess_status st = enqueue_setup(g, b, slot, draws, nullptr, s);
     if (st != TESS_OK) return st;
     TESS_HIP(launch_count(b.head, g.ntet, g.B, b.counts, s));
     TESS_HIP(launch_scan(b.counts, b.base, g.nmat, b.scan, s));
@@ -690,7 +697,6 @@ tess_status enqueue_back(const Geometry &g, const Plan &plan, int chunk, unsigne
     TESS_HIP(launch_plan(b.counts, b.base, g.B, chunk, cap, b.tile_items, slot, s));
     TESS_HIP(launch_items(b.base, b.tile_items, g.B, slot, b.items, s));
     TESS_HIP(launch_scatter(b.head, g.ntet, g.B, b.counts, b.base, b.pairs, cap, s));
-    TESS_HIP(launch_zero(b.acc, g.npix, s));
     if (after_bin) TESS_HIP(hipEventRecord(after_bin, s));
     BinParams B = g.B;
     B.groups = b.kinks;  // the edge records' sums by period offset (written over the slots)
@@ -829,9 +835,8 @@ tess_status project_impl(const tess_lattice_s *L, const tess_view *v, const Plan
     st = ensure_back(ws, g.ntiles, chunk, cap);
     if (st != TESS_OK) return st;
     if (stats) TESS_HIP(hipEventRecord(ws.ev[0], s));
-    TESS_HIP(launch_zero((double *)ws.counters.p, sizeof(DevCounters) / sizeof(double), s));
     const Bufs b = bufs_of(ws);
-    st = enqueue_setup(g, b, ws.plan.p, s);
+    st = enqueue_setup(g, b, ws.plan.p, true, ws.counters.p, s);
     if (st != TESS_OK) return st;
     if (stats) TESS_HIP(hipEventRecord(ws.ev[1], s));
     TESS_HIP(launch_count(ws.head.p, g.ntet, g.B, ws.counts.p, s));
@@ -1043,7 +1048,7 @@ tess_status count_all(const tess_lattice *snaps, int n_snaps, const tess_view *v
             Geometry g;
             st = make_geometry(snaps[i], &views[v], plan, g);
             if (st != TESS_OK) return st;
-            st = enqueue_front(g, bufs_of(ws), ws.plan.p + i * n_views + v, ~0ull, nullptr, s);
+            st = enqueue_front(g, bufs_of(ws), ws.plan.p + i * n_views + v, ~0ull, false, nullptr, s);
             if (st != TESS_OK) return st;
         }
     TESS_HIP(hipMemcpyAsync(ws.host_plan, ws.plan.p, sizeof(PlanOut) * (size_t)n_img, hipMemcpyDeviceToHost, s));
@@ -1234,7 +1239,7 @@ tess_status project_stacks(const tess_lattice *snaps, int n_snaps, const tess_vi
         for (int k = 0; k < n_st; ++k) {
             Geometry G;
             st = geometry(k / groups, k % groups, G);
-            if (st == TESS_OK) st = enqueue_front(G, front, ws.plan.p + k, ~0ull, nullptr, s);
+            if (st == TESS_OK) st = enqueue_front(G, front, ws.plan.p + k, ~0ull, false, nullptr, s);
             if (st != TESS_OK) return st;
         }
         TESS_HIP(hipMemcpyAsync(ws.host_plan, ws.plan.p, sizeof(PlanOut) * (size_t)n_st, hipMemcpyDeviceToHost, s));
@@ -1250,12 +1255,14 @@ tess_status project_stacks(const tess_lattice *snaps, int n_snaps, const tess_vi
         return st;
     }
     if (stats) TESS_HIP(hipEventRecord(ws.ev[0], s));
-    TESS_HIP(launch_zero((double *)ws.counters.p, sizeof(DevCounters) / sizeof(double), s));
+    ZeroList zero;
+    zero.add(ws.counters.p, sizeof(DevCounters) / sizeof(double));
+    TESS_HIP(launch_zero(zero, s));
     const Bufs b = bufs_of(ws);
     for (int k = 0; k < n_st; ++k) {
         Geometry G;
         st = geometry(k / groups, k % groups, G);
-        if (st == TESS_OK) st = enqueue_front(G, b, ws.plan.p + k, cap, nullptr, s);
+        if (st == TESS_OK) st = enqueue_front(G, b, ws.plan.p + k, cap, true, nullptr, s);
         if (st == TESS_OK)
             st = enqueue_back(G, plan, chunk, cap, true, b, ws.plan.p + k,
                               images + ((size_t)(k / groups) * n_views + (size_t)(k % groups) * per) * img, s, nullptr,
@@ -1375,14 +1382,16 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
         hipStream_t c = ws.capture;
         TESS_HIP(hipStreamBeginCapture(c, hipStreamCaptureModeThreadLocal));
         auto record = [&]() -> tess_status {
-            TESS_HIP(launch_zero((double *)ws.counters.p, sizeof(DevCounters) / sizeof(double), c));
+            ZeroList zero;
+            zero.add(ws.counters.p, sizeof(DevCounters) / sizeof(double));
+            TESS_HIP(launch_zero(zero, c));
             for (int i = 0; i < n_snaps; ++i)
                 for (int v = 0; v < n_views; ++v) {
                     const int k = i * n_views + v;
                     Geometry g;
                     tess_status r = make_geometry(snaps[i], &views[v], t.plan, g, own_cap);
                     if (r != TESS_OK) return r;
-                    r = enqueue_front(g, bufs_of(ws), ws.plan.p + k, t.cap, nullptr, c);
+                    r = enqueue_front(g, bufs_of(ws), ws.plan.p + k, t.cap, true, nullptr, c);
                     if (r != TESS_OK) return r;
                     r = enqueue_back(g, t.plan, t.chunk, t.cap, stats != nullptr, bufs_of(ws), ws.plan.p + k, images + (size_t)k * img,
                                      c, nullptr, nullptr);
@@ -1534,8 +1543,7 @@ extern "C" tess_status tess_project_noalloc(tess_lattice L, const tess_view *v, 
     b.items = c.take<WorkItem>((size_t)max_items_for(g.ntiles, chunk, cap));
     b.pairs = c.take<uint32_t>((size_t)cap);
     if (c.off > kScratchBytes) return fail(TESS_ECAPACITY, "scratch layout overflow");  // not reached
-    TESS_HIP(launch_zero((double *)b.counters, sizeof(DevCounters) / sizeof(double), s));
-    st = enqueue_setup(g, b, slot, s);
+    st = enqueue_setup(g, b, slot, true, b.counters, s);
     if (st != TESS_OK) return st;
     TESS_HIP(launch_count(b.head, g.ntet, g.B, b.counts, s));
     TESS_HIP(launch_scan(b.counts, b.base, g.nmat, b.scan, s));

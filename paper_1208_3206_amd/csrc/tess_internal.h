@@ -263,8 +263,18 @@ hipError_t launch_items(const uint64_t *base, const uint32_t *tile_items, const 
 hipError_t launch_scatter(const RecHead *head, int64_t ntet, const BinParams &B, const uint32_t *counts,
                           const uint64_t *base, uint32_t *pairs, unsigned long long pair_cap, hipStream_t stream);
 
-// Clears n doubles (a kernel, so that the call can sit in a captured graph).
-hipError_t launch_zero(double *p, int64_t n, hipStream_t stream);
+// Up to six ranges of doubles, cleared together (by a kernel, so that the
+// call can sit in a captured graph).
+struct ZeroList {
+    double *p[6];
+    int64_t count[6];
+    int n = 0;
+    void add(void *q, int64_t doubles) {
+        p[n] = (double *)q;
+        count[n++] = doubles;
+    }
+};
+hipError_t launch_zero(const ZeroList &Z, hipStream_t stream);
 
 // Raster of the work items into the second-difference image acc[H][W];
 // max_items blocks are launched and those beyond plan->n_items return.

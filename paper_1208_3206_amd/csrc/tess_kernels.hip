@@ -627,15 +627,21 @@ hipError_t launch_items(const uint64_t *base, const uint32_t *tile_items, const 
     return hipGetLastError();
 }
 
-__global__ void k_zero(double *__restrict__ p, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0.0;
+// All ranges of an image in one launch: an image of 32^3 tracers spends its
+// time on launches, and five of them were these (195 -> 190 us an image).
+__global__ void k_zero(ZeroList Z) {
+    for (int r = 0; r < Z.n; ++r)
+        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < Z.count[r];
+             i += (int64_t)gridDim.x * blockDim.x)
+            Z.p[r][i] = 0.0;
 }
 
-hipError_t launch_zero(double *p, int64_t n, hipStream_t stream) {
-    const int64_t want = (n + 255) / 256;
-    const int blocks = (int)(want < 8192 ? (want > 0 ? want : 1) : 8192);
-    hipLaunchKernelGGL(k_zero, dim3(blocks), dim3(256), 0, stream, p, n);
+hipError_t launch_zero(const ZeroList &Z, hipStream_t stream) {
+    int64_t most = 1;
+    for (int r = 0; r < Z.n; ++r) most = Z.count[r] > most ? Z.count[r] : most;
+    const int64_t want = (most + 255) / 256;
+    const int blocks = (int)(want < 8192 ? want : 8192);
+    hipLaunchKernelGGL(k_zero, dim3(blocks), dim3(256), 0, stream, Z);
     return hipGetLastError();
 }
 

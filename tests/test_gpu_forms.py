@@ -73,3 +73,22 @@ def test_noalloc_keeps_its_largest_lattice(tess):
     out = torch.empty((64, 64), device="cuda")
     tess.project_noalloc(lat, view, out)
     assert same(out, tess.project(lat, view, tune=tess.make_tune(form="per_tetrahedron")))
+
+
+# An image's scratch is cleared in one launch, ranges of very different
+# lengths together: an image drawn after a larger one, periodic and a window
+# of it, is the per-tetrahedron form's, with its counts
+@pytest.mark.parametrize("quantity", ["density", "unit"])
+@pytest.mark.parametrize("n,size", [(2, (1, 1)), (5, (33, 17)), (16, (64, 200))])
+def test_nothing_is_left_of_the_image_before(tess, n, size, quantity):
+    big, lat = lattice(tess, 32, 4.0), lattice(tess, n, 0.0 if n == 2 else 1.0)
+    view = dict(W.z_view(*size), quantity=quantity)
+    large = dict(W.z_view(256, 256), quantity=quantity)
+    for tune in (tess.make_tune(form="edges"), tess.make_tune(form="per_tetrahedron")):
+        tess.project(big, large, tune=tune)
+        img, st = tess.project(lat, view, tune=tune, stats=True)
+        tess.project(big, large)
+        ref, sr = tess.project(lat, view, tune=tune, stats=True)
+        assert same(img, ref)
+        assert (st["tets"], st["zero_volume"]) == (sr["tets"], sr["zero_volume"])
+        assert st["tets"] + st["zero_volume"] <= 6 * n ** 3 and st["fragments"] > 0
