@@ -110,3 +110,16 @@ def test_prefix_sum_sizes(tess, n, size, tiles):
     # (a pixel that a footprint's edge touches may fall either way at another tile's seam)
     assert abs(st["fragments"] - sr["fragments"]) <= 1e-6 * sr["fragments"] + 8
     assert st["overflow"] == 0
+
+
+# Most tetrahedra of a strongly displaced window keep their own records (more
+# than the first guess): a batch of a new shape has counted them before it
+# draws.
+def test_first_batch_of_a_window_has_room_for_its_own_records(tess):
+    import torch
+    lat = tess.build(*[torch.from_numpy(a).cuda() for a in W.zeldovich(64, 16, 8.0)], (64, 64, 64))
+    views = [W.rotated_view(r, 203) for r in W.random_rotations(2, 1)]
+    img, st = tess.project_batch([lat], views, stats=True)
+    assert st["overflow"] == 0
+    for i, v in enumerate(views):
+        assert same(img[0, i], tess.project(lat, v, tune=tess.make_tune(form="per_tetrahedron")))
