@@ -47,8 +47,8 @@ TRAFFIC = {
     "sources": ["paper_1208_3206_amd/csrc/tess_kernels.hip", "paper_1208_3206_amd/csrc/tess_tet.h",
                 "paper_1208_3206_amd/csrc/tess_internal.h"],
     "workload": "stress_256^3_to_2048^2", "tile": [32, 512], "block": 1024,
-    "sha256": "946348e51242f5fc4224eedefa6189e91ca0dea5dc6aea1e21062f10b9e75107",
-    "fetch_kib": 46861873.6, "write_kib": 1427621.1, "fetch_scale": 2.0, "write_scale": 1.0,
+    "sha256": "85d33369ca77ebdb3cf2195ab2841842b475b2e138d8d1ddb5d6978fa5eb008a",
+    "fetch_kib": 45821456.6, "write_kib": 1422494.9, "fetch_scale": 2.0, "write_scale": 1.0,
 }
 
 
