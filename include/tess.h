@@ -256,7 +256,8 @@ typedef struct {
  * FP32 at the end: repeated calls agree to FP64 rounding, not bit for bit.
  * Plain pyramids are drawn in the form tune->form selects (automatic: the
  * edge form for periodic lattices, and for others when a lattice cell spans
- * at least 6 pixels); the edge form is not used
+ * at least 6 pixels; an image of few pixels per cell whose edge form finds no
+ * room is drawn per tetrahedron); the edge form is not used
  * when its 13 records per lattice point would not fit 32-bit ids.
  * With stats == NULL the call only enqueues work on `stream`: it never waits
  * for the device, so it may be captured into a HIP graph once a first call

@@ -809,6 +809,14 @@ tess_status give_feedback(Workspace &ws, const PlanOut *plan, int n, const std::
     return TESS_OK;
 }
 
+// Images of few pixels per lattice cell, where the edge form gains least: they
+// are drawn per tetrahedron when its buffers find no memory or exceed the
+// caller's limit (the two forms' sizes lie within a third of each other,
+// either way).
+bool may_fall_back(const Geometry &g, const tess_view *v, const Plan &plan) {
+    return plan.form == TESS_FORM_AUTO && g.vp.edges && g.cell_px < (v->wrap ? 1.5 : 6.0);
+}
+
 // One image.  Without stats nothing waits for the device.
 tess_status project_impl(const tess_lattice_s *L, const tess_view *v, const Plan &plan, float *image,
                          tess_stats *stats, hipStream_t s, Workspace &ws) {
@@ -828,12 +836,16 @@ tess_status project_impl(const tess_lattice_s *L, const tess_view *v, const Plan
     const unsigned long long cap = plan.cap ? plan.cap : (known ? capacity_for(it->second) : first_guess(g));
     const int chunk = plan.chunk ? plan.chunk : auto_chunk(known ? it->second : cap / 2, g.B);
     st = check_limit(ws, plan, z, chunk, cap, 1);
-    if (st != TESS_OK) return st;
-    st = ensure_front(ws, z);
+    if (st == TESS_OK) st = ensure_front(ws, z);
+    if (st == TESS_OK) st = ensure_back(ws, g.ntiles, chunk, cap);
+    if (st == TESS_ENOMEM && may_fall_back(g, v, plan)) {
+        (void)hipGetLastError();  // (the failed allocation's)
+        Plan p = plan;
+        p.form = TESS_FORM_PER_TETRAHEDRON;
+        return project_impl(L, v, p, image, stats, s, ws);
+    }
     if (st != TESS_OK) return st;
     TESS_HIP(ws.plan.ensure(1));
-    st = ensure_back(ws, g.ntiles, chunk, cap);
-    if (st != TESS_OK) return st;
     if (stats) TESS_HIP(hipEventRecord(ws.ev[0], s));
     const Bufs b = bufs_of(ws);
     st = enqueue_setup(g, b, ws.plan.p, true, ws.counters.p, s);
@@ -1315,6 +1327,23 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
     }
     const std::string key = shape_key(snaps[0], &views[0], n_snaps, n_views, tune);
     const std::string count_key = "batch|" + key;
+    bool falls_back = false;
+    {
+        const Plan p = choose_plan(&views[0], tune);
+        Geometry g;
+        const tess_status st = make_geometry(snaps[0], &views[0], p, g);
+        if (st != TESS_OK) return st;
+        falls_back = may_fall_back(g, &views[0], p);
+    }
+    auto per_tetrahedron = [&]() {
+        (void)hipGetLastError();  // (the failed allocation's)
+        tess_tune t2{};
+        if (tune) t2 = *tune;
+        t2.form = TESS_FORM_PER_TETRAHEDRON;
+        return project_batch_impl(snaps, n_snaps, views, n_views, &t2, images, stats, s, ws);
+    };
+    // (the counting passes' edge buffers would stay and count against the limit)
+    if (falls_back && tune && tune->workspace_limit) return per_tetrahedron();
     // raster parameters and capacity: this process's, the cache file's, or tuned now
     Tuned t;
     bool have = false;
@@ -1337,6 +1366,7 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
     if (!have) {
         unsigned long long most_own = 0;
         tess_status rc = tune_batch(snaps, n_snaps, views, n_views, tune, images, s, ws, t, &most_own);
+        if (rc == TESS_ENOMEM && falls_back) return per_tetrahedron();
         if (rc != TESS_OK) return rc;
         if (most_own) {
             unsigned long long &own = ws.learned_own[count_key];
@@ -1377,10 +1407,9 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
             z.add(g);
         }
     tess_status st = check_limit(ws, t.plan, z, t.chunk, t.cap, (size_t)n_img);
-    if (st != TESS_OK) return st;
-    st = ensure_front(ws, z);
-    if (st != TESS_OK) return st;
-    st = ensure_back(ws, z.ntiles, t.chunk, t.cap);
+    if (st == TESS_OK) st = ensure_front(ws, z);
+    if (st == TESS_OK) st = ensure_back(ws, z.ntiles, t.chunk, t.cap);
+    if (st == TESS_ENOMEM && falls_back) return per_tetrahedron();
     if (st != TESS_OK) return st;
     TESS_HIP(ws.plan.ensure((size_t)n_img));
     if (ws.host_plan_cap < (size_t)n_img) {

@@ -123,3 +123,32 @@ def test_first_batch_of_a_window_has_room_for_its_own_records(tess):
     assert st["overflow"] == 0
     for i, v in enumerate(views):
         assert same(img[0, i], tess.project(lat, v, tune=tess.make_tune(form="per_tetrahedron")))
+
+
+# A workspace limit that the per-tetrahedron form meets is met by the
+# automatic form of a coarse image too, single and in a batch
+@pytest.mark.parametrize("batch", [False, True])
+def test_coarse_windows_fit_the_limits_of_the_per_tetrahedron_form(tess, batch):
+    import torch
+    lat = lattice(tess, 24, 2.0)
+    view = W.rotated_view(W.random_rotations(1, 1)[0], 64)
+    ref = tess.project(lat, view, tune=tess.make_tune(form="per_tetrahedron"))
+
+    def drawn(form, limit):
+        with torch.cuda.stream(torch.cuda.Stream()):  # (a workspace of its own)
+            tune = tess.make_tune(form=form, workspace_limit=limit)
+            try:
+                img = tess.project_batch([lat], [view], tune=tune)[0, 0] if batch else tess.project(lat, view, tune=tune)
+            except tess.TessError as e:
+                assert e.status == -2
+                return False
+            torch.cuda.current_stream().synchronize()
+            assert same(img, ref)
+            return True
+
+    seen = set()
+    for limit in [int(2 ** (20 + k / 2)) for k in range(0, 16, 1)]:
+        tet, auto = drawn("per_tetrahedron", limit), drawn("auto", limit)
+        assert auto or not tet, limit
+        seen.add(tet)
+    assert seen == {False, True}
