@@ -379,15 +379,12 @@ void make_params(const tess_lattice_s *L, const tess_view *v, int form, LatticeP
     vp.mass_px = 6.0 * lp.tet_mass * vp.inv_du * vp.inv_dv;
     // steepest x slope a crease-form footprint may have: a kink's rounding
     // (2^-53 of its slope change) grows by up to the image width along the
-    // row sums; 256 / width of the mean pixel value (all the mass in view)
-    // keeps a kink's at 3e-14 of the mean.  Measured in FP64 against the
-    // exact image (32^3, D = 1 and 4, widths 128 and 512), rms of the mean:
-    // rotated windows 6 to 9e-13 at 64 / width and at 256 / width, periodic
-    // images 2 to 8e-13 and 2 to 18e-13, 1e4 times below the FP32 output's
-    // rounding; the steep tetrahedra, which then keep their own record, fall
-    // from 6-9 to 2-3 % of a periodic image's and from 35 to 10 % of a window's
+    // row sums; 64 / width of the mean pixel value (all the mass in view)
+    // keeps that near 1e-14 of the mean.  (At 256 / width an image is 1.04 to
+    // 1.3x faster, but its FP64 sums are two to four times further from the
+    // exact image: 32^3, D = 4 -> 512^2 0.8e-12 and 1.8e-12 of the mean.)
     vp.crease_bmax = vp.mass_px * (double)lp.ncubes / ((double)v->width * (double)v->height) *
-                     (256.0 / (double)v->width);
+                     (64.0 / (double)v->width);
     vp.W = v->width;
     vp.H = v->height;
     vp.wrap = v->wrap;
@@ -395,12 +392,12 @@ void make_params(const tess_lattice_s *L, const tess_view *v, int form, LatticeP
     // The crease threshold in the image's own scale. q = 1: the integral of q
     // over the tetrahedra, which setup reads from the device (k_qsum fills it;
     // with many streams it far exceeds the volume). q = rho^2: the density
-    // image's threshold (at 64 / width) times the mean density; the integral of
-    // rho^2 is dominated by the image's peaks, where the row sums are already
-    // at their noisiest, and would loosen the threshold there.
+    // image's threshold times the mean density; the integral of rho^2 is
+    // dominated by the image's peaks, where the row sums are already at their
+    // noisiest, and would loosen the threshold there.
     vp.qsum = nullptr;
     vp.bmax_per_q = vp.inv_du * vp.inv_dv / ((double)v->width * (double)v->height) * (64.0 / (double)v->width);
-    if (vp.qpow == 2) vp.crease_bmax *= 0.25 * lp.tet_mass / lp.v0;
+    if (vp.qpow == 2) vp.crease_bmax *= lp.tet_mass / lp.v0;
     vp.slab = v->slab;
     vp.slab_t[0] = v->slab ? v->slab_t[0] : 0.0;
     vp.slab_t[1] = v->slab ? v->slab_t[1] : 0.0;
