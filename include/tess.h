@@ -177,7 +177,8 @@ typedef enum {
  * table form a conforming mesh); it regroups FP64 sums and changes nothing
  * else.  Other views ignore the field. */
 typedef enum {
-    TESS_FORM_AUTO = 0,            /* edge form for periodic lattices, else when a cell spans >= 6 pixels */
+    TESS_FORM_AUTO = 0,            /* edge form when a lattice cell spans >= 1.5 pixels (wrapped image) or >= 6,
+                                      and for coarser wrapped density images of 2^20 cubes and more */
     TESS_FORM_PER_TETRAHEDRON = 1, /* every tetrahedron drawn on its own              */
     TESS_FORM_EDGES = 2            /* edge form whenever the record ids fit 32 bits    */
 } tess_form;
@@ -206,8 +207,8 @@ typedef struct {
                                before allocating anything.  0: no limit         */
     uint64_t own_capacity;  /* edge form: payloads kept for the tetrahedra that
                                keep their own record (steep or wide footprints,
-                               a fraction of a percent of a finely drawn image,
-                               a fifth of a coarse window's); those beyond are set
+                               a fraction of a percent of a finely drawn image);
+                               those beyond are set
                                up again and drawn by the overflow raster
                                (correct, slower).  0: learned per shape from
                                earlier calls (first guess: one in 64, one in 4
@@ -255,9 +256,10 @@ typedef struct {
  * Pixel values are sums of FP64 terms accumulated with atomics, rounded to
  * FP32 at the end: repeated calls agree to FP64 rounding, not bit for bit.
  * Plain pyramids are drawn in the form tune->form selects (automatic: the
- * edge form for periodic lattices, and for others when a lattice cell spans
- * at least 6 pixels; an image of few pixels per cell whose edge form finds no
- * room is drawn per tetrahedron); the edge form is not used
+ * edge form when a lattice cell spans at least 1.5 pixels of a periodic
+ * image, or 6 pixels of a window without wrap, and for coarser periodic
+ * density images of large lattices; such a one whose edge form finds no room
+ * is drawn per tetrahedron); the edge form is not used
  * when its 13 records per lattice point would not fit 32-bit ids.
  * With stats == NULL the call only enqueues work on `stream`: it never waits
  * for the device, so it may be captured into a HIP graph once a first call

@@ -352,7 +352,42 @@ extern "C" void tess_free(tess_lattice L) {
 
 // ------------------------------------------------------------ projection
 namespace {
-void make_params(const tess_lattice_s *L, const tess_view *v, int form, LatticeParams &lp, ViewParams &vp) {
+struct Plan {
+    int Th, Tw, chunk, block;  // chunk 0: from the pair count
+    int form;                  // tess_form
+    unsigned long long cap;    // pair capacity; 0: learned
+    int counts;                // 0: a call with stats skips the edge raster's fragment count
+    unsigned long long limit;  // workspace bytes allowed after the call; 0: no limit
+    unsigned long long own;    // edge form: payloads for tetrahedra with own records; 0: learned
+};
+
+// How an image is drawn, from the lattice, the view and the form asked for.
+// Only plain pyramids have an edge form.  Automatically it is taken by
+//  - periodic images from 1.5 pixels per lattice cell (128^3 -> 512^2 6.4 ms
+//    per tetrahedron, 1.9 by edges; 64^3 -> 256^2 0.92 and 0.40);
+//  - coarser periodic density images of 2^20 cubes and more, as kCoarse
+//    (200^3 -> 256^2 18.1 and 6.3 ms; 140^3 -> 112^2 5.6 and 2.8 at D = 5,
+//    3.6 and 3.4 at D = 1; 100^3 -> 80^2 2.0 and 1.1, 1.3 and 1.4; smaller
+//    lattices gain and lose alike: 64^3 -> 51^2 0.54 and 0.45, 0.40 and 0.49);
+//  - windows from 6 pixels per cell.  Below, a fifth of a periodic lattice's
+//    tetrahedra (those of cubes unwrapped across the box) and the steep ones
+//    keep their own records, and the forms come out alike at 128^3 (-> 512^2
+//    3.8 and 3.4 ms at D = 4; -> 160^2 3.2 and 3.1), while smaller lattices
+//    lose by edges (64^3 -> 512^2 0.70 and 0.83, -> 128^2 0.48 and 0.57; 32^3
+//    -> 200^2 0.21 and 0.25).
+// tess_tune.form forces either (the two give the same image up to rounding).
+enum Drawn { kPerTetrahedron, kEdges, kCoarse };
+constexpr int64_t kCoarseCubes = (int64_t)1 << 20;
+Drawn drawn_form(const LatticeParams &lp, const ViewParams &vp, int form) {
+    if (view_form(vp) != kFormPyramid || form == TESS_FORM_PER_TETRAHEDRON) return kPerTetrahedron;
+    if (form == TESS_FORM_EDGES) return kEdges;
+    const double cell_px = std::cbrt(lp.box[0] * lp.box[1] * lp.box[2] / (double)lp.ncubes) *
+                           std::sqrt(vp.inv_du * vp.inv_dv);
+    if (cell_px >= (vp.wrap ? 1.5 : 6.0)) return kEdges;
+    return vp.wrap && vp.qpow == 1 && lp.ncubes >= kCoarseCubes ? kCoarse : kPerTetrahedron;
+}
+
+Drawn make_params(const tess_lattice_s *L, const tess_view *v, int form, LatticeParams &lp, ViewParams &vp) {
     const tess_build_desc &d = L->desc;
     lp.x = L->x;
     lp.y = L->y;
@@ -408,34 +443,21 @@ void make_params(const tess_lattice_s *L, const tess_view *v, int form, LatticeP
     // q / rho needs |V| to full precision (the face form stores q itself, a
     // splat q |V| and |V|^(1/3))
     if (vp.qpow != 1 || vp.slab || vp.splat || vp.persp) lp.det_cond_k = -1.0;
-    // Plain pyramids of periodic lattices take the edge form (measured on
-    // lattices of 16^3 to 256^3, D = 1 to 8: periodic images of 0.3 to 21
-    // pixels per lattice cell 1.15x faster at 32^3 -> 24^2, 2 to 3x at 64^3
-    // and up; rotated windows of 1 to 16 pixels per cell 1.0 to 1.3x, 64^3
-    // 0.93x, though the tetrahedra of cubes unwrapped across the box, a fifth
-    // of them, keep their own records there).  Lattices without periods from
-    // 6 pixels per cell: one cut from a periodic box has cubes stretched over
-    // it, whose tetrahedra all keep their own (128^3 at 2 pixels 5.2 ms per
-    // tetrahedron, 5.3 by edges).  tess_tune.form forces either (the two give
-    // the same image up to rounding).
-    const double cell_px = std::cbrt(d.box[0] * d.box[1] * d.box[2] / (double)lp.ncubes) *
-                           std::sqrt(vp.inv_du * vp.inv_dv);
-    const bool force_tet = form == TESS_FORM_PER_TETRAHEDRON, force_edges = form == TESS_FORM_EDGES;
-    vp.edges = (view_form(vp) == kFormPyramid && !force_tet && (force_edges || d.periodic || cell_px >= 6.0)) ? 1 : 0;
+    const Drawn drawn = drawn_form(lp, vp, form);
+    vp.edges = drawn != kPerTetrahedron;
+    // Where the automatic form takes the edge form below 1.5 pixels per cell,
+    // nearly all of a pixel's many kinks are its own tetrahedra's and the
+    // steep ones weigh most: at 2 / width the sums are as near the exact image
+    // as the per-tetrahedron form's (lattices of 64^3 to 110^3, D = 1 to 8,
+    // 20^2 to 160 x 150: rms 0.98 to 1.04 of it, largest error 0.98 to 1.00;
+    // at 64 / width the rms is 1.04 to 2.7 of it).
+    if (drawn == kCoarse) vp.crease_bmax *= 2.0 / 64.0;
     vp.kinks = nullptr;
     vp.sil = nullptr;
     vp.stack = nullptr;
     vp.nstack = 0;
+    return drawn;
 }
-
-struct Plan {
-    int Th, Tw, chunk, block;  // chunk 0: from the pair count
-    int form;                  // tess_form
-    unsigned long long cap;    // pair capacity; 0: learned
-    int counts;                // 0: a call with stats skips the edge raster's fragment count
-    unsigned long long limit;  // workspace bytes allowed after the call; 0: no limit
-    unsigned long long own;    // edge form: payloads for tetrahedra with own records; 0: learned
-};
 
 // Default tiling: tiles of up to 512 columns with as many rows as the
 // 128 KiB accumulator allows (at most 64). Taller tiles mean fewer (record,
@@ -497,6 +519,7 @@ struct Geometry {
     BinParams B;
     int64_t ntet, ntiles, nmat, npix;  // (a stack: lists and pixels of all its slabs)
     double cell_px;  // pixels per lattice cell
+    bool coarse;     // edge form taken as kCoarse
     int64_t stored;  // tetrahedron payloads: all (6 ncubes), or (edge form) own_cap
     int64_t spill;   // edge form: 32-bit words of the spill bit set (one spare)
 };
@@ -507,7 +530,7 @@ struct Geometry {
 // as one (v's slab holds all of theirs); 0: a single image
 tess_status make_geometry(const tess_lattice_s *L, const tess_view *v, const Plan &plan, Geometry &g,
                           int64_t own_cap = -1, int nstack = 0) {
-    make_params(L, v, plan.form, g.lp, g.vp);
+    g.coarse = make_params(L, v, plan.form, g.lp, g.vp) == kCoarse;
     g.vp.nstack = nstack;
     g.cell_px = std::cbrt(g.lp.box[0] * g.lp.box[1] * g.lp.box[2] / (double)g.lp.ncubes) *
                 std::sqrt(g.vp.inv_du * g.vp.inv_dv);
@@ -516,7 +539,12 @@ tess_status make_geometry(const tess_lattice_s *L, const tess_view *v, const Pla
     // edge form only while all ids fit in 32 bits
     const int64_t nvert = (int64_t)g.lp.d[0] * g.lp.d[1] * g.lp.d[2];
     const int64_t ntets = 6 * g.lp.ncubes;
-    if (g.vp.edges && ntets + 7 * nvert >= (int64_t)0xffffffff) g.vp.edges = 0;
+    if (g.vp.edges && ntets + 7 * nvert >= (int64_t)0xffffffff) {
+        // (as kCoarse too: the bound of the per-tetrahedron form)
+        if (g.coarse) g.vp.crease_bmax *= 64.0 / 2.0;
+        g.vp.edges = 0;
+        g.coarse = false;
+    }
     g.stored = g.vp.edges && own_cap >= 0 ? std::min<int64_t>(own_cap, ntets) : ntets;
     g.spill = g.vp.edges ? (ntets + 31) / 32 + 1 : 0;
     g.vp.own_cap = (uint64_t)g.stored;
@@ -735,7 +763,7 @@ void fill_stats(tess_stats *stats, const DevCounters &c, const Plan &plan, int c
 std::string count_key(const Geometry &g) {
     char buf[256];
     snprintf(buf, sizeof(buf), "%d:%d:%d:%d|%dx%d:%d:%d:%d:%d:%d|%dx%d", g.lp.d[0], g.lp.d[1], g.lp.d[2], g.lp.periodic,
-             g.B.W, g.B.H, g.B.wrap, g.B.form, g.B.edges, g.vp.qpow, g.vp.hybrid, g.B.Th, g.B.Tw);
+             g.B.W, g.B.H, g.B.wrap, g.B.form, g.B.edges + g.coarse, g.vp.qpow, g.vp.hybrid, g.B.Th, g.B.Tw);
     return buf;
 }
 
@@ -806,13 +834,9 @@ tess_status give_feedback(Workspace &ws, const PlanOut *plan, int n, const std::
     return TESS_OK;
 }
 
-// Images of few pixels per lattice cell, where the edge form gains least: they
-// are drawn per tetrahedron when its buffers find no memory or exceed the
-// caller's limit (the two forms' sizes lie within a third of each other,
-// either way).
-bool may_fall_back(const Geometry &g, const tess_view *v, const Plan &plan) {
-    return plan.form == TESS_FORM_AUTO && g.vp.edges && g.cell_px < (v->wrap ? 1.5 : 6.0);
-}
+// Coarse images are drawn per tetrahedron when the edge form's buffers find no
+// memory or exceed the caller's limit.
+bool may_fall_back(const Geometry &g) { return g.coarse; }
 
 // One image.  Without stats nothing waits for the device.
 tess_status project_impl(const tess_lattice_s *L, const tess_view *v, const Plan &plan, float *image,
@@ -835,7 +859,7 @@ tess_status project_impl(const tess_lattice_s *L, const tess_view *v, const Plan
     st = check_limit(ws, plan, z, chunk, cap, 1);
     if (st == TESS_OK) st = ensure_front(ws, z);
     if (st == TESS_OK) st = ensure_back(ws, g.ntiles, chunk, cap);
-    if (st == TESS_ENOMEM && may_fall_back(g, v, plan)) {
+    if (st == TESS_ENOMEM && may_fall_back(g)) {
         (void)hipGetLastError();  // (the failed allocation's)
         Plan p = plan;
         p.form = TESS_FORM_PER_TETRAHEDRON;
@@ -1330,7 +1354,7 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
         Geometry g;
         const tess_status st = make_geometry(snaps[0], &views[0], p, g);
         if (st != TESS_OK) return st;
-        falls_back = may_fall_back(g, &views[0], p);
+        falls_back = may_fall_back(g);
     }
     auto per_tetrahedron = [&]() {
         (void)hipGetLastError();  // (the failed allocation's)
