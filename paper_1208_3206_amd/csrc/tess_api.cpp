@@ -470,10 +470,13 @@ Drawn make_params(const tess_lattice_s *L, const tess_view *v, int form, Lattice
 // 512^2 1.30 ms at 32 x 512, 1.50 at 32 x 128).
 Plan choose_plan(const tess_view *v, const tess_tune *tune) {
     Plan p;
-    const bool small = v->wrap && v->width <= 512 && !v->slab && v->method == TESS_METHOD_TESSELLATION;
+    // (given rows go with the wide tiles: up to 16384 rows of narrow ones one
+    // high would be more than kMaxTiles)
+    const bool small = v->wrap && v->width <= 512 && !v->slab && v->method == TESS_METHOD_TESSELLATION &&
+                       !(tune && (tune->tile_rows || tune->tile_cols));
     int Tw = (tune && tune->tile_cols) ? tune->tile_cols : std::min(v->width, small ? 128 : 512);
     int Th = 1;
-    const int most_rows = small && !(tune && tune->tile_cols) ? 32 : 64;
+    const int most_rows = small ? 32 : 64;
     while (Th < most_rows && 2 * Th * Tw <= kMaxTileCells) Th *= 2;
     if (tune && tune->tile_rows) Th = tune->tile_rows;
     p.Th = Th;

@@ -89,3 +89,16 @@ def test_coarse_images_are_as_exact_by_edges(n, size, growth):
     rms = [np.sqrt((e ** 2).mean()) for e in err]
     assert rms[1] <= 1.05 * rms[0]
     assert np.abs(err[1]).max() <= 1.05 * np.abs(err[0]).max()
+
+
+# A caller's tile rows go with tiles up to 512 wide, on periodic images too:
+# an image of the largest side in rows one high stays within the tile limit,
+# and a tile too large for the LDS stays refused
+def test_given_tile_rows_keep_wide_tiles(dev):
+    lat = dev.build((8, 8, 8))
+    for call in (dev.project, lambda lat, v, **t: dev.batch([lat], [v], **t), dev.noalloc):
+        assert call(lat, W.z_view(512, 8200), tile_rows=1) == 0, dev.error()
+        assert (dev.log.Th, dev.log.Tw) == (1, 512)
+        assert call(lat, W.z_view(200), tile_rows=100) == EINVAL
+    assert dev.project(lat, W.z_view(512, 16384), tile_rows=1) == 0, dev.error()
+    assert dev.project(lat, W.z_view(512)) == 0 and (dev.log.Th, dev.log.Tw) == (32, 128)
