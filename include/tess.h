@@ -207,12 +207,11 @@ typedef struct {
                                before allocating anything.  0: no limit         */
     uint64_t own_capacity;  /* edge form: payloads kept for the tetrahedra that
                                keep their own record (steep or wide footprints,
-                               a fraction of a percent of a finely drawn image);
-                               those beyond are set
+                               a fraction of a percent); those beyond are set
                                up again and drawn by the overflow raster
                                (correct, slower).  0: learned per shape from
-                               earlier calls (first guess: one in 64, one in 4
-                               below 6 pixels per lattice cell)                */
+                               earlier calls (first guess: one in 64, all for
+                               images below 1.5 pixels per lattice cell)       */
 } tess_tune;
 
 typedef struct {

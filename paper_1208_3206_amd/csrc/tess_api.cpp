@@ -521,7 +521,6 @@ struct Geometry {
     ViewParams vp;
     BinParams B;
     int64_t ntet, ntiles, nmat, npix;  // (a stack: lists and pixels of all its slabs)
-    double cell_px;  // pixels per lattice cell
     bool coarse;     // edge form taken as kCoarse
     int64_t stored;  // tetrahedron payloads: all (6 ncubes), or (edge form) own_cap
     int64_t spill;   // edge form: 32-bit words of the spill bit set (one spare)
@@ -535,8 +534,6 @@ tess_status make_geometry(const tess_lattice_s *L, const tess_view *v, const Pla
                           int64_t own_cap = -1, int nstack = 0) {
     g.coarse = make_params(L, v, plan.form, g.lp, g.vp) == kCoarse;
     g.vp.nstack = nstack;
-    g.cell_px = std::cbrt(g.lp.box[0] * g.lp.box[1] * g.lp.box[2] / (double)g.lp.ncubes) *
-                std::sqrt(g.vp.inv_du * g.vp.inv_dv);
     // records: the tetrahedra (edge form: the few that keep their own record,
     // own_cap of them), then (edge form) seven edges per lattice vertex; the
     // edge form only while all ids fit in 32 bits
@@ -774,14 +771,14 @@ unsigned long long capacity_for(unsigned long long most) { return most + most / 
 
 // Edge form: payloads for the tetrahedra that keep their own record (steep
 // or wide footprints): from the most seen for this shape, else a first guess
-// of one in 64 at 6 pixels per lattice cell and more (measured: 0.2 % on a
-// 64^3 lattice at 8), one in 4 below (2 to 27 % at 0.3 to 4 pixels); those
-// beyond are drawn by the overflow raster and raise the next call's.
+// of one in 64 (measured: 0.2 % on a 64^3 lattice at 8 pixels per cell), for
+// a coarse image all (3 to 60 %); those beyond are drawn by the overflow
+// raster and raise the next call's.
 int64_t own_capacity(const Workspace &ws, const Geometry &g0, const std::string &key, const Plan &plan) {
     const int64_t ntets = 6 * g0.lp.ncubes;
     if (plan.own) return std::min<int64_t>((int64_t)plan.own, ntets);
     auto it = ws.learned_own.find(key);
-    const int64_t want = it != ws.learned_own.end() ? (int64_t)capacity_for(it->second) : ntets / (g0.cell_px < 6.0 ? 4 : 64) + 65536;
+    const int64_t want = it != ws.learned_own.end() ? (int64_t)capacity_for(it->second) : (g0.coarse ? ntets : ntets / 64 + 65536);
     return std::min<int64_t>(want, ntets);
 }
 

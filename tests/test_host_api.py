@@ -102,3 +102,24 @@ def test_given_tile_rows_keep_wide_tiles(dev):
         assert call(lat, W.z_view(200), tile_rows=100) == EINVAL
     assert dev.project(lat, W.z_view(512, 16384), tile_rows=1) == 0, dev.error()
     assert dev.project(lat, W.z_view(512)) == 0 and (dev.log.Th, dev.log.Tw) == (32, 128)
+
+
+# Payloads for own records at a shape's first call: one tetrahedron in 64 (and
+# 65,536) where the edge form always was the automatic one, all for the coarse
+# images; then from the count
+@pytest.mark.parametrize("n,width,first", [(64, 97, 64), (128, 512, 64), (64, 380, 64), (32, 256, 64), (102, 80, 1)])
+def test_first_guess_of_own_records(dev, n, width, first):
+    lat, ntets = dev.build((n, n, n)), 6 * n ** 3
+    guess = ntets if first == 1 else min(ntets, ntets // 64 + 65536)
+    dev.counts(own=1000)
+    for tune, want in ((dict(own_capacity=5000), 5000), ({}, guess), ({}, 1000 + 125 + 4096)):
+        # (a stream has what its own calls have counted)
+        assert dev.project(lat, W.z_view(width), stats=True, stream=2 if tune else 1, **tune) == 0, dev.error()
+        assert dev.log.edges == 1 and dev.log.stored == want
+
+
+# a workspace limit that held a periodic image of 4 pixels per cell with that
+# guess (128^3 -> 512^2 in tiles of 32 x 512: 2,066,967,552 bytes)
+def test_limit_of_a_periodic_image_at_four_pixels_per_cell(dev):
+    lat = dev.build((128, 128, 128))
+    assert dev.project(lat, W.z_view(512), tile_rows=32, chunk=12768, workspace_limit=2066967552) == 0, dev.error()
