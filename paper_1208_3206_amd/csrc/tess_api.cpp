@@ -359,6 +359,7 @@ struct Plan {
     int counts;                // 0: a call with stats skips the edge raster's fragment count
     unsigned long long limit;  // workspace bytes allowed after the call; 0: no limit
     unsigned long long own;    // edge form: payloads for tetrahedra with own records; 0: learned
+    bool lean;                 // as little memory as there is to it: wide tiles, long work items, no kCoarse
 };
 
 // How an image is drawn, from the lattice, the view and the form asked for.
@@ -378,16 +379,16 @@ struct Plan {
 // tess_tune.form forces either (the two give the same image up to rounding).
 enum Drawn { kPerTetrahedron, kEdges, kCoarse };
 constexpr int64_t kCoarseCubes = (int64_t)1 << 20;
-Drawn drawn_form(const LatticeParams &lp, const ViewParams &vp, int form) {
+Drawn drawn_form(const LatticeParams &lp, const ViewParams &vp, int form, bool lean) {
     if (view_form(vp) != kFormPyramid || form == TESS_FORM_PER_TETRAHEDRON) return kPerTetrahedron;
     if (form == TESS_FORM_EDGES) return kEdges;
     const double cell_px = std::cbrt(lp.box[0] * lp.box[1] * lp.box[2] / (double)lp.ncubes) *
                            std::sqrt(vp.inv_du * vp.inv_dv);
     if (cell_px >= (vp.wrap ? 1.5 : 6.0)) return kEdges;
-    return vp.wrap && vp.qpow == 1 && lp.ncubes >= kCoarseCubes ? kCoarse : kPerTetrahedron;
+    return !lean && vp.wrap && vp.qpow == 1 && lp.ncubes >= kCoarseCubes ? kCoarse : kPerTetrahedron;
 }
 
-Drawn make_params(const tess_lattice_s *L, const tess_view *v, int form, LatticeParams &lp, ViewParams &vp) {
+Drawn make_params(const tess_lattice_s *L, const tess_view *v, int form, bool lean, LatticeParams &lp, ViewParams &vp) {
     const tess_build_desc &d = L->desc;
     lp.x = L->x;
     lp.y = L->y;
@@ -443,7 +444,7 @@ Drawn make_params(const tess_lattice_s *L, const tess_view *v, int form, Lattice
     // q / rho needs |V| to full precision (the face form stores q itself, a
     // splat q |V| and |V|^(1/3))
     if (vp.qpow != 1 || vp.slab || vp.splat || vp.persp) lp.det_cond_k = -1.0;
-    const Drawn drawn = drawn_form(lp, vp, form);
+    const Drawn drawn = drawn_form(lp, vp, form, lean);
     vp.edges = drawn != kPerTetrahedron;
     // Where the automatic form takes the edge form below 1.5 pixels per cell,
     // nearly all of a pixel's many kinks are its own tetrahedra's and the
@@ -472,7 +473,11 @@ Plan choose_plan(const tess_view *v, const tess_tune *tune) {
     Plan p;
     // (given rows go with the wide tiles: up to 16384 rows of narrow ones one
     // high would be more than kMaxTiles)
-    const bool small = v->wrap && v->width <= 512 && !v->slab && v->method == TESS_METHOD_TESSELLATION &&
+    // A caller's limits and capacities go with the lean plan: narrow tiles have
+    // more pairs, short work items are more of them, and a coarse image by
+    // edges has other pairs than per tetrahedron and takes more room.
+    p.lean = tune && (tune->workspace_limit || tune->pair_capacity || tune->own_capacity);
+    const bool small = !p.lean && v->wrap && v->width <= 512 && !v->slab && v->method == TESS_METHOD_TESSELLATION &&
                        !(tune && (tune->tile_rows || tune->tile_cols));
     int Tw = (tune && tune->tile_cols) ? tune->tile_cols : std::min(v->width, small ? 128 : 512);
     int Th = 1;
@@ -506,10 +511,12 @@ Plan choose_plan(const tess_view *v, const tess_tune *tune) {
 //  - pairs drawn pixel by pixel, which vary most and are handed out to the
 //    wavefronts one by one: 128^3 in perspective 48.5 at 2,048, 51 at 7,400;
 //    64^3 1.44 at 256 to 512, 1.85 at 2,048.
-int auto_chunk(unsigned long long total_pairs, const BinParams &B) {
+// The lean plan's are of a 4096th of the pairs, at least 1,024.
+int auto_chunk(unsigned long long total_pairs, const BinParams &B, bool lean) {
     auto within = [](unsigned long long x, unsigned long long lo, unsigned long long hi) {
         return (int)std::min(hi, std::max(lo, x));
     };
+    if (lean) return within(total_pairs / 4096ull, 1024ull, 65536ull);
     if (B.direct) return within(total_pairs / 16384ull, 256ull, 65536ull);
     if (B.wrap) return within(std::max(std::min(total_pairs / 128ull, 8192ull), total_pairs / 1024ull), 1024ull, 65536ull);
     return within(std::max(std::min(total_pairs / 512ull, 4096ull), total_pairs / 4096ull), 512ull, 65536ull);
@@ -532,7 +539,7 @@ struct Geometry {
 // as one (v's slab holds all of theirs); 0: a single image
 tess_status make_geometry(const tess_lattice_s *L, const tess_view *v, const Plan &plan, Geometry &g,
                           int64_t own_cap = -1, int nstack = 0) {
-    g.coarse = make_params(L, v, plan.form, g.lp, g.vp) == kCoarse;
+    g.coarse = make_params(L, v, plan.form, plan.lean, g.lp, g.vp) == kCoarse;
     g.vp.nstack = nstack;
     // records: the tetrahedra (edge form: the few that keep their own record,
     // own_cap of them), then (edge form) seven edges per lattice vertex; the
@@ -855,7 +862,7 @@ tess_status project_impl(const tess_lattice_s *L, const tess_view *v, const Plan
     auto it = ws.learned.find(key);
     const bool known = it != ws.learned.end();
     const unsigned long long cap = plan.cap ? plan.cap : (known ? capacity_for(it->second) : first_guess(g));
-    const int chunk = plan.chunk ? plan.chunk : auto_chunk(known ? it->second : cap / 2, g.B);
+    const int chunk = plan.chunk ? plan.chunk : auto_chunk(known ? it->second : cap / 2, g.B, plan.lean);
     st = check_limit(ws, plan, z, chunk, cap, 1);
     if (st == TESS_OK) st = ensure_front(ws, z);
     if (st == TESS_OK) st = ensure_back(ws, g.ntiles, chunk, cap);
@@ -1163,7 +1170,7 @@ tess_status tune_batch(const tess_lattice *snaps, int n_snaps, const tess_view *
     Geometry g0;
     tess_status st = make_geometry(snaps[0], &views[0], plan, g0);
     if (st != TESS_OK) return st;
-    out.chunk = plan.chunk ? plan.chunk : auto_chunk(most, g0.B);
+    out.chunk = plan.chunk ? plan.chunk : auto_chunk(most, g0.B, plan.lean);
     out.cap = plan.cap ? plan.cap : most + most / 16 + 4096;
     return TESS_OK;
 }
@@ -1293,7 +1300,7 @@ tess_status project_stacks(const tess_lattice *snaps, int n_snaps, const tess_vi
         ws.learned[key] = most;
     }
     const unsigned long long cap = capacity_for(most);
-    const int chunk = plan.chunk ? plan.chunk : auto_chunk(most, bins);
+    const int chunk = plan.chunk ? plan.chunk : auto_chunk(most, bins, plan.lean);
     st = ensure_back(ws, z.ntiles, chunk, cap);
     if (st != TESS_OK) {
         *taken = st != TESS_ENOMEM;
@@ -1346,16 +1353,18 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
         const tess_status st = project_stacks(snaps, n_snaps, views, n_views, per, tune, images, stats, s, ws, &taken);
         if (taken) return st;
     }
-    const std::string key = shape_key(snaps[0], &views[0], n_snaps, n_views, tune);
-    const std::string count_key = "batch|" + key;
+    const Plan asked = choose_plan(&views[0], tune);
     bool falls_back = false;
-    {
-        const Plan p = choose_plan(&views[0], tune);
+    for (int v = 0; v < n_views; ++v) {
         Geometry g;
-        const tess_status st = make_geometry(snaps[0], &views[0], p, g);
+        const tess_status st = make_geometry(snaps[0], &views[v], asked, g);
         if (st != TESS_OK) return st;
-        falls_back = may_fall_back(g);
+        falls_back = falls_back || may_fall_back(g);
     }
+    // (the counts of coarse images by edges are not those of the lean plan,
+    // nor of what a file holds from before there were any)
+    const std::string key = shape_key(snaps[0], &views[0], n_snaps, n_views, tune) + (falls_back ? "|coarse" : "");
+    const std::string count_key = "batch|" + key;
     auto per_tetrahedron = [&]() {
         (void)hipGetLastError();  // (the failed allocation's)
         tess_tune t2{};
@@ -1363,8 +1372,6 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
         t2.form = TESS_FORM_PER_TETRAHEDRON;
         return project_batch_impl(snaps, n_snaps, views, n_views, &t2, images, stats, s, ws);
     };
-    // (the counting passes' edge buffers would stay and count against the limit)
-    if (falls_back && tune && tune->workspace_limit) return per_tetrahedron();
     // raster parameters and capacity: this process's, the cache file's, or tuned now
     Tuned t;
     bool have = false;
@@ -1397,8 +1404,10 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
         g_tuned[key] = t;
         if (const char *path = tune_cache_path()) write_tune_cache(path, key, t);
     }
-    // this call's workspace limit, whatever tuning the shape got
-    t.plan.limit = choose_plan(&views[0], tune).limit;
+    // this call's limits, whatever tuning the shape got
+    t.plan.limit = asked.limit;
+    t.plan.lean = asked.lean;
+    if (asked.lean && !asked.chunk) t.chunk = std::max(t.chunk, auto_chunk(t.cap, BinParams{}, true));
     // counts of an earlier call that overflowed raise the capacity
     take_feedback(ws, s);
     {

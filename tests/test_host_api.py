@@ -112,7 +112,7 @@ def test_first_guess_of_own_records(dev, n, width, first):
     lat, ntets = dev.build((n, n, n)), 6 * n ** 3
     guess = ntets if first == 1 else min(ntets, ntets // 64 + 65536)
     dev.counts(own=1000)
-    for tune, want in ((dict(own_capacity=5000), 5000), ({}, guess), ({}, 1000 + 125 + 4096)):
+    for tune, want in ((dict(own_capacity=5000, form="edges"), 5000), ({}, guess), ({}, 1000 + 125 + 4096)):
         # (a stream has what its own calls have counted)
         assert dev.project(lat, W.z_view(width), stats=True, stream=2 if tune else 1, **tune) == 0, dev.error()
         assert dev.log.edges == 1 and dev.log.stored == want
@@ -123,3 +123,45 @@ def test_first_guess_of_own_records(dev, n, width, first):
 def test_limit_of_a_periodic_image_at_four_pixels_per_cell(dev):
     lat = dev.build((128, 128, 128))
     assert dev.project(lat, W.z_view(512), tile_rows=32, chunk=12768, workspace_limit=2066967552) == 0, dev.error()
+
+
+# Under a workspace limit a call takes the plan that needs least memory: limits
+# (bytes) that hold these images, single and twice in a batch of 10^5 pairs a
+# list, to the byte
+SLAB = dict(W.z_view(200), slab=(-0.1, 0.2))
+PERSP = W.perspective_view(np.eye(3), (0.5, 0.5, 0.05), 200, 200, extent=(2.0, 2.0))
+LIMITS = [
+    ((64, 64, 64), W.z_view(200), 270644072, 510970692), ((32, 32, 32), W.z_view(512), 47279532, 123605352),
+    ((64, 64, 64), W.z_view(512), 272719732, 513637352), ((50, 50, 50), SLAB, 135431360, 135453876),
+    ((50, 50, 50), dict(W.z_view(200), method="centroids"), 135431360, 135453876),
+    ((50, 50, 50), PERSP, 135431360, 135453876), ((128, 128, 128), W.z_view(200), 2064376260, 3927094244),
+    ((128, 128, 128), W.z_view(100), 2131035504, 2131118480),
+    ((128, 128, 128), W.rotated_view(ROT, 512), 2133885664, 2138531980),
+    ((97, 120, 75), W.z_view(1000, 707), 877422196, 1691801120), ((8, 8, 8), W.z_view(512, 16384), 81146456, 1987038632),
+]
+
+
+@pytest.mark.parametrize("dims,view,single,batch", LIMITS)
+def test_workspace_limits_that_hold_a_call(tess, dims, view, single, batch):
+    dev = hostapi.Device(tess)
+    lat = dev.build(dims)
+    base = dev.held()
+    assert dev.project(lat, view, workspace_limit=single - (1 << 20)) == ENOMEM
+    assert dev.held() == base  # (refused before anything is allocated)
+    assert dev.project(lat, view, workspace_limit=single) == 0, dev.error()
+    assert dev.held() <= base + single
+    dev = hostapi.Device(tess)
+    dev.counts(100000, 5000)
+    lat = dev.build(dims)
+    assert dev.batch([lat], [view] * 2, workspace_limit=batch) == 0, dev.error()
+
+
+# ... and so do calls with a capacity of their own, whose pairs are counted in
+# that plan's tiles and form
+@pytest.mark.parametrize("tune", [dict(pair_capacity=10 ** 6), dict(own_capacity=10 ** 5)])
+def test_given_capacities_keep_tiles_and_forms(dev, tune):
+    lat = dev.build((128, 128, 128))
+    assert dev.project(lat, W.z_view(100), **tune) == 0 and dev.log.edges == 0
+    assert dev.project(lat, W.z_view(512), **tune) == 0 and (dev.log.Th, dev.log.Tw) == (32, 512)
+    assert dev.project(lat, W.z_view(100)) == 0 and dev.log.edges == 1
+    assert dev.project(lat, W.z_view(512)) == 0 and (dev.log.Th, dev.log.Tw) == (32, 128)
