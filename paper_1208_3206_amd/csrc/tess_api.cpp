@@ -13,6 +13,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <utility>
 #include <vector>
@@ -103,6 +104,18 @@ struct Workspace {
     hipStream_t capture = nullptr;
     hipGraphExec_t graph = nullptr;
     std::string graph_key;
+    // shapes whose plan found no memory (by their count keys) and are drawn by
+    // the next smaller one since, with what the attempt had allocated given
+    // back: tried once, so that later calls neither free and allocate again
+    // nor, captured, allocate at all
+    std::set<std::string> no_room;
+    void out_of_memory(const std::string &key) {
+        (void)hipGetLastError();  // (a pinned allocation's)
+        head.release(); coef.release(); ecoef.release(); kinks.release(); sil.release(); spill.release();
+        counts.release(); base.release(); scan.release(); tile_items.release(); items.release(); pairs.release();
+        acc.release(); stack.release();
+        no_room.insert(key);
+    }
     std::mutex mu;
 };
 
@@ -359,6 +372,7 @@ struct Plan {
     int counts;                // 0: a call with stats skips the edge raster's fragment count
     unsigned long long limit;  // workspace bytes allowed after the call; 0: no limit
     unsigned long long own;    // edge form: payloads for tetrahedra with own records; 0: learned
+    bool given;                // the tiles are the caller's or tuned
     bool lean;                 // as little memory as there is to it: wide tiles, long work items, no kCoarse
 };
 
@@ -469,16 +483,18 @@ Drawn make_params(const tess_lattice_s *L, const tess_view *v, int form, bool le
 // of 64^3 -> 512^2 0.23 -> 0.14 ms, 200^3 -> 256^2 2.9 (64 x 256) -> 2.0, 32^3
 // -> 256^2 91 -> 64 us (windows of rotated views gain nothing there: 128^3 ->
 // 512^2 1.30 ms at 32 x 512, 1.50 at 32 x 128).
-Plan choose_plan(const tess_view *v, const tess_tune *tune) {
+// A caller's limits and capacities go with the lean plan (and so may a call
+// that finds no memory): narrow tiles have more pairs, short work items are
+// more of them, and a coarse image by edges has other pairs than per
+// tetrahedron and takes more room.
+Plan choose_plan(const tess_view *v, const tess_tune *tune, bool lean = false) {
     Plan p;
+    p.lean = lean || (tune && (tune->workspace_limit || tune->pair_capacity || tune->own_capacity));
+    p.given = tune && (tune->tile_rows || tune->tile_cols);
     // (given rows go with the wide tiles: up to 16384 rows of narrow ones one
     // high would be more than kMaxTiles)
-    // A caller's limits and capacities go with the lean plan: narrow tiles have
-    // more pairs, short work items are more of them, and a coarse image by
-    // edges has other pairs than per tetrahedron and takes more room.
-    p.lean = tune && (tune->workspace_limit || tune->pair_capacity || tune->own_capacity);
-    const bool small = !p.lean && v->wrap && v->width <= 512 && !v->slab && v->method == TESS_METHOD_TESSELLATION &&
-                       !(tune && (tune->tile_rows || tune->tile_cols));
+    const bool small =
+        !p.lean && !p.given && v->wrap && v->width <= 512 && !v->slab && v->method == TESS_METHOD_TESSELLATION;
     int Tw = (tune && tune->tile_cols) ? tune->tile_cols : std::min(v->width, small ? 128 : 512);
     int Th = 1;
     const int most_rows = small ? 32 : 64;
@@ -841,10 +857,6 @@ tess_status give_feedback(Workspace &ws, const PlanOut *plan, int n, const std::
     return TESS_OK;
 }
 
-// Coarse images are drawn per tetrahedron when the edge form's buffers find no
-// memory or exceed the caller's limit.
-bool may_fall_back(const Geometry &g) { return g.coarse; }
-
 // One image.  Without stats nothing waits for the device.
 tess_status project_impl(const tess_lattice_s *L, const tess_view *v, const Plan &plan, float *image,
                          tess_stats *stats, hipStream_t s, Workspace &ws) {
@@ -853,6 +865,18 @@ tess_status project_impl(const tess_lattice_s *L, const tess_view *v, const Plan
     if (st != TESS_OK) return st;
     take_feedback(ws, s);
     const std::string key = count_key(g);
+    // a coarse image is drawn per tetrahedron when the edge form finds no memory
+    auto per_tetrahedron = [&]() {
+        Plan p = plan;
+        if (!p.given) {
+            const Plan tiles = choose_plan(v, nullptr, true);
+            p.Th = tiles.Th;
+            p.Tw = tiles.Tw;
+        }
+        p.lean = true;
+        return project_impl(L, v, p, image, stats, s, ws);
+    };
+    if (g.coarse && ws.no_room.count(key)) return per_tetrahedron();
     if (g.vp.edges) {
         st = make_geometry(L, v, plan, g, own_capacity(ws, g, key, plan));
         if (st != TESS_OK) return st;
@@ -866,11 +890,9 @@ tess_status project_impl(const tess_lattice_s *L, const tess_view *v, const Plan
     st = check_limit(ws, plan, z, chunk, cap, 1);
     if (st == TESS_OK) st = ensure_front(ws, z);
     if (st == TESS_OK) st = ensure_back(ws, g.ntiles, chunk, cap);
-    if (st == TESS_ENOMEM && may_fall_back(g)) {
-        (void)hipGetLastError();  // (the failed allocation's)
-        Plan p = plan;
-        p.form = TESS_FORM_PER_TETRAHEDRON;
-        return project_impl(L, v, p, image, stats, s, ws);
+    if (st == TESS_ENOMEM && g.coarse) {
+        ws.out_of_memory(key);
+        return per_tetrahedron();
     }
     if (st != TESS_OK) return st;
     TESS_HIP(ws.plan.ensure(1));
@@ -1105,10 +1127,9 @@ tess_status count_all(const tess_lattice *snaps, int n_snaps, const tess_view *v
 // of 512 of them took 6.2 s with it, 2.4 of them in the overflow raster, and
 // takes 3.8.
 tess_status tune_batch(const tess_lattice *snaps, int n_snaps, const tess_view *views, int n_views,
-                       const tess_tune *tune, float *scratch_image, hipStream_t s, Workspace &ws, Tuned &out,
+                       const tess_tune *tune, Plan plan, float *scratch_image, hipStream_t s, Workspace &ws, Tuned &out,
                        unsigned long long *most_own) {
     const int n_img = n_snaps * n_views;
-    Plan plan = choose_plan(&views[0], tune);
     if (!tune || (!tune->tile_rows && !tune->tile_cols)) {
         tess_status st = count_all(snaps, n_snaps, views, n_views, plan, s, ws);
         if (st != TESS_OK) return st;
@@ -1130,6 +1151,7 @@ tess_status tune_batch(const tess_lattice *snaps, int n_snaps, const tess_view *
                 Plan p = plan;
                 p.Th = Th;
                 p.Tw = Tw;
+                p.given = true;
                 p.cap = 0;
                 if (!p.own) p.own = heavy_own;
                 cands.push_back(p);
@@ -1235,15 +1257,23 @@ int stack_size(const tess_view *views, int n_views, const tess_tune *tune) {
 }
 
 // The batch as stacks of up to `per` slabs; *taken = false (and nothing
-// drawn) when they find no memory.
+// drawn or kept) when they find no memory, now or on an earlier call.
 tess_status project_stacks(const tess_lattice *snaps, int n_snaps, const tess_view *views, int n_views, int per,
                            const tess_tune *tune, float *images, tess_stats *stats, hipStream_t s, Workspace &ws,
                            bool *taken) {
-    *taken = true;
     const Plan plan = choose_plan(&views[0], tune);
     const size_t img = (size_t)views[0].width * views[0].height;
     const int groups = (n_views + per - 1) / per, n_st = n_snaps * groups;
     const std::string key = "stack " + std::to_string(per) + "|" + shape_key(snaps[0], &views[0], n_snaps, n_views, tune);
+    *taken = !ws.no_room.count(key);
+    if (!*taken) return TESS_OK;
+    auto no_room = [&](tess_status st) {
+        if (st == TESS_ENOMEM) {
+            ws.out_of_memory(key);
+            *taken = false;
+        }
+        return st;
+    };
     auto slabs = [&](int g) { return std::min(per, n_views - g * per); };
     auto geometry = [&](int i, int g, Geometry &G) {
         tess_view v = views[g * per];
@@ -1265,20 +1295,22 @@ tess_status project_stacks(const tess_lattice *snaps, int n_snaps, const tess_vi
     take_feedback(ws, s);
     auto it = ws.learned.find(key);
     unsigned long long most = it != ws.learned.end() ? it->second : 0;
-    tess_status st = ensure_front(ws, z);
-    if (st != TESS_OK) {
-        *taken = st != TESS_ENOMEM;
-        return st;
-    }
-    TESS_HIP(ws.stack.ensure(2 * (size_t)n_views));
-    TESS_HIP(ws.plan.ensure((size_t)n_st));
-    if (ws.host_plan_cap < (size_t)n_st) {
-        TESS_HIP(hipHostFree(ws.host_plan));
-        ws.host_plan = nullptr;
-        ws.host_plan_cap = 0;
-        TESS_HIP(hipHostMalloc((void **)&ws.host_plan, sizeof(PlanOut) * (size_t)n_st, hipHostMallocDefault));
-        ws.host_plan_cap = (size_t)n_st;
-    }
+    auto front_room = [&]() -> tess_status {
+        const tess_status st = ensure_front(ws, z);
+        if (st != TESS_OK) return st;
+        TESS_HIP(ws.stack.ensure(2 * (size_t)n_views));
+        TESS_HIP(ws.plan.ensure((size_t)n_st));
+        if (ws.host_plan_cap < (size_t)n_st) {
+            TESS_HIP(hipHostFree(ws.host_plan));
+            ws.host_plan = nullptr;
+            ws.host_plan_cap = 0;
+            TESS_HIP(hipHostMalloc((void **)&ws.host_plan, sizeof(PlanOut) * (size_t)n_st, hipHostMallocDefault));
+            ws.host_plan_cap = (size_t)n_st;
+        }
+        return TESS_OK;
+    };
+    tess_status st = no_room(front_room());
+    if (st != TESS_OK) return st;
     std::vector<double> t(2 * (size_t)n_views);
     for (int v = 0; v < n_views; ++v) {
         t[2 * v] = views[v].slab_t[0];
@@ -1301,11 +1333,8 @@ tess_status project_stacks(const tess_lattice *snaps, int n_snaps, const tess_vi
     }
     const unsigned long long cap = capacity_for(most);
     const int chunk = plan.chunk ? plan.chunk : auto_chunk(most, bins, plan.lean);
-    st = ensure_back(ws, z.ntiles, chunk, cap);
-    if (st != TESS_OK) {
-        *taken = st != TESS_ENOMEM;
-        return st;
-    }
+    st = no_room(ensure_back(ws, z.ntiles, chunk, cap));
+    if (st != TESS_OK) return st;
     if (stats) TESS_HIP(hipEventRecord(ws.ev[0], s));
     ZeroList zero;
     zero.add(ws.counters.p, sizeof(DevCounters) / sizeof(double));
@@ -1345,33 +1374,34 @@ tess_status project_stacks(const tess_lattice *snaps, int n_snaps, const tess_vi
 
 tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tess_view *views, int n_views,
                                const tess_tune *tune, float *images, tess_stats *stats, hipStream_t s,
-                               Workspace &ws) {
+                               Workspace &ws, bool lean = false) {
     const size_t img = (size_t)views[0].width * views[0].height;
     const int n_img = n_snaps * n_views;
-    if (const int per = stack_size(views, n_views, tune)) {
+    const int per = lean ? 0 : stack_size(views, n_views, tune);
+    if (per) {
         bool taken = false;
         const tess_status st = project_stacks(snaps, n_snaps, views, n_views, per, tune, images, stats, s, ws, &taken);
         if (taken) return st;
+        lean = true;
     }
-    const Plan asked = choose_plan(&views[0], tune);
-    bool falls_back = false;
+    const Plan asked = choose_plan(&views[0], tune, lean);
+    bool falls_back = false;  // coarse images by edges, per tetrahedron when they find no memory
     for (int v = 0; v < n_views; ++v) {
         Geometry g;
         const tess_status st = make_geometry(snaps[0], &views[v], asked, g);
         if (st != TESS_OK) return st;
-        falls_back = falls_back || may_fall_back(g);
+        falls_back = falls_back || g.coarse;
     }
     // (the counts of coarse images by edges are not those of the lean plan,
     // nor of what a file holds from before there were any)
     const std::string key = shape_key(snaps[0], &views[0], n_snaps, n_views, tune) + (falls_back ? "|coarse" : "");
     const std::string count_key = "batch|" + key;
-    auto per_tetrahedron = [&]() {
-        (void)hipGetLastError();  // (the failed allocation's)
-        tess_tune t2{};
-        if (tune) t2 = *tune;
-        t2.form = TESS_FORM_PER_TETRAHEDRON;
-        return project_batch_impl(snaps, n_snaps, views, n_views, &t2, images, stats, s, ws);
+    auto no_room = [&]() {
+        ws.out_of_memory(count_key);
+        return project_batch_impl(snaps, n_snaps, views, n_views, tune, images, stats, s, ws, true);
     };
+    if (ws.no_room.count(count_key))
+        return project_batch_impl(snaps, n_snaps, views, n_views, tune, images, stats, s, ws, true);
     // raster parameters and capacity: this process's, the cache file's, or tuned now
     Tuned t;
     bool have = false;
@@ -1393,8 +1423,8 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
     }
     if (!have) {
         unsigned long long most_own = 0;
-        tess_status rc = tune_batch(snaps, n_snaps, views, n_views, tune, images, s, ws, t, &most_own);
-        if (rc == TESS_ENOMEM && falls_back) return per_tetrahedron();
+        tess_status rc = tune_batch(snaps, n_snaps, views, n_views, tune, asked, images, s, ws, t, &most_own);
+        if (rc == TESS_ENOMEM && falls_back) return no_room();
         if (rc != TESS_OK) return rc;
         if (most_own) {
             unsigned long long &own = ws.learned_own[count_key];
@@ -1439,7 +1469,7 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
     tess_status st = check_limit(ws, t.plan, z, t.chunk, t.cap, (size_t)n_img);
     if (st == TESS_OK) st = ensure_front(ws, z);
     if (st == TESS_OK) st = ensure_back(ws, z.ntiles, t.chunk, t.cap);
-    if (st == TESS_ENOMEM && falls_back) return per_tetrahedron();
+    if (st == TESS_ENOMEM && falls_back) return no_room();
     if (st != TESS_OK) return st;
     TESS_HIP(ws.plan.ensure((size_t)n_img));
     if (ws.host_plan_cap < (size_t)n_img) {

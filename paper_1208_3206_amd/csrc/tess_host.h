@@ -50,6 +50,7 @@ struct DevBuf {
         hipError_t e = hipMalloc((void **)&p, want * sizeof(T));
         if (e != hipSuccess) {
             p = nullptr;
+            (void)hipGetLastError();  // (reported here: the next launch would report it again)
             return e;
         }
         cap = want;

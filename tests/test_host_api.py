@@ -165,3 +165,97 @@ def test_given_capacities_keep_tiles_and_forms(dev, tune):
     assert dev.project(lat, W.z_view(512), **tune) == 0 and (dev.log.Th, dev.log.Tw) == (32, 512)
     assert dev.project(lat, W.z_view(100)) == 0 and dev.log.edges == 1
     assert dev.project(lat, W.z_view(512)) == 0 and (dev.log.Th, dev.log.Tw) == (32, 128)
+
+
+# When memory ends, a call that fits in its smaller plan is drawn by that, with
+# nothing kept of the attempt: the budget here is what the smaller plan takes
+def budget_of(tess, dims, call):
+    """Bytes that a device holds after `call` of the smaller plan (the calls under a limit take it)."""
+    dev = hostapi.Device(tess)
+    dev.counts(1000, 500)
+    lat = dev.build(dims)
+    for _ in range(2):
+        assert call(dev, lat, workspace_limit=1 << 50) == 0, dev.error()
+    return dev.held()
+
+
+SLABS = [dict(W.z_view(400), slab=(a, a + 0.02)) for a in np.linspace(-0.5, 0.48, 50)]
+
+
+def test_slab_stack_without_memory_is_drawn_slab_by_slab(tess):
+    def call(dev, lat, **tune):
+        return dev.batch([lat], SLABS, **tune)
+    budget = budget_of(tess, (48, 48, 48), call)
+    dev = hostapi.Device(tess)
+    dev.counts(1000, 500)
+    lat = dev.build((48, 48, 48))
+    assert call(dev, lat) == 0 and dev.log.stack_setups > 0 and dev.held() > budget
+    dev = hostapi.Device(tess)
+    dev.counts(1000, 500)
+    lat = dev.build((48, 48, 48))
+    dev.budget(budget + 4096)
+    for k in range(3):
+        dev.reset()
+        assert call(dev, lat) == 0, dev.error()
+        assert dev.lib.fake_last_error() == 0 and dev.held() <= budget + 4096
+        # (later calls replay the graph)
+        assert dev.log.stack_setups == 0 and dev.log.graph_launches == 1
+        assert k == 0 or dev.log.mallocs == dev.log.frees == dev.log.failed_mallocs == 0
+
+
+def test_coarse_image_without_memory_is_drawn_per_tetrahedron(tess):
+    def call(dev, lat, **tune):
+        return dev.project(lat, W.z_view(100), **tune)
+    dims = (128, 128, 128)
+    budget = budget_of(tess, dims, call)
+    dev = hostapi.Device(tess)
+    dev.counts(1000, 500)
+    lat = dev.build(dims)
+    dev.budget(budget + 4096)
+    for k in range(3):
+        dev.reset()
+        dev.capturing(k == 2)
+        assert call(dev, lat) == 0, dev.error()
+        assert dev.log.edges == 0 and dev.lib.fake_last_error() == 0 and dev.held() <= budget + 4096
+        assert k == 0 or dev.log.mallocs == dev.log.frees == dev.log.failed_mallocs == dev.log.illegal == 0
+
+
+# ... a batch too, whichever of its views is the coarse one, and the views that
+# are finer keep the edge form
+@pytest.mark.parametrize("order", [(0, 1), (1, 0), (2, 1), (1,)])
+def test_coarse_batch_without_memory(tess, order):
+    dims, box = (128, 128, 128), (1.0, 1.0, 4.0)
+    eye = np.eye(3)
+    # 2.5 and 1.2 pixels per cell of the periodic images, a window
+    kinds = [dict(W.z_view(200), center=(0.5, 0.5, 2.0)),
+             dict(W.z_view(200), rot=eye[[2, 0, 1]].ravel().tolist(), center=(0.5, 0.5, 2.0), extent=(4.0, 1.0)),
+             W.rotated_view(ROT, 200)]
+    views = [kinds[k] for k in order]
+
+    def run(budget=None, **tune):
+        dev = hostapi.Device(tess)
+        dev.counts(1000, 500)
+        lat = dev.build(dims, box=box)
+        if budget:
+            dev.budget(budget)
+        for _ in range(2):
+            assert dev.batch([lat], views, **tune) == 0, dev.error()
+        return dev
+    lean, free = run(workspace_limit=1 << 50), run()
+    assert free.log.edge_setups > lean.log.edge_setups
+    tight = run(budget=lean.held() + 4096)
+    assert tight.lib.fake_last_error() == 0 and tight.held() <= lean.held() + 4096
+    if 0 not in order:
+        assert free.held() > lean.held() and tight.log.failed_mallocs > 0
+        assert tight.log.edges == 0
+
+
+# A call refused for want of memory leaves nothing for the next one to report
+def test_refused_call_does_not_fail_the_next(dev):
+    lat = dev.build((64, 64, 64))
+    dev.budget(dev.held() + (1 << 20))
+    for call in (lambda: dev.project(lat, W.z_view(512)), lambda: dev.batch([lat], [W.z_view(512)])):
+        assert call() == ENOMEM
+        assert dev.lib.fake_last_error() == 0
+    dev.budget()
+    assert dev.project(lat, W.z_view(512)) == 0, dev.error()
