@@ -111,10 +111,13 @@ struct Workspace {
     std::set<std::string> no_room;
     void out_of_memory(const std::string &key) {
         (void)hipGetLastError();  // (a pinned allocation's)
+        release();
+        no_room.insert(key);
+    }
+    void release() {
         head.release(); coef.release(); ecoef.release(); kinks.release(); sil.release(); spill.release();
         counts.release(); base.release(); scan.release(); tile_items.release(); items.release(); pairs.release();
         acc.release(); stack.release();
-        no_room.insert(key);
     }
     std::mutex mu;
 };
@@ -653,10 +656,24 @@ size_t workspace_bytes_after(const Workspace &ws, const Sizes &z, int chunk, uns
     return b;
 }
 
-tess_status check_limit(const Workspace &ws, const Plan &plan, const Sizes &z, int chunk, unsigned long long cap,
-                        size_t n_plan) {
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
+}
+
+tess_status check_limit(Workspace &ws, const Plan &plan, const Sizes &z, int chunk, unsigned long long cap,
+                        size_t n_plan, hipStream_t s) {
     if (!plan.limit) return TESS_OK;
-    const size_t b = workspace_bytes_after(ws, z, chunk, cap, n_plan);
+    size_t b = workspace_bytes_after(ws, z, chunk, cap, n_plan);
+    if (b > plan.limit && !capturing(s)) {
+        // what earlier calls without the limit made larger is given back
+        // when the call fits without it
+        const Workspace none;
+        if (workspace_bytes_after(none, z, chunk, cap, n_plan) + ws.plan.cap * sizeof(PlanOut) <= plan.limit) {
+            ws.release();
+            b = workspace_bytes_after(ws, z, chunk, cap, n_plan);
+        }
+    }
     if (b > plan.limit)
         return fail(TESS_ENOMEM, "the workspace would hold %.1f MiB, above tune.workspace_limit (%.1f MiB)",
                     b / 1048576.0, plan.limit / 1048576.0);
@@ -813,11 +830,6 @@ unsigned long long first_guess(const Geometry &g) {
     return std::min<unsigned long long>(std::max<unsigned long long>(want, 1ull << 20), 1ull << 31);
 }
 
-bool capturing(hipStream_t s) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(s, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
-}
-
 // Takes the counts of the last call if they have arrived (never waits).
 void take_feedback(Workspace &ws, hipStream_t s) {
     if (!ws.fb_pending || capturing(s)) return;
@@ -887,9 +899,12 @@ tess_status project_impl(const tess_lattice_s *L, const tess_view *v, const Plan
     const bool known = it != ws.learned.end();
     const unsigned long long cap = plan.cap ? plan.cap : (known ? capacity_for(it->second) : first_guess(g));
     const int chunk = plan.chunk ? plan.chunk : auto_chunk(known ? it->second : cap / 2, g.B, plan.lean);
-    st = check_limit(ws, plan, z, chunk, cap, 1);
+    st = check_limit(ws, plan, z, chunk, cap, 1, s);
     if (st == TESS_OK) st = ensure_front(ws, z);
-    if (st == TESS_OK) st = ensure_back(ws, g.ntiles, chunk, cap);
+    // (work items for the lean plan's length too, a hundredth of the pairs'
+    // bytes: a later call under a limit then finds room, also under capture)
+    const int shorter = plan.chunk || plan.lean ? chunk : std::min(chunk, auto_chunk(known ? it->second : cap / 2, g.B, true));
+    if (st == TESS_OK) st = ensure_back(ws, g.ntiles, shorter, cap);
     if (st == TESS_ENOMEM && g.coarse) {
         ws.out_of_memory(key);
         return per_tetrahedron();
@@ -1466,7 +1481,7 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
             if (st != TESS_OK) return st;
             z.add(g);
         }
-    tess_status st = check_limit(ws, t.plan, z, t.chunk, t.cap, (size_t)n_img);
+    tess_status st = check_limit(ws, t.plan, z, t.chunk, t.cap, (size_t)n_img, s);
     if (st == TESS_OK) st = ensure_front(ws, z);
     if (st == TESS_OK) st = ensure_back(ws, z.ntiles, t.chunk, t.cap);
     if (st == TESS_ENOMEM && falls_back) return no_room();

@@ -259,3 +259,21 @@ def test_refused_call_does_not_fail_the_next(dev):
         assert dev.lib.fake_last_error() == 0
     dev.budget()
     assert dev.project(lat, W.z_view(512)) == 0, dev.error()
+
+
+# A limit holds after calls without one too, whose plan may have taken more:
+# what it made larger is given back (but not under capture)
+@pytest.mark.parametrize("dims,view,single,batch", LIMITS)
+def test_workspace_limit_after_a_call_without(tess, dims, view, single, batch):
+    dev = hostapi.Device(tess)
+    lat = dev.build(dims)
+    base = dev.held()
+    assert dev.project(lat, view) == 0
+    over = dev.held() > base + single + 4096
+    dev.capturing(1)
+    assert dev.project(lat, view, workspace_limit=single + 4096) == (ENOMEM if over else 0)
+    assert dev.log.illegal == 0
+    dev.capturing(0)
+    for _ in range(2):
+        assert dev.project(lat, view, workspace_limit=single + 4096) == 0, dev.error()
+    assert dev.held() <= base + single + 4096
