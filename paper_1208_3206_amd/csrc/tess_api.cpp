@@ -903,7 +903,9 @@ tess_status project_impl(const tess_lattice_s *L, const tess_view *v, const Plan
     if (st == TESS_OK) st = ensure_front(ws, z);
     // (work items for the lean plan's length too, a hundredth of the pairs'
     // bytes: a later call under a limit then finds room, also under capture)
-    const int shorter = plan.chunk || plan.lean ? chunk : std::min(chunk, auto_chunk(known ? it->second : cap / 2, g.B, true));
+    const int shorter = plan.chunk || plan.lean
+                            ? chunk
+                            : std::min(chunk, auto_chunk(known ? it->second : cap / 2, g.B, true));
     if (st == TESS_OK) st = ensure_back(ws, g.ntiles, shorter, cap);
     if (st == TESS_ENOMEM && g.coarse) {
         ws.out_of_memory(key);
@@ -1625,8 +1627,10 @@ extern "C" tess_status tess_project_noalloc(tess_lattice L, const tess_view *v, 
     Geometry g;
     st = make_geometry(L, v, plan, g);
     if (st != TESS_OK) return st;
-    if (g.vp.edges && plan.form == TESS_FORM_AUTO && noalloc_fixed_bytes(g) > kScratchBytes) {
-        plan.form = TESS_FORM_PER_TETRAHEDRON;  // the smaller of the two
+    // the lean plan unless the pairs expected fit too: narrow tiles have more
+    // of them, and those beyond cost the overflow raster
+    if (!plan.lean && noalloc_fixed_bytes(g) + sizeof(uint32_t) * (size_t)first_guess(g) > kScratchBytes) {
+        plan = choose_plan(v, tune, true);
         st = make_geometry(L, v, plan, g);
         if (st != TESS_OK) return st;
     }

@@ -277,3 +277,17 @@ def test_workspace_limit_after_a_call_without(tess, dims, view, single, batch):
     for _ in range(2):
         assert dev.project(lat, view, workspace_limit=single + 4096) == 0, dev.error()
     assert dev.held() <= base + single + 4096
+
+
+# The allocation-free projection refuses what does not fit its scratch in the
+# automatic form, and keeps wide tiles, of fewer pairs, where these take all
+# the room that is left
+@pytest.mark.parametrize("n,width,rc,tile", [
+    (32, 256, 0, (32, 128)), (40, 320, 0, (32, 128)), (43, 344, 0, (32, 344)), (44, 352, 0, (32, 352)),
+    (50, 200, ECAPACITY, None), (48, 400, ECAPACITY, None), (50, 64, 0, (32, 64)), (52, 60, 0, (64, 60))])
+def test_allocation_free_plans(dev, n, width, rc, tile):
+    lat = dev.build((n, n, n))
+    assert dev.noalloc(lat, W.z_view(width)) == rc
+    if tile:
+        assert (dev.log.Th, dev.log.Tw) == tile
+        assert dev.log.edges == (1 if width >= 1.5 * n else 0)
