@@ -1069,6 +1069,9 @@ std::map<std::string, Tuned> read_tune_cache(const char *path) {
         t.plan.cap = 0;
         t.plan.counts = 1;
         t.plan.limit = 0;
+        t.plan.own = 0;
+        t.plan.given = true;
+        t.plan.lean = false;
         t.chunk = (int)chunk;
         t.cap = cap;
         m[key] = t;
@@ -1453,6 +1456,7 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
     }
     // this call's limits, whatever tuning the shape got
     t.plan.limit = asked.limit;
+    t.plan.own = asked.own;
     t.plan.lean = asked.lean;
     if (asked.lean && !asked.chunk) t.chunk = std::max(t.chunk, auto_chunk(t.cap, BinParams{}, true));
     // counts of an earlier call that overflowed raise the capacity
@@ -1469,11 +1473,11 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
     // between images), then the graph; edge-form images store the payloads of
     // as many tetrahedra with own records as the batch was seen to need
     int64_t own_cap = -1;
-    {
+    for (int v = 0; v < n_views; ++v) {
         Geometry g0;
-        tess_status st = make_geometry(snaps[0], &views[0], t.plan, g0);
+        tess_status st = make_geometry(snaps[0], &views[v], t.plan, g0);
         if (st != TESS_OK) return st;
-        own_cap = own_capacity(ws, g0, count_key, t.plan);
+        own_cap = std::max(own_cap, own_capacity(ws, g0, count_key, t.plan));
     }
     Sizes z;
     for (int i = 0; i < n_snaps; ++i)

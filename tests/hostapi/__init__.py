@@ -32,7 +32,7 @@ class Log(ctypes.Structure):
                   "frees", "failed_mallocs", "graphs", "graph_launches", "illegal")]
                 + [(k, ctypes.c_int32) for k in ("edges", "Th", "Tw", "chunk", "block", "nstack")]
                 + [("ntet", ctypes.c_int64), ("stored", ctypes.c_int64), ("crease_bmax", ctypes.c_double),
-                   ("bmax_per_q", ctypes.c_double), ("cap", ctypes.c_ulonglong), ("max_items", ctypes.c_ulonglong)])
+                   ("bmax_per_q", ctypes.c_double), ("cap", ctypes.c_ulonglong), ("max_items", ctypes.c_ulonglong), ("own_room", ctypes.c_int64)])
 
 
 class Device:

@@ -45,6 +45,7 @@ struct FakeLog {
     int64_t ntet, stored;
     double crease_bmax, bmax_per_q;
     unsigned long long cap, max_items;
+    int64_t own_room;  // payloads for own records of the last image by edges
 };
 FakeLog fake_log;
 void fake_reset() { std::memset(&fake_log, 0, sizeof(fake_log)); }
@@ -153,6 +154,7 @@ hipError_t launch_setup(const LatticeParams &, const ViewParams &V, RecHead *, P
     fake_log.edges = V.edges;
     fake_log.nstack = V.nstack;
     fake_log.stored = (int64_t)V.own_cap;
+    if (V.edges) fake_log.own_room = (int64_t)V.own_cap;
     fake_log.crease_bmax = V.crease_bmax;
     fake_log.bmax_per_q = V.bmax_per_q;
     return launched();

@@ -291,3 +291,24 @@ def test_allocation_free_plans(dev, n, width, rc, tile):
     if tile:
         assert (dev.log.Th, dev.log.Tw) == tile
         assert dev.log.edges == (1 if width >= 1.5 * n else 0)
+
+
+# Plans read from a tune cache file: room for own records as the call asks, or
+# the first guess for any of the batch's views
+def test_cached_plan_has_room_for_own_records(tess, tmp_path, monkeypatch):
+    monkeypatch.setenv("TESS_TUNE_CACHE", str(tmp_path / "tune.json"))
+    n, ntets = 128, 6 * 128 ** 3
+    window, coarse, fine = W.rotated_view(ROT, 100), W.z_view(100), dict(W.z_view(100), quantity="unit")
+    cases = [((64,) * 3, [W.z_view(128)] * 2, {}, 6 * 64 ** 3 // 64 + 65536),
+             ((64,) * 3, [W.z_view(128)] * 2, dict(own_capacity=7000), 7000),
+             ((n,) * 3, [window, coarse], {}, ntets), ((n,) * 3, [coarse, fine], {}, ntets)]
+    for first in (True, False):  # tuned and saved, then read by another process
+        for dims, views, tune, room in cases:
+            dev = hostapi.Device(tess)
+            dev.counts(1000, 500)
+            lat = dev.build(dims)
+            assert dev.batch([lat], views, **tune) == 0, dev.error()
+            if not first:
+                assert dev.log.rasters == len(views)  # (no tuning)
+                assert dev.log.edge_setups == len([v for v in views if v is not window and v is not fine])
+                assert dev.log.own_room == room
