@@ -100,10 +100,12 @@ struct Workspace {
     hipEvent_t fb_event = nullptr;
     std::map<std::string, unsigned long long> learned;  // largest pair count seen per shape key
     std::map<std::string, unsigned long long> learned_own;  // edge form: most tetrahedra with own records
-    // batch graph (captured on `capture`, replayed on the caller's stream)
+    // batch graphs (captured on `capture`, replayed on the caller's stream):
+    // without and with the fragment count, for calls with stats, so that a
+    // caller that asks now and then captures neither again
     hipStream_t capture = nullptr;
-    hipGraphExec_t graph = nullptr;
-    std::string graph_key;
+    hipGraphExec_t graph[2] = {nullptr, nullptr};
+    std::string graph_key[2];
     // shapes whose plan found no memory (by their count keys) and are drawn by
     // the next smaller one since, with what the attempt had allocated given
     // back: tried once, so that later calls neither free and allocate again
@@ -1218,7 +1220,7 @@ tess_status tune_batch(const tess_lattice *snaps, int n_snaps, const tess_view *
 }
 
 std::string graph_key(const tess_lattice *snaps, int n_snaps, const tess_view *views, int n_views, float *images,
-                      const Tuned &t, int64_t own_cap, bool count, const Workspace &ws) {
+                      const Tuned &t, int64_t own_cap, const Workspace &ws) {
     std::string k;
     auto put = [&](const void *p, size_t n) { k.append((const char *)p, n); };
     for (int i = 0; i < n_snaps; ++i) {
@@ -1231,7 +1233,6 @@ std::string graph_key(const tess_lattice *snaps, int n_snaps, const tess_view *v
     put(&images, sizeof(images));
     put(&t, sizeof(t));
     put(&own_cap, sizeof(own_cap));
-    put(&count, sizeof(count));
     const void *bufs[] = {ws.head.p, ws.coef.p, ws.ecoef.p, ws.kinks.p, ws.sil.p, ws.spill.p, ws.counts.p, ws.base.p,
                           ws.scan.p, ws.tile_items.p, ws.items.p, ws.pairs.p, ws.acc.p, ws.plan.p, ws.counters.p,
                           ws.overflow.p};
@@ -1500,11 +1501,13 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
         TESS_HIP(hipHostMalloc((void **)&ws.host_plan, sizeof(PlanOut) * (size_t)n_img, hipHostMallocDefault));
         ws.host_plan_cap = (size_t)n_img;
     }
-    const std::string gkey = graph_key(snaps, n_snaps, views, n_views, images, t, own_cap, stats != nullptr, ws);
-    if (!ws.graph || ws.graph_key != gkey) {
-        if (ws.graph) {
-            TESS_HIP(hipGraphExecDestroy(ws.graph));
-            ws.graph = nullptr;
+    const std::string gkey = graph_key(snaps, n_snaps, views, n_views, images, t, own_cap, ws);
+    const int counts = stats ? 1 : 0;
+    hipGraphExec_t &exec = ws.graph[counts];
+    if (!exec || ws.graph_key[counts] != gkey) {
+        if (exec) {
+            TESS_HIP(hipGraphExecDestroy(exec));
+            exec = nullptr;
         }
         hipStream_t c = ws.capture;
         TESS_HIP(hipStreamBeginCapture(c, hipStreamCaptureModeThreadLocal));
@@ -1520,8 +1523,8 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
                     if (r != TESS_OK) return r;
                     r = enqueue_front(g, bufs_of(ws), ws.plan.p + k, t.cap, true, nullptr, c);
                     if (r != TESS_OK) return r;
-                    r = enqueue_back(g, t.plan, t.chunk, t.cap, stats != nullptr, bufs_of(ws), ws.plan.p + k, images + (size_t)k * img,
-                                     c, nullptr, nullptr);
+                    r = enqueue_back(g, t.plan, t.chunk, t.cap, stats != nullptr, bufs_of(ws), ws.plan.p + k,
+                                     images + (size_t)k * img, c, nullptr, nullptr);
                     if (r != TESS_OK) return r;
                 }
             return TESS_OK;
@@ -1534,16 +1537,16 @@ tess_status project_batch_impl(const tess_lattice *snaps, int n_snaps, const tes
             return cst;
         }
         if (end != hipSuccess) return fail(TESS_EHIP, "batch graph capture: %s", hipGetErrorString(end));
-        const hipError_t inst = hipGraphInstantiate(&ws.graph, graph, nullptr, nullptr, 0);
+        const hipError_t inst = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
         (void)hipGraphDestroy(graph);
         if (inst != hipSuccess) {
-            ws.graph = nullptr;
+            exec = nullptr;
             return fail(TESS_EHIP, "batch graph instantiation: %s", hipGetErrorString(inst));
         }
-        ws.graph_key = gkey;
+        ws.graph_key[counts] = gkey;
     }
     if (stats) TESS_HIP(hipEventRecord(ws.ev[0], s));
-    TESS_HIP(hipGraphLaunch(ws.graph, s));
+    TESS_HIP(hipGraphLaunch(exec, s));
     if (!stats) return give_feedback(ws, ws.plan.p, n_img, count_key, s);
     TESS_HIP(hipEventRecord(ws.ev[4], s));
     TESS_HIP(hipMemcpyAsync(ws.host_plan, ws.plan.p, sizeof(PlanOut) * (size_t)n_img, hipMemcpyDeviceToHost, s));

@@ -312,3 +312,16 @@ def test_cached_plan_has_room_for_own_records(tess, tmp_path, monkeypatch):
                 assert dev.log.rasters == len(views)  # (no tuning)
                 assert dev.log.edge_setups == len([v for v in views if v is not window and v is not fine])
                 assert dev.log.own_room == room
+
+
+# A batch's graphs, with and without the fragment count, are both kept: calls
+# that ask for statistics now and then capture neither again
+def test_batches_with_and_without_stats_keep_their_graphs(dev):
+    lat = dev.build((32, 32, 32))
+    views = [W.z_view(128)] * 3
+    for k in range(6):
+        assert dev.batch([lat], views, stats=k % 2 == 1) == 0, dev.error()
+        if k == 2:  # (the first counts settle the capacities)
+            dev.reset()
+    assert dev.log.graphs == 0 and dev.log.graph_launches == 3
+    assert dev.batch([lat], views[:2]) == 0 and dev.log.graphs == 1
