@@ -93,8 +93,7 @@ __global__ void __launch_bounds__(256, 2) k_setup(LatticeParams L, ViewParams V,
         for (int64_t cube = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; cube < L.ncubes; cube += stride) {
             uint32_t todo = 0u;
             setup_cube<FORM, EDGES, 1>(
-                L, V, cube, [](int, const RecHead &, const Payload &) {}, cnt, &todo,
-                [](int, const RecHead &) -> Payload * { return nullptr; }, [](int) {});
+                L, V, cube, [](int, const RecHead &, const Payload &) {}, cnt, &todo);
             if (todo) {
                 // (the six bits lie in one word or two)
                 const int64_t tet = 6 * cube;

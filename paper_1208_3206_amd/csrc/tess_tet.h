@@ -743,16 +743,14 @@ TESS_HD inline double vertex_px(const LatticeParams &L, const ViewParams &V, int
 // silhouette, both ends for a diagonal of a quadrilateral one, averaged).
 // Returns -1, having counted nothing, when the tetrahedron needs the
 // general setup: a face seen edge-on, a silhouette set that is neither a
-// triangle nor a quadrilateral, crossing diagonals not found, or a period
-// or margin test that fails; 0 (zeros) when it has no volume or covers no
-// pixel centre; 8 when its footprint is steep along x, past the crease
-// form's bound: it then keeps its own record in the line form, returned in
-// own; else its number of silhouette edges.
-template <typename OwnSink>
+// triangle nor a quadrilateral, crossing diagonals not found, a period or
+// margin test that fails, or a footprint steep along x, past the crease
+// form's bound (it keeps its own record, in the line form); 0 (zeros) when it
+// has no volume or covers no pixel centre; else its number of silhouette
+// edges.
 TESS_HD inline int edge_tet_fast(const LatticeParams &L, const ViewParams &V, int t, const double e[8][3],
                                  const double PX[8], const double PY[8], double crease_bmax, bool same_frame,
-                                 uint32_t qpack, double kd[6], uint32_t &sil, uint32_t &shf, OwnSink &&own_sink,
-                                 CubeCounts &cnt) {
+                                 uint32_t qpack, double kd[6], uint32_t &sil, uint32_t &shf, CubeCounts &cnt) {
     const int v0 = kTet[t][0], v1 = kTet[t][1], v2 = kTet[t][2], v3 = kTet[t][3];
     bool flagged;
     const double det6 = tet_det6(L, e, v0, v1, v2, v3, flagged);
@@ -818,41 +816,7 @@ TESS_HD inline int edge_tet_fast(const LatticeParams &L, const ViewParams &V, in
     const bool tri = smask == 0x38u || smask == 0x26u || smask == 0x15u || smask == 0x0bu;
     const bool quad = smask == 0x1eu || smask == 0x2du || smask == 0x33u;
     if (!(tri || quad)) return -1;
-    if (!(bmax <= crease_bmax)) {
-        // steep along x: the line form, whatever the edge form's tests say;
-        // its record holds the silhouette edges' face functions in edge
-        // order (footprint's G functions a + b u + c v: K times the cross
-        // product with the edge)
-        RecHead R;
-        R.bx = pack_range(ix0, ix1);
-        R.by = pack_range(iy0, iy1);
-        R.flags = (tri ? 3u : 4u) | REC_VALID;
-        R.spare = 0u;
-        // the payload is written where own_sink places it, a value at a time
-        // (no place: the general setup takes the tetrahedron)
-        Payload *const P = own_sink(t, R);
-        if (!P) return -1;
-        {
-            int k = 0;
-#pragma unroll
-            for (int g = 0; g < 6; ++g) {
-                if (!((smask >> g) & 1u)) continue;
-                const EdgeInfo E = kEdge[g];
-                const double dx = qx[E.j] - qx[E.i], dy = qy[E.j] - qy[E.i];
-                const double ck = (double)E.sk * D[E.l];
-                const double cl = (double)E.sl * D[E.k];
-                const double K = mass_px / (ck * fabs(cl));
-                P->c[3 * k + 0] = K * (dy * qx[E.i] - dx * qy[E.i]);
-                P->c[3 * k + 1] = -K * dy;
-                P->c[3 * k + 2] = K * dx;
-                ++k;
-            }
-            for (int g = 3 * k; g < 14; ++g) P->c[g] = 0.0;
-            P->h = R;
-        }
-        count_tet(L, det6, flagged, cnt);
-        return 8;
-    }
+    if (!(bmax <= crease_bmax)) return -1;
     // the period and margin tests of the edge form (as in setup_cube)
     if (!same_frame) return -1;
     uint32_t shift = 0x555u;
@@ -918,24 +882,9 @@ TESS_HD inline int edge_tet_fast(const LatticeParams &L, const ViewParams &V, in
 // tetrahedron t's record goes to emit(t, head, payload) (flags 0 when it can
 // cover no pixel centre; REC_EDGED when its creases went to its edges' slots,
 // which setup_cube writes itself).
-//
-// The edge form's common path writes a line-form record (edge_tet_fast) to
-// where own_sink(t, head) says, then calls own_done(t); without them the
-// record is built in a local payload and goes to emit like the others.
-template <int FORM, bool EDGES, int PASS, typename Emit, typename OwnSink, typename OwnDone>
-TESS_HD inline void setup_cube(const LatticeParams &L, const ViewParams &V, int64_t cube, Emit &&emit,
-                               CubeCounts &cnt, uint32_t *todo_io, OwnSink &&own_sink, OwnDone &&own_done);
 template <int FORM, bool EDGES = false, int PASS = 0, typename Emit>
 TESS_HD inline void setup_cube(const LatticeParams &L, const ViewParams &V, int64_t cube, Emit &&emit,
                                CubeCounts &cnt, uint32_t *todo_io = nullptr) {
-    Payload own;
-    setup_cube<FORM, EDGES, PASS>(
-        L, V, cube, emit, cnt, todo_io, [&](int, const RecHead &) -> Payload * { return &own; },
-        [&](int t) { emit(t, own.h, own); });
-}
-template <int FORM, bool EDGES, int PASS, typename Emit, typename OwnSink, typename OwnDone>
-TESS_HD inline void setup_cube(const LatticeParams &L, const ViewParams &V, int64_t cube, Emit &&emit,
-                               CubeCounts &cnt, uint32_t *todo_io, OwnSink &&own_sink, OwnDone &&own_done) {
     double X0[3], e[8][3];
     const bool moved = cube_corners(L, cube, X0, e);
     int64_t ci, cj, ck;
@@ -1033,17 +982,12 @@ TESS_HD inline void setup_cube(const LatticeParams &L, const ViewParams &V, int6
             double kd[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
             uint32_t ksil = 0u, kshf = 0x555u;
             const int fast =
-                edge_tet_fast(L, V, t, e, PX, PY, crease_bmax, same_frame, qpack, kd, ksil, kshf, own_sink, cnt);
+                edge_tet_fast(L, V, t, e, PX, PY, crease_bmax, same_frame, qpack, kd, ksil, kshf, cnt);
             if (fast < 0) {
                 todo |= 1u << t;
                 // (PASS 3 then writes only the slots of those whose creases
                 // go to their edges: here a wavefront's writes are whole lines)
                 if constexpr (PASS == 1) edge_slots(t, kd, 0u, 0x555u);
-                continue;
-            }
-            if (fast == 8) {  // its own record is written
-                own_done(t);
-                edge_slots(t, kd, 0u, 0x555u);
                 continue;
             }
             // (no payload: the head says whether its creases went to the edges)
@@ -2680,8 +2624,9 @@ TESS_HD inline uint32_t raster_record(const RecHead &h, const double *cf, const 
                                       int ty0, int n, int rows, Dep &&dep, Seam &&seam, uint32_t &spans,
                                       uint32_t &kinks) {
     if constexpr (FORM == kFormFace) {
-        // as second differences, for a caller that sums the rows: the pixels
-        // of the tile and of the two columns left of it
+        // as second differences, for the host checks, which sum the rows of
+        // every form (the kernels deposit slab_pair's values): the pixels of
+        // the tile and of the two columns left of it
         const int left = min(2, tx0);
         uint32_t frags = 0;
         slab_pair(h, cf, B, tx0 - left, ty0, n + left, rows, 0, 1,
