@@ -487,7 +487,7 @@ Drawn make_params(const tess_lattice_s *L, const tess_view *v, int form, bool le
 // two blocks share a CU and one works while the other starts or ends: raster
 // of 64^3 -> 512^2 0.23 -> 0.14 ms, 200^3 -> 256^2 2.9 (64 x 256) -> 2.0, 32^3
 // -> 256^2 91 -> 64 us (windows of rotated views gain nothing there: 128^3 ->
-// 512^2 1.30 ms at 32 x 512, 1.50 at 32 x 128).
+// 512^2 2.94 ms at 32 x 512, 3.17 at 32 x 128).
 // A caller's limits and capacities go with the lean plan (and so may a call
 // that finds no memory): narrow tiles have more pairs, short work items are
 // more of them, and a coarse image by edges has other pairs than per
@@ -525,10 +525,14 @@ Plan choose_plan(const tess_view *v, const tess_tune *tune, bool lean = false) {
 //  - periodic images, whose pairs are nearly all edges and cost alike: 128^3
 //    -> 1024^2 1.61 at 4,096, 1.16 at 8,192, 1.09 at 32,768; 200^3 -> 256^2
 //    2.40 at 8,192, 1.96 at 32,768; 97x120x75 -> 1000x707 0.52 at 4,096, 0.38
-//    at 8,192 and 16,384; 64^3 -> 512^2 0.19 at 4,096, 0.17 at 16,384;
-//  - windows, with own records, ten times an edge's cost, at the front of the
-//    lists: 128^3 -> 512^2 1.37 at 2,048, 1.25 at 4,096, 1.54 at 16,384; 96^3
-//    -> 400^2 0.64 at 4,096, 0.94 at 16,384; 32^3 -> 512^2 0.12 at 512;
+//    at 8,192 and 16,384; 64^3 -> 512^2 0.19 at 4,096, 0.17 at 16,384 (per
+//    tetrahedron 64^3 -> 90^2 0.57 at 3,608, 0.46 at 8,192; 96^3 -> 128^2
+//    1.55 at 4,096, 1.72 at 8,192);
+//  - windows, whose pairs differ more (tetrahedra of all sizes; by edges own
+//    records, ten times an edge's cost): 128^3 -> 512^2 3.26 at 2,048, 2.96 at
+//    4,096, 3.09 at 16,384; 64^3 -> 512^2 0.75 at 1,024, 0.53 at 4,096, 0.67
+//    at 8,192; 32^3 -> 200^2 0.108 at 512, 0.077 at 1,024, 0.102 at 2,048;
+//    by edges 32^3 -> 512^2 0.135 at 512, 0.123 at 1,024, 0.173 at 2,048;
 //  - pairs drawn pixel by pixel, which vary most and are handed out to the
 //    wavefronts one by one: 128^3 in perspective 48.5 at 2,048, 51 at 7,400;
 //    64^3 1.44 at 256 to 512, 1.85 at 2,048.
@@ -540,7 +544,7 @@ int auto_chunk(unsigned long long total_pairs, const BinParams &B, bool lean) {
     if (lean) return within(total_pairs / 4096ull, 1024ull, 65536ull);
     if (B.direct) return within(total_pairs / 16384ull, 256ull, 65536ull);
     if (B.wrap) return within(std::max(std::min(total_pairs / 128ull, 8192ull), total_pairs / 1024ull), 1024ull, 65536ull);
-    return within(std::max(std::min(total_pairs / 512ull, 4096ull), total_pairs / 4096ull), 512ull, 65536ull);
+    return within(std::max(std::min(total_pairs / 512ull, 4096ull), total_pairs / 4096ull), 1024ull, 65536ull);
 }
 
 // Sizes of one image's pipeline.

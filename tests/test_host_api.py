@@ -325,3 +325,13 @@ def test_batches_with_and_without_stats_keep_their_graphs(dev):
             dev.reset()
     assert dev.log.graphs == 0 and dev.log.graph_launches == 3
     assert dev.batch([lat], views[:2]) == 0 and dev.log.graphs == 1
+
+
+# Work items of a window have 1,024 entries at least, at most what fills the chip
+@pytest.mark.parametrize("pairs,chunk", [(1000, 1024), (220000, 1024), (2400000, 4096), (40000000, 9765)])
+def test_work_items_of_windows(dev, pairs, chunk):
+    lat = dev.build((32, 32, 32))
+    dev.counts(pairs)
+    for _ in range(2):  # one tile; the second call knows its pairs
+        assert dev.project(lat, W.rotated_view(ROT, 100, 64), stats=True) == 0
+    assert dev.log.Th == 64 and dev.log.chunk == chunk
