@@ -186,7 +186,9 @@ typedef enum {
 /* Raster parameters.  0 in a field means "choose automatically".  The image
  * is cut into tiles of tile_rows x tile_cols pixels (row bands when tile_cols
  * >= width); one raster work group holds a tile's FP64 accumulator, so
- * tile_rows * tile_cols must be <= 16384 (128 KiB of LDS). */
+ * tile_rows * tile_cols must be <= 16384 (128 KiB of LDS).  With a
+ * pair_capacity, workspace_limit or own_capacity the automatic choices are
+ * those that need least memory. */
 typedef struct {
     int32_t tile_rows;      /* 1 .. 256                                           */
     int32_t tile_cols;      /* 16 .. 16384                                        */
@@ -204,7 +206,9 @@ typedef struct {
     uint64_t workspace_limit; /* bytes of device memory the library's workspace
                                for this stream may hold after the call; a call
                                that would grow it beyond returns TESS_ENOMEM
-                               before allocating anything.  0: no limit         */
+                               before allocating anything (buffers that earlier
+                               calls made larger are given back first when the
+                               call fits without them).  0: no limit            */
     uint64_t own_capacity;  /* edge form: payloads kept for the tetrahedra that
                                keep their own record (steep or wide footprints,
                                a fraction of a percent); those beyond are set
@@ -315,7 +319,12 @@ tess_status tess_project_noalloc(tess_lattice lat, const tess_view *view, const 
  * environment variable TESS_TUNE_CACHE names a file, the choice is kept
  * there as JSON keyed by shape and device and read back by later processes.
  * An image whose pairs exceed the capacity is drawn by the overflow raster
- * inside the graph, and later calls capture with a larger capacity.
+ * inside the graph, and later calls capture with a larger capacity.  (Calls
+ * with and without stats have a graph each.)
+ * Views that differ only in depth slabs of which neither end decreases along
+ * the views are drawn, per snapshot, as one image of many layers: enqueued
+ * without a graph, the default tiling, nothing in the cache file; without
+ * memory for that, or with a pair_capacity or workspace_limit, slab by slab.
  * stats (host, nullable) receives the sums over all images (synchronises).
  * Errors: as tess_project; views of different sizes, snapshots of different
  * dims or periodicity -> TESS_EINVAL.
