@@ -26,11 +26,12 @@ PEAK_VALU_OPS = 256 * 4 * 16 * 2.4e9          # 3.93e13 lane-ops/s
 # along the crease, floor it, the fraction phi from the crossing (2), and the
 # two second-difference entries D*phi and D - D*phi (2).
 OPS_PER_KINK = 6
-# A perspective view's raster evaluates every pixel of a footprint's box (the
+# A perspective view's raster evaluates every pixel of the rows' spans (the
 # chord is not piecewise linear along a row; tess_stats.kinks counts those
-# pixels): 4 faces x (n . d, 2; the quotient h / n . d, 1; the min or max, 1),
-# the ray length |(pu, pv, 1)| (3) and q times the chord (3).
-OPS_PER_RAY_PIXEL = 22
+# pixels): the four inverse-depth planes (an FMA each), the larger and the
+# smaller bound (2), their two tests (2), the difference, the product of the
+# bounds, its reciprocal, the two products of the chord (5) and its add (1).
+OPS_PER_RAY_PIXEL = 14
 # Its LDS traffic: two FP64 read-modify-writes.
 LDS_BYTES_PER_KINK = 2 * 16
 PEAK_LDS_BYTES = 256 * 128 * 2.4e9            # 128 B/clk/CU: 78.6 TB/s
@@ -47,8 +48,8 @@ TRAFFIC = {
     "sources": ["paper_1208_3206_amd/csrc/tess_kernels.hip", "paper_1208_3206_amd/csrc/tess_tet.h",
                 "paper_1208_3206_amd/csrc/tess_internal.h"],
     "workload": "stress_256^3_to_2048^2", "tile": [32, 512], "block": 1024,
-    "sha256": "85d33369ca77ebdb3cf2195ab2841842b475b2e138d8d1ddb5d6978fa5eb008a",
-    "fetch_kib": 45821456.6, "write_kib": 1422494.9, "fetch_scale": 2.0, "write_scale": 1.0,
+    "sha256": "d3ae409bd0df19f83971b530c88741b5a9a3df1cf472bfbbe84690f6fa0ae8ca",
+    "fetch_kib": 45854224.9, "write_kib": 1422495.0, "fetch_scale": 2.0, "write_scale": 1.0,
 }
 
 
