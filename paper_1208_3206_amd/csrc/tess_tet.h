@@ -407,9 +407,13 @@ TESS_HD inline uint32_t crease_profile(const double cf[14], int height) {
 // when the opposite vertex lies behind it (the ray enters there) and back
 // otherwise; a face seen edge-on is a wall, stored and tied as in the line
 // form. qv is the projected value q. Returns false when the tetrahedron lies
-// outside the slab or its projection is degenerate.
+// outside the slab or its projection is degenerate.  Without contraction: a
+// face with two vertices on one ray has equal products in D, which differ by
+// their rounding when one of them is fused, and a wall then passes for a face
+// of slope 1e17.
 TESS_HD inline bool face_payload(const double qx[4], const double qy[4], const double T[4], double s0,
                                  double s1, double qv, double out[14], uint32_t &flags) {
+#pragma clang fp contract(off)
     if (fmax(fmax(T[0], T[1]), fmax(T[2], T[3])) <= s0 || fmin(fmin(T[0], T[1]), fmin(T[2], T[3])) >= s1)
         return false;
     uint32_t fl = 0;
@@ -453,6 +457,13 @@ TESS_HD inline bool face_payload(const double qx[4], const double qy[4], const d
     out[13] = 0.0;
     flags = fl;
     return true;
+}
+
+// A wall's half-plane (c0, c1, c2 of its face) at a pixel centre: exactly 0 on
+// an axis-aligned wall through it, so without contraction too.
+TESS_HD inline double wall_side(const double *c, double X, double Y) {
+#pragma clang fp contract(off)
+    return c[0] + c[1] * X + c[2] * Y;
 }
 
 // A face payload without walls in the order front faces, back faces; returns
@@ -2172,7 +2183,7 @@ TESS_HD inline uint32_t slab_pair(const RecHead &h, const double *cf, const BinP
 #pragma unroll
                         for (int g = 0; g < 4; ++g) {
                             const uint32_t type = (h.flags >> (REC_FACE_TYPE_SHIFT + 2 * g)) & 3u;
-                            const double w = cf[3 * g] + cf[3 * g + 1] * X + cf[3 * g + 2] * Y;
+                            const double w = wall_side(&cf[3 * g], X, Y);
                             if (type == REC_FACE_FRONT) lo = fmax(lo, w);
                             else if (type == REC_FACE_BACK) hi = fmin(hi, w);
                             else if (type == REC_FACE_WALL)
