@@ -48,8 +48,8 @@ TRAFFIC = {
     "sources": ["paper_1208_3206_amd/csrc/tess_kernels.hip", "paper_1208_3206_amd/csrc/tess_tet.h",
                 "paper_1208_3206_amd/csrc/tess_internal.h"],
     "workload": "stress_256^3_to_2048^2", "tile": [32, 512], "block": 1024,
-    "sha256": "d3ae409bd0df19f83971b530c88741b5a9a3df1cf472bfbbe84690f6fa0ae8ca",
-    "fetch_kib": 45854224.9, "write_kib": 1422495.0, "fetch_scale": 2.0, "write_scale": 1.0,
+    "sha256": "06be9722cd1ee019b56e7d4d95fea30b0dd000b3f43579958b3266530c1fbce8",
+    "fetch_kib": 45858420.2, "write_kib": 1422494.9, "fetch_scale": 2.0, "write_scale": 1.0,
 }
 
 

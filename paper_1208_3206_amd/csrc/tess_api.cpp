@@ -386,7 +386,7 @@ struct Plan {
 //  - periodic images from 1.5 pixels per lattice cell (128^3 -> 512^2 6.4 ms
 //    per tetrahedron, 1.9 by edges; 64^3 -> 256^2 0.92 and 0.40);
 //  - coarser periodic density images of 2^20 cubes and more, as kCoarse
-//    (200^3 -> 256^2 18.1 and 6.3 ms; 140^3 -> 112^2 5.6 and 2.8 at D = 5,
+//    (200^3 -> 256^2 18.1 and 7.0 ms; 140^3 -> 112^2 5.6 and 2.8 at D = 5,
 //    3.6 and 3.4 at D = 1; 100^3 -> 80^2 2.0 and 1.1, 1.3 and 1.4; smaller
 //    lattices gain and lose alike: 64^3 -> 51^2 0.54 and 0.45, 0.40 and 0.49);
 //  - windows from 6 pixels per cell.  Below, a fifth of a periodic lattice's
@@ -1148,10 +1148,9 @@ tess_status count_all(const tess_lattice *snaps, int n_snaps, const tess_view *v
 // fastest candidate, timed on the image with the most pairs) and the pair
 // capacity (tune's, or the largest count over all images under that tiling,
 // with a small margin, so that no image of these snapshots overflows).  The
-// counts also give the most tetrahedra with own records, *most_own: windows
-// of 128^3 tracers at D = 8 have more than the first guess, and a first batch
-// of 512 of them took 6.2 s with it, 2.4 of them in the overflow raster, and
-// takes 3.8.
+// counts also give the most tetrahedra with own records, *most_own, which may
+// be more than the first guess (by edges 512 windows of 128^3 tracers took 6.2
+// s with the guess, 2.4 of them in the overflow raster, and 3.8 with the count).
 tess_status tune_batch(const tess_lattice *snaps, int n_snaps, const tess_view *views, int n_views,
                        const tess_tune *tune, Plan plan, float *scratch_image, hipStream_t s, Workspace &ws, Tuned &out,
                        unsigned long long *most_own) {
