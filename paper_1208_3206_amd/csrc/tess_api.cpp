@@ -531,8 +531,12 @@ Plan choose_plan(const tess_view *v, const tess_tune *tune, bool lean = false) {
 //  - windows, whose pairs differ more (tetrahedra of all sizes; by edges own
 //    records, ten times an edge's cost): 128^3 -> 512^2 3.26 at 2,048, 2.96 at
 //    4,096, 3.09 at 16,384; 64^3 -> 512^2 0.75 at 1,024, 0.53 at 4,096, 0.67
-//    at 8,192; 32^3 -> 200^2 0.108 at 512, 0.077 at 1,024, 0.102 at 2,048;
-//    by edges 32^3 -> 512^2 0.135 at 512, 0.123 at 1,024, 0.173 at 2,048;
+//    at 8,192.  Small ones, with binning, are best in about 200 items, not
+//    quite one a CU, down to 512 entries each: 18 x 12 x 12 -> 1389^2 0.145 at
+//    512 (151 items), 0.179 at 1,024; 30^3 -> 100^2 0.106 at 512 (285), 0.081
+//    at 726 (201), 0.083 at 1,024 (143); 32^3 -> 200^2 0.151 at 512 (432),
+//    0.121 at 1,024 (217); by edges 20^3 -> 500 x 400 0.125 at 512 (171), 0.165
+//    at 1,024; 32^3 -> 512^2 0.177 at 512 (692), 0.162 at 1,024 (349);
 //  - pairs drawn pixel by pixel, which vary most and are handed out to the
 //    wavefronts one by one: 128^3 in perspective 48.5 at 2,048, 51 at 7,400;
 //    64^3 1.44 at 256 to 512, 1.85 at 2,048.
@@ -544,7 +548,9 @@ int auto_chunk(unsigned long long total_pairs, const BinParams &B, bool lean) {
     if (lean) return within(total_pairs / 4096ull, 1024ull, 65536ull);
     if (B.direct) return within(total_pairs / 16384ull, 256ull, 65536ull);
     if (B.wrap) return within(std::max(std::min(total_pairs / 128ull, 8192ull), total_pairs / 1024ull), 1024ull, 65536ull);
-    return within(std::max(std::min(total_pairs / 512ull, 4096ull), total_pairs / 4096ull), 1024ull, 65536ull);
+    return within(std::max({std::min(total_pairs / 200ull, 1024ull), std::min(total_pairs / 512ull, 4096ull),
+                            total_pairs / 4096ull}),
+                  512ull, 65536ull);
 }
 
 // Sizes of one image's pipeline.

@@ -327,8 +327,10 @@ def test_batches_with_and_without_stats_keep_their_graphs(dev):
     assert dev.batch([lat], views[:2]) == 0 and dev.log.graphs == 1
 
 
-# Work items of a window have 1,024 entries at least, at most what fills the chip
-@pytest.mark.parametrize("pairs,chunk", [(1000, 1024), (220000, 1024), (2400000, 4096), (40000000, 9765)])
+# Work items of a window: 512 entries at least, then about 200 items of up to
+# 1,024, then what fills the chip
+@pytest.mark.parametrize("pairs,chunk", [(1000, 512), (102000, 512), (160000, 800), (220000, 1024), (500000, 1024),
+                                         (2400000, 4096), (40000000, 9765)])
 def test_work_items_of_windows(dev, pairs, chunk):
     lat = dev.build((32, 32, 32))
     dev.counts(pairs)
